@@ -1,0 +1,416 @@
+"""The work that a user of this framework has it do, as cases that can be timed.
+
+A lattice is evolved from a random-phase start with diagnostics every few steps
+(`Lattice.init`, `step_measured`, `measure`), its snapshots are written out and
+read back (`get_state`, `set_state`, `winding`), and many lattices share the
+GPU in a pool, all at once (an ensemble) or as memory frees up (a stream of
+requests).  `kind` says which:
+
+  run       a whole small simulation: start, evolution with diagnostics, final diagnostics and final fields
+  evolve    part of the evolution of a lattice that is too large to download for a look: the diagnostics series and
+            the fields at a fixed set of sites (`gather`, which is there for that; no call hands out the fields on
+            the device, and 10 GB copied to the host would be all that the case times)
+  measure   the diagnostics of the snapshot in hand (one record is all that the call returns)
+  snapshot  a checkpoint put back and written out again, with its windings (what `restore` and `dump` do)
+  ensemble  lattices of a few sizes, all in one pool, to the end
+  stream    requests of mixed sizes and both precisions through a pool that holds only some of them at a time
+
+`tuned` cases load the tuning table that comes with the package, as the
+benchmark does; the others take the automatic choice, as the scaling analysis
+and the workloads do.  Physical parameters are the defaults of `Params`.
+"""
+import math
+import random
+
+import numpy as np
+import torch
+
+import paper_2005_14454_amd as ah
+from paper_2005_14454_amd.tune import TABLE
+
+TUNED_SIZES = (32, 48, 64, 96, 128, 192, 256, 512)
+
+
+def listed():
+    return [
+        # the smallest call: a look at the diagnostics of a small ensemble member
+        {"name": "measure 32 fp32", "kind": "measure", "N": 32, "precision": "fp32", "m": 1.0, "tuned": False,
+         "warm": 40},
+        # the 64^3 workload of the paper's parameters, from the start to half the light-crossing time
+        {"name": "run 64 fp64", "kind": "run", "N": 64, "precision": "fp64", "m": 1.0, "tuned": True, "steps": 160,
+         "every": 10},
+        # a small lattice whose side fits no tile and no cache line
+        {"name": "run 50 fp32", "kind": "run", "N": 50, "precision": "fp32", "m": 2.0, "tuned": False, "steps": 115,
+         "every": 20},
+        # the benchmark lattice in both precisions
+        {"name": "evolve 512 fp32", "kind": "evolve", "N": 512, "precision": "fp32", "m": 1.0, "tuned": True,
+         "steps": 20, "every": 10, "warm": 10},
+        {"name": "evolve 512 fp64", "kind": "evolve", "N": 512, "precision": "fp64", "m": 1.0, "tuned": True,
+         "steps": 10, "every": 10, "warm": 10},
+        # the size class of a production run on one GPU, matter era, sparse diagnostics
+        {"name": "evolve 768 fp32", "kind": "evolve", "N": 768, "precision": "fp32", "m": 2.0, "tuned": False,
+         "steps": 20, "every": 20, "warm": 10},
+        # odd sides with the cadences of the scaling analysis (5) and of single runs (10)
+        {"name": "evolve 337 fp32", "kind": "evolve", "N": 337, "precision": "fp32", "m": 1.0, "tuned": False,
+         "steps": 20, "every": 5, "warm": 10},
+        {"name": "evolve 150 fp64", "kind": "evolve", "N": 150, "precision": "fp64", "m": 2.0, "tuned": False,
+         "steps": 20, "every": 10, "warm": 10},
+        # diagnostics on demand of a snapshot of medium size
+        {"name": "measure 256 fp64", "kind": "measure", "N": 256, "precision": "fp64", "m": 1.0, "tuned": False,
+         "warm": 10},
+        # a checkpoint restored and dumped, of a side such as requests have: no multiple of a cache line
+        {"name": "snapshot 90 fp32", "kind": "snapshot", "N": 90, "precision": "fp32", "m": 1.0, "tuned": False},
+        # an ensemble of small realisations in one pool
+        {"name": "ensemble 32-64 fp32", "kind": "ensemble", "count": 48, "nmin": 32, "nmax": 64, "tuned": True,
+         "steps": 60, "every": 20},
+        # a stream of requests, both precisions and expansion histories, half of them resident at a time
+        {"name": "stream 64-192", "kind": "stream", "count": 12, "nmin": 64, "nmax": 192, "tuned": False,
+         "steps": 40, "every": 10},
+    ]
+
+
+def _log_uniform(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["run", "run", "evolve", "evolve", "evolve", "evolve", "measure", "snapshot", "ensemble", "stream"])
+    case = {"kind": kind, "tuned": rng.random() < 0.4}
+    if kind in ("ensemble", "stream"):
+        many = kind == "ensemble"
+        case["count"] = rng.randint(16, 64) if many else rng.randint(6, 14)
+        case["nmin"] = rng.randint(24, 40) if many else rng.randint(48, 80)
+        case["nmax"] = case["nmin"] + (rng.randint(12, 40) if many else rng.randint(40, 120))
+        case["every"] = rng.choice([5, 10, 20])
+        case["steps"] = case["every"] * rng.randint(2, 4) + rng.randint(0, 3)
+        return case
+    fp32 = rng.random() < 0.6
+    case["precision"] = "fp32" if fp32 else "fp64"
+    case["m"] = rng.choice([1.0, 2.0])
+    lo, hi = {"run": (24, 96), "evolve": (96, 640 if fp32 else 512), "measure": (24, 320), "snapshot": (40, 90)}[kind]
+    case["N"] = _log_uniform(rng, lo, hi)
+    if kind == "snapshot" and rng.random() < 0.5:
+        case["N"] = rng.choice([64, 96, 128, 160])
+    elif case["tuned"]:  # the table holds these sides
+        case["N"] = rng.choice([n for n in TUNED_SIZES if lo <= n <= hi])
+    if kind == "run":
+        case["every"] = rng.choice([5, 10, 20])
+        case["steps"] = rng.randint(30, 160)
+    elif kind == "evolve":
+        case["every"] = rng.choice([5, 10, 20])
+        case["steps"] = case["every"] * rng.choice([1, 2]) if case["every"] > 5 else 5 * rng.randint(1, 4)
+        if case["steps"] * case["N"] ** 3 * (1 if fp32 else 2) > 20 * 768 ** 3:
+            case["steps"] = case["every"]
+        case["warm"] = 10
+    elif kind == "measure":
+        case["warm"] = rng.randint(5, 40)
+    return case
+
+
+# ------------------------------------------------------------------- inputs
+
+def _params(case):
+    return ah.Params(N=case["N"], precision=case["precision"], m=case["m"])
+
+
+def _sites(N, count=4096):
+    """Sites of the spot check of a large lattice: its first and last corner and an even spread with an odd stride."""
+    k = np.arange(count, dtype=np.int64)
+    return np.concatenate([[0, N ** 3 - 1], k * 2654435761 % N ** 3])
+
+
+def _requests(case, seed):
+    """The lattices of an ensemble or a stream: parameters, seed, steps."""
+    rng = random.Random(seed * 7919 + 17)
+    out = []
+    for k in range(case["count"]):
+        if case["kind"] == "ensemble":  # a few sizes, each many times
+            step = max(1, (case["nmax"] - case["nmin"]) // 2)
+            N = rng.choice([case["nmin"], case["nmin"] + step, case["nmax"]])
+            s = 0.0
+        else:
+            # the sizes of a batch of requests, spread evenly over the logarithm: every batch is as much work
+            u = (k + 0.5) / case["count"]
+            N = int(round(case["nmin"] * (case["nmax"] / case["nmin"]) ** u))
+            s = float(k % 2)
+        precision = "fp64" if case["kind"] == "stream" and k % 5 == 2 else "fp32"
+        out.append((dict(N=N, precision=precision, m=rng.choice([1.0, 2.0]), s_early=s, s_late=s),
+                    rng.getrandbits(62), case["steps"]))
+    if case["kind"] == "ensemble":
+        return out
+    rng.shuffle(out)
+    return out
+
+
+def _state(N, seed):
+    """A dense FP64 state of the magnitudes evolved fields have, (10, N^3)."""
+    rng = np.random.default_rng(seed)
+    st = rng.standard_normal((10, N ** 3))
+    mod = 1.0 + 0.1 * st[0]
+    ang = 2.0 * np.pi * rng.random(N ** 3)
+    st[0], st[1] = mod * np.cos(ang), mod * np.sin(ang)
+    st[2:4] *= 0.3
+    st[4:7] *= 0.6
+    st[7:10] *= 0.3
+    return st
+
+
+def prepare(case, seed):
+    ah.tune_clear()
+    if case["tuned"]:
+        ah.tune_load(TABLE)
+    kind = case["kind"]
+    if kind in ("ensemble", "stream"):
+        reqs = [(ah.Params(**p), s, n) for p, s, n in _requests(case, seed)]
+        need = [ah.pool_footprint(p, n, case["every"]) for p, _, n in reqs]
+        # the ensemble fits whole; the stream's pool holds about half of the requests
+        budget = sum(need) + (64 << 20) if kind == "ensemble" else max(max(need), sum(need) // 2) + (16 << 20)
+        return {"case": case, "pool": ah.Pool(budget, max_slots=len(reqs)), "reqs": reqs}
+    lat = ah.Lattice(_params(case))
+    state = {"case": case, "lat": lat, "seed": seed}
+    if kind == "evolve":
+        lat.init(seed)
+        lat.step(case["warm"])
+        state["sites"] = _sites(case["N"])
+    elif kind == "measure":
+        lat.init(seed)
+        lat.step(case["warm"])
+    elif kind == "snapshot":
+        state["fields"] = _state(case["N"], seed)
+    return state
+
+
+# ---------------------------------------------------------------------- run
+
+COUNTS = ("step", "winding_sum_abs", "nonfinite", "flags")
+
+
+def _columns(series):
+    """A list of measurement records as one array per quantity."""
+    return {k: np.array([m[k] for m in series], dtype=np.int64 if k in COUNTS else np.float64) for k in series[0]}
+
+
+def run(state):
+    case = state["case"]
+    kind = case["kind"]
+    if kind == "ensemble":
+        pool, left, got = state["pool"], {}, {}
+        for k, (p, seed, n) in enumerate(state["reqs"]):
+            left[pool.submit(p, seed, n, case["every"])] = k
+        while left:
+            pool.advance(16)
+            for rid in pool.poll():
+                got[left.pop(rid)] = pool.results(rid)
+        return _columns([m for k in sorted(got) for m in got[k]])
+    if kind == "stream":
+        pool, resident, got = state["pool"], {}, {}
+        waiting = list(enumerate(state["reqs"]))
+        while waiting or resident:
+            still = []
+            for k, (p, seed, n) in waiting:  # first fit in arrival order
+                rid = pool.submit(p, seed, n, case["every"])
+                if rid is None:
+                    still.append((k, (p, seed, n)))
+                else:
+                    resident[rid] = k
+            waiting = still
+            pool.advance(1)
+            for rid in pool.poll_async():
+                got[resident.pop(rid)] = pool.results(rid)
+        return _columns([m for k in sorted(got) for m in got[k]])
+    lat = state["lat"]
+    if kind == "measure":
+        return _columns([lat.measure()])
+    if kind == "snapshot":
+        lat.set_state(state["fields"], 0)
+        return {"fields": lat.get_state(), "windings": lat.winding()}
+    if kind == "run":
+        lat.init(state["seed"])
+        series = lat.step_measured(case["steps"], case["every"])
+        series.append(lat.measure())
+        return {"series": _columns(series), "fields": lat.get_state()}
+    series = lat.step_measured(case["steps"], case["every"])
+    return {"series": _columns(series), "fields": lat.gather(state["sites"])}
+
+
+# --------------------------------------------------------------------- work
+
+# Floating-point operations per site: three links (a sine and a cosine each), the covariant Laplacian and the
+# currents, three plaquettes, the curl, the potential, kick and drift; and of the diagnostics of a snapshot.
+STEP_FLOPS, MEASURE_FLOPS = 220, 350
+
+
+def work(case):
+    """State (ten fields) read once and written once; the arithmetic of every step and of every snapshot measured."""
+    if case["kind"] in ("ensemble", "stream"):
+        b = f = 0.0
+        for p, _, n in _requests(case, 0):
+            v = p["N"] ** 3
+            b += 10 * v * (4 if p["precision"] == "fp32" else 8)
+            f += v * (n * STEP_FLOPS + (n // case["every"] + 1) * MEASURE_FLOPS)
+        return {"bytes": b, "flops": f}
+    v, real = case["N"] ** 3, 4 if case["precision"] == "fp32" else 8
+    if case["kind"] == "measure":
+        return {"bytes": 10 * v * real, "flops": v * (STEP_FLOPS + MEASURE_FLOPS)}
+    if case["kind"] == "snapshot":
+        return {"bytes": 20 * v * 8 + 3 * v, "flops": v * 150}
+    first = case.get("warm", 0)
+    snaps = len([n for n in range(first, first + case["steps"]) if n % case["every"] == 0]) + (case["kind"] == "run")
+    return {"bytes": 20 * v * real, "flops": v * (case["steps"] * STEP_FLOPS + snaps * MEASURE_FLOPS)}
+
+
+# -------------------------------------------------------------------- exact
+# The discretised equations (Correia & Martins, section 2) in 64 bits with plain torch operations on whole lattices,
+# arrays indexed [z, y, x].
+
+def _i64(v):
+    return v - (1 << 64) if v >= 1 << 63 else v
+
+
+def _random_phase(N, seed, dev):
+    """phi = exp(2 pi i u), u the top 53 bits of output k of SplitMix64(seed) at site k; the other fields zero."""
+    z = torch.arange(1, N ** 3 + 1, dtype=torch.int64, device=dev) * _i64(0x9E3779B97F4A7C15) + _i64(seed % (1 << 64))
+    z = (z ^ ((z >> 30) & ((1 << 34) - 1))) * _i64(0xBF58476D1CE4E5B9)
+    z = (z ^ ((z >> 27) & ((1 << 37) - 1))) * _i64(0x94D049BB133111EB)
+    z = z ^ ((z >> 31) & ((1 << 33) - 1))
+    th = ((z >> 11) & ((1 << 53) - 1)).double().mul_(2.0 ** -53 * 2.0 * math.pi).reshape(N, N, N)
+    zero = torch.zeros_like(th)
+    return [torch.cos(th), torch.sin(th)] + [zero.clone() for _ in range(8)]
+
+
+class _Exact:
+    dx, deta, lam, e0, sigma, alpha, eta0 = 0.5, 0.1, 2.0, 1.0, 1.0, 2.0, 1.0
+
+    def __init__(self, p, seed):
+        self.N, self.m, self.s = p["N"], p["m"], p.get("s_early", 0.0)
+        dev = "cuda" if torch.cuda.is_available() else "cpu"
+        st = _random_phase(self.N, seed, dev)
+        self.phi, self.pi, self.A, self.E = st[0:2], st[2:4], st[4:7], st[7:10]
+        self.n = 0
+
+    @staticmethod
+    def up(t, d):  # value at x + k_d
+        return torch.roll(t, -1, 2 - d)
+
+    @staticmethod
+    def dn(t, d):
+        return torch.roll(t, 1, 2 - d)
+
+    def scalars(self):
+        eta = self.eta0 + self.n * self.deta
+        a = (eta / (0.5 * self.dx * self.N)) ** self.m
+        delta = 0.5 * self.alpha * self.m * self.deta / eta
+        return eta, a, a ** (2.0 * self.s), delta, (1.0 - self.s) * delta
+
+    def theta(self, i, j):
+        A = self.A
+        return self.dx * (A[i] + self.up(A[j], i) - self.up(A[i], j) - A[j])
+
+    def kick(self):
+        """Pi and E half a step on, |D+ phi|^2 summed over directions, the plaquette angles."""
+        _, _, f, delta, omega = self.scalars()
+        dx, (pr, pi) = self.dx, self.phi
+        lr, li, grad, J = -6.0 * pr, -6.0 * pi, 0.0, []
+        for d in range(3):
+            c, s = torch.cos(dx * self.A[d]), torch.sin(dx * self.A[d])  # U = c - i s
+            ur, ui = self.up(pr, d), self.up(pi, d)
+            fr, fi = c * ur + s * ui, c * ui - s * ur
+            br, bi = self.dn(c * pr - s * pi, d), self.dn(c * pi + s * pr, d)
+            lr, li = lr + fr + br, li + fi + bi
+            J.append((pr * fi - pi * fr) / dx)
+            grad = grad + ((fr - pr) ** 2 + (fi - pi) ** 2) / dx ** 2
+        pot = 0.5 * self.lam * f * (pr * pr + pi * pi - self.sigma ** 2)
+        kp = self.deta / (1 + delta)
+        npi = [(1 - delta) / (1 + delta) * q + kp * (l / dx ** 2 - pot * v)
+               for q, l, v in zip(self.pi, (lr, li), (pr, pi))]
+        th = {(i, j): self.theta(i, j) for i in range(3) for j in range(i + 1, 3)}
+        C = [0.0, 0.0, 0.0]
+        for (i, j), t in th.items():
+            F = torch.sin(t) / dx ** 2
+            C[i] = C[i] + (F - self.dn(F, j)) / dx
+            C[j] = C[j] - (F - self.dn(F, i)) / dx
+        ke = self.deta / (1 + omega)
+        nE = [(1 - omega) / (1 + omega) * e + ke * (2.0 * self.e0 ** 2 * f * j - c)
+              for e, j, c in zip(self.E, J, C)]
+        return npi, nE, grad, th
+
+    def step(self, kicked=None):
+        self.pi, self.E = (kicked or self.kick())[:2]
+        self.phi = [v + self.deta * q for v, q in zip(self.phi, self.pi)]
+        self.A = [a + self.deta * e for a, e in zip(self.A, self.E)]
+        self.n += 1
+
+    def windings(self, th):
+        (pr, pi), Y = self.phi, []
+        for d in range(3):
+            c, s = torch.cos(self.dx * self.A[d]), torch.sin(self.dx * self.A[d])
+            ur, ui = self.up(pr, d), self.up(pi, d)
+            fr, fi = c * ur + s * ui, c * ui - s * ur
+            Y.append(torch.atan2(pr * fi - pi * fr + 0.0, pr * fr + pi * fi))
+        w = 0
+        for (i, j), t in th.items():
+            tw = t - 2 * math.pi * torch.round(t / (2 * math.pi))
+            w += int(torch.round((Y[i] + self.up(Y[j], i) - self.up(Y[i], j) - Y[j] + tw) / (2 * math.pi)).abs().sum())
+        return w
+
+    def measure(self, kicked=None):
+        npi, nE, grad, th = kicked or self.kick()
+        eta, a, f, _, _ = self.scalars()
+        dx3, vol, g2 = self.dx ** 3, (self.dx * self.N) ** 3, 1.0 / (2.0 * self.e0 ** 2 * f)
+        kin = sum((0.5 * (p + q)) ** 2 for p, q in zip(self.pi, npi))
+        el = g2 * sum((0.5 * (p + q)) ** 2 for p, q in zip(self.E, nE))
+        mag = g2 * sum(4.0 * torch.sin(0.5 * t) ** 2 for t in th.values()) / self.dx ** 4
+        pot = 0.25 * self.lam * f * (self.phi[0] ** 2 + self.phi[1] ** 2 - self.sigma ** 2) ** 2
+        L = kin - grad - pot + el - mag
+        rho, prs = kin + grad + pot + el + mag, kin - grad / 3 - pot + (el + mag) / 3
+        S = lambda t: float(t.sum())  # noqa: E731
+        sum_L, R, lw = dx3 * S(L), S(kin * L) / S(grad * L), self.dx * self.windings(th)
+        out = {"eta": eta, "a": a, "f": f, "L_W": lw, "xi_W": math.sqrt(vol / lw) if lw else math.inf, "sum_L": sum_L,
+               "xi_L": math.sqrt(-2 * math.pi * self.sigma ** 2 * vol / sum_L) if sum_L < 0 else math.nan, "R": R,
+               "v2_phi": 2 * R / (1 + R), "e_kin": dx3 * S(kin), "e_grad": dx3 * S(grad), "e_pot": dx3 * S(pot),
+               "e_el": dx3 * S(el), "e_mag": dx3 * S(mag), "v2_omega": 0.5 * (1 + 3 * S(prs * L) / S(rho * L))}
+        out["energy"] = sum(out[k] for k in ("e_kin", "e_grad", "e_pot", "e_el", "e_mag"))
+        return out
+
+    def series(self, steps, every, last=True):
+        """Records of the due snapshots of `steps` steps, and of the final one."""
+        out = []
+        for _ in range(steps):
+            k = self.kick()
+            if self.n % every == 0:
+                out.append(self.measure(k))
+            self.step(k)
+        return out + ([self.measure()] if last else [])
+
+    def fields(self):
+        return [t.reshape(-1) for t in (*self.phi, *self.pi, *self.A, *self.E)]
+
+
+def _exact_columns(series):
+    """As _columns; the counts are whole numbers and the Gauss residual is rounding alone: no values for them."""
+    c = {k: np.array([m[k] for m in series]) for k in series[0]}
+    return {**c, **{k: None for k in (*COUNTS, "gauss_rms", "gauss_max", "gauss_rel")}}
+
+
+def exact(case, seed):
+    kind = case["kind"]
+    if kind in ("ensemble", "stream"):
+        out = []
+        for p, s, n in _requests(case, seed):
+            out += _Exact(p, s).series(n, case["every"])
+        return _exact_columns(out)
+    if kind == "snapshot":
+        return {"fields": _state(case["N"], seed), "windings": None}
+    if case["N"] > 520:
+        return None  # takes too long and too much memory
+    x = _Exact(case, seed)
+    for _ in range(case.get("warm", 0)):
+        x.step()
+    if kind == "measure":
+        return _exact_columns([x.measure()])
+    if kind == "run":
+        s = x.series(case["steps"], case["every"])
+        return {"series": _exact_columns(s), "fields": torch.stack(x.fields())}
+    s = x.series(case["steps"], case["every"], last=False)
+    sites = torch.from_numpy(_sites(case["N"])).to(x.phi[0].device)
+    return {"series": _exact_columns(s), "fields": torch.stack([t[sites] for t in x.fields()], 1)}
