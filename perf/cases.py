@@ -220,7 +220,7 @@ def run(state):
         return _columns([m for k in sorted(got) for m in got[k]])
     lat = state["lat"]
     if kind == "measure":
-        return _columns([lat.measure()])
+        return {k: np.float64(v) if isinstance(v, float) else v for k, v in lat.measure().items()}
     if kind == "snapshot":
         lat.set_state(state["fields"], 0)
         return {"fields": lat.get_state(), "windings": lat.winding()}
@@ -407,7 +407,7 @@ def exact(case, seed):
     for _ in range(case.get("warm", 0)):
         x.step()
     if kind == "measure":
-        return _exact_columns([x.measure()])
+        return {k: None if v is None else v[0] for k, v in _exact_columns([x.measure()]).items()}
     if kind == "run":
         s = x.series(case["steps"], case["every"])
         return {"series": _exact_columns(s), "fields": torch.stack(x.fields())}
