@@ -346,10 +346,10 @@ __global__ void __launch_bounds__(kMeasThreads) k_measure(Fields<R> f, Dims D, i
 }
 
 // Second stage: one block folds the per-block records in a fixed order.
-__global__ void __launch_bounds__(256) k_measure_final(const double* __restrict__ partials, int nblocks,
-                                                       double* __restrict__ result)
+__global__ void __launch_bounds__(kFoldThreads) k_measure_final(const double* __restrict__ partials, int nblocks,
+                                                                double* __restrict__ result)
 {
-    __shared__ double red[256];
+    __shared__ double red[kFoldRed];
     fold_records(partials, nblocks, result, red);
 }
 
@@ -418,7 +418,7 @@ hipError_t launch_measure(const Fields<R>& f, const LatticeConst& L, const StepC
 
 hipError_t launch_measure_final(const double* partials, int nblocks, double* result, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_measure_final, dim3(1), dim3(256), 0, s, partials, nblocks, result);
+    hipLaunchKernelGGL(k_measure_final, dim3(1), dim3(kFoldThreads), 0, s, partials, nblocks, result);
     return hipGetLastError();
 }
 

@@ -34,10 +34,11 @@ struct ah_handle {
     void* mom[2][5] = {};
     int curm = 0;  // current Pi/E buffer
     double* partials = nullptr;
-    double* result = nullptr;
-    double* series = nullptr;       // kSeriesCap folded records (ah_step_measured)
-    double* host_result = nullptr;  // pinned
-    double* host_series = nullptr;  // pinned, kSeriesCap records
+    // kSeriesCap folded records in pinned host memory, and the address the
+    // device knows them by: the fold writes a record (120 bytes) straight to
+    // the host, so no copy follows it
+    double* host_series = nullptr;
+    double* series = nullptr;
     int cur = 0;
     int64_t step = 0;
     bool ready = false;
@@ -200,12 +201,11 @@ size_t partial_records(const ah_params& p)
     return (size_t)(best > kMeasBlocks ? best : kMeasBlocks);
 }
 
-constexpr int kSeriesCap = 1024;  // device measurement records per ah_step_measured batch
+constexpr int kSeriesCap = 1024;  // measurement records per ah_step_measured batch
 
 size_t required_bytes(const ah_params& p)
 {
-    return 20 * field_bytes(p) + align_up(partial_records(p) * kMeasStride * sizeof(double)) +
-           align_up(kMeasStride * sizeof(double)) + align_up((size_t)kSeriesCap * kMeasStride * sizeof(double));
+    return 20 * field_bytes(p) + align_up(partial_records(p) * kMeasStride * sizeof(double));
 }
 
 template <typename R>
@@ -507,7 +507,7 @@ TileConfig meas_tiles(const ah_handle* h)
     return measured_tiling(h->p, h->cfg);
 }
 
-// Diagnostics of the current snapshot folded into dst[M_COUNT] (device), and
+// Diagnostics of the current snapshot folded into dst[M_COUNT] (a record of h->series), and
 // with `advance` the step of that snapshot in the same pass, which writes Pi
 // and E into the other buffer (the Gauss residual reads E of neighbours).
 template <typename R>
@@ -768,16 +768,12 @@ int ah_create(const ah_params* p, void* dev_arena, size_t arena_bytes, void* hip
                 base += fb;
             }
         h->partials = (double*)base;
-        base += align_up(partial_records(*p) * kMeasStride * sizeof(double));
-        h->result = (double*)base;
-        base += align_up(kMeasStride * sizeof(double));
-        h->series = (double*)base;
-        e = hipHostMalloc((void**)&h->host_result, kMeasStride * sizeof(double), hipHostMallocDefault);
-        if (e == hipSuccess)
-            e = hipHostMalloc((void**)&h->host_series, (size_t)kSeriesCap * kMeasStride * sizeof(double),
-                              hipHostMallocDefault);
+        e = hipHostMalloc((void**)&h->host_series, (size_t)kSeriesCap * kMeasStride * sizeof(double),
+                          hipHostMallocDefault);
+        if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&h->series, h->host_series, 0);
         if (e != hipSuccess) {
-            if (h->host_result) (void)hipHostFree(h->host_result);
+            (void)hipGetLastError();
+            if (h->host_series) (void)hipHostFree(h->host_series);
             if (h->owns_arena) (void)hipFree(h->arena);
             delete h;
             return AH_E_NOMEM;
@@ -786,7 +782,7 @@ int ah_create(const ah_params* p, void* dev_arena, size_t arena_bytes, void* hip
             std::string why2;
             const ah_step_config dflt{AH_KERNEL_AUTO, 0, 0, 0};
             if (resolve_config(h->p, dflt, &h->cfg, &why2) != AH_OK) {
-                (void)hipHostFree(h->host_result);
+                (void)hipHostFree(h->host_series);
                 if (h->owns_arena) (void)hipFree(h->arena);
                 delete h;
                 return AH_E_INVAL;
@@ -1008,9 +1004,7 @@ int ah_step_measured(ah_handle* h, int64_t nsteps, int32_t measure_every, ah_mea
         std::vector<int64_t> steps;
         auto flush = [&]() -> hipError_t {
             if (steps.empty()) return hipSuccess;
-            hipError_t e = hipMemcpyAsync(h->host_series, h->series, steps.size() * kMeasStride * sizeof(double),
-                                          hipMemcpyDeviceToHost, h->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+            hipError_t e = hipStreamSynchronize(h->stream);
             if (e != hipSuccess) return e;
             for (size_t j = 0; j < steps.size(); ++j)
                 to_measurement(h->p, steps[j], h->host_series + j * kMeasStride, h->V, &series[written++]);
@@ -1023,7 +1017,7 @@ int ah_step_measured(ah_handle* h, int64_t nsteps, int32_t measure_every, ah_mea
             if (h->step % measure_every == 0) {
                 if ((int)steps.size() == kSeriesCap) {
                     e = flush();
-                    if (e != hipSuccess) return hip_fail(h, e, "ah_step_measured copy");
+                    if (e != hipSuccess) return hip_fail(h, e, "ah_step_measured sync");
                 }
                 steps.push_back(h->step);
                 double* dst = h->series + (steps.size() - 1) * kMeasStride;
@@ -1036,7 +1030,7 @@ int ah_step_measured(ah_handle* h, int64_t nsteps, int32_t measure_every, ah_mea
             if (e != hipSuccess) return hip_fail(h, e, "ah_step_measured launch");
         }
         hipError_t e = flush();
-        if (e != hipSuccess) return hip_fail(h, e, "ah_step_measured copy");
+        if (e != hipSuccess) return hip_fail(h, e, "ah_step_measured sync");
         *n = written;
         return AH_OK;
     });
@@ -1072,22 +1066,20 @@ int ah_measure(ah_handle* h, ah_measurement* out)
         const ah_params& p = h->p;
         hipError_t e;
         if (p.gauge_action == AH_COMPACT) {
-            e = p.precision == AH_FP64 ? measured_pass<double>(h, h->result, false)
-                                       : measured_pass<float>(h, h->result, false);
+            e = p.precision == AH_FP64 ? measured_pass<double>(h, h->series, false)
+                                       : measured_pass<float>(h, h->series, false);
         } else {
             const StepCoef c = coef_at(p, h->step);
             const MeasConst mc = meas_const(p, h->step);
             e = p.precision == AH_FP64 ? launch_measure<double>(fields_of<double>(h, h->cur), lconst(p), c, mc,
-                                                                h->partials, h->result, h->stream)
+                                                                h->partials, h->series, h->stream)
                                        : launch_measure<float>(fields_of<float>(h, h->cur), lconst(p), c, mc,
-                                                               h->partials, h->result, h->stream);
+                                                               h->partials, h->series, h->stream);
         }
         if (e != hipSuccess) return hip_fail(h, e, "ah_measure launch");
-        e = hipMemcpyAsync(h->host_result, h->result, M_COUNT * sizeof(double), hipMemcpyDeviceToHost, h->stream);
-        if (e != hipSuccess) return hip_fail(h, e, "ah_measure copy");
         e = hipStreamSynchronize(h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "ah_measure sync");
-        to_measurement(p, h->step, h->host_result, h->V, out);
+        to_measurement(p, h->step, h->host_series, h->V, out);
         return AH_OK;
     });
 }
@@ -1168,7 +1160,6 @@ int ah_destroy(ah_handle* h)
     DeviceGuard g(h->device);
     (void)hipStreamSynchronize(h->stream);
     for (hipEvent_t ev : h->ev) (void)hipEventDestroy(ev);
-    if (h->host_result) (void)hipHostFree(h->host_result);
     if (h->host_series) (void)hipHostFree(h->host_series);
     if (h->owns_arena && h->arena) (void)hipFree(h->arena);
     delete h;

@@ -901,9 +901,9 @@ __global__ void __launch_bounds__(TX* TY, (kMinWaves<R, MEAS>)) k_step_batch(con
 
 // Fold the records of every due lattice into its measurement series (one
 // block per lattice, the same fixed order as the single-lattice fold).
-__global__ void __launch_bounds__(256) k_fold_batch(const PoolLattice* __restrict__ lat, int nlat)
+__global__ void __launch_bounds__(kFoldThreads) k_fold_batch(const PoolLattice* __restrict__ lat, int nlat)
 {
-    __shared__ double red[256];
+    __shared__ double red[kFoldRed];
     const PoolLattice& L = lat[blockIdx.x];
     const int64_t k = L.counter[0];
     if (!measure_due(L, k)) return;
@@ -1053,7 +1053,7 @@ hipError_t launch_step_batch(const PoolLattice* lat, const WorkItem* work, int n
 
 hipError_t launch_fold_batch(const PoolLattice* lat, int nlat, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_fold_batch, dim3(nlat), dim3(256), 0, s, lat, nlat);
+    hipLaunchKernelGGL(k_fold_batch, dim3(nlat), dim3(kFoldThreads), 0, s, lat, nlat);
     return hipGetLastError();
 }
 
