@@ -40,6 +40,41 @@ struct Fields {
     R* e2;
 };
 
+// The same fields as the marches take them: phi_re, phi_im, A0, A1, A2 and
+// Pi_re, Pi_im, E0, E1, E2 of the snapshot read and of the one written, each
+// five in one block with `fs` values from field to field, as every arena lays
+// them out.  Four pointers and a stride stay in a kernel's scalar registers
+// where twenty pointers spill.
+template <typename R>
+struct Blocks {
+    const R *ip, *im;
+    R *op, *om;
+    int64_t fs;
+};
+// The ten fields of two blocks with stride fs (in bytes).
+template <typename R>
+inline Fields<R> fields_at(void* pp, void* mom, size_t fs)
+{
+    char *p = (char*)pp, *m = (char*)mom;
+    return Fields<R>{(R*)p,            (R*)(p + fs),     (R*)m,            (R*)(m + fs),     (R*)(p + 2 * fs),
+                     (R*)(p + 3 * fs), (R*)(p + 4 * fs), (R*)(m + 2 * fs), (R*)(m + 3 * fs), (R*)(m + 4 * fs)};
+}
+// The blocks of a snapshot read and one written; false if the fields are not
+// so laid out.
+template <typename R>
+inline bool blocks_of(const Fields<R>& in, const Fields<R>& out, Blocks<R>* b)
+{
+    const size_t fs = (size_t)((char*)in.phi - (char*)in.phr);
+    for (const Fields<R>* f : {&in, &out}) {
+        const Fields<R> g = fields_at<R>(f->phr, f->pir, fs);
+        if (g.phi != f->phi || g.a0 != f->a0 || g.a1 != f->a1 || g.a2 != f->a2 || g.pii != f->pii || g.e0 != f->e0 ||
+            g.e1 != f->e1 || g.e2 != f->e2)
+            return false;
+    }
+    *b = Blocks<R>{in.phr, in.pir, out.phr, out.pir, (int64_t)(fs / sizeof(R))};
+    return true;
+}
+
 // Per-step scalars of the update, formed on the host in FP64 and rounded to
 // the storage type (kick: X^{n+1/2} = c1 X^{n-1/2} + c2 force).
 struct StepCoef {
@@ -150,16 +185,16 @@ TileConfig measured_tiling(const ah_params& p, const ah_step_config& cfg);
 // diagnostics records a handle holds.
 inline int min_zchunk(int N) { return N <= 128 ? 2 : 8; }
 
-// Tile shape for the measured march of a lattice stepped on (tx, ty): the
-// fastest measured march, FP32 64 x 8 and FP64 32 x 8 (the 1024-thread FP32
-// and 512-thread FP64 shapes would spill registers).  Returns whether it
-// changed.
-inline bool measured_tile(int precision, int* tx, int* ty)
+// Tile shape for the measured march of a lattice stepped on (tx, ty): 32 x 8.
+// Its four waves leave room for two workgroups per CU, which fill the chip
+// more evenly than one of eight waves (FP32 on MI355X, us per measured step
+// on 32 x 8 / 64 x 8: 512^3 3645 / 3659, 337^3 1143 / 1649, 200^3 285 / 293),
+// and the FP64 march would spill on larger ones.  Returns whether it changed.
+inline bool measured_tile(int* tx, int* ty)
 {
-    const int mx = precision == AH_FP64 ? 32 : 64, my = 8;
-    const bool changed = mx != *tx || my != *ty;
-    *tx = mx;
-    *ty = my;
+    const bool changed = *tx != 32 || *ty != 8;
+    *tx = 32;
+    *ty = 8;
     return changed;
 }
 
@@ -169,9 +204,10 @@ enum CoefSlot { C_P1 = 0, C_P2, C_E1, C_E2, C_LAMH, C_KAPPA, C_INV2E2F, C_LAMQ, 
 
 // Device-resident descriptor of one pool lattice (plain data; uploaded by the host).
 struct PoolLattice {
-    void* pp[2][5];        // ping-pong phi_re, phi_im, A0, A1, A2; counter[2] names the current one
-    void* mom[2][5];       // Pi_re, Pi_im, E0, E1, E2; counter[3] names the current one (updated in place by a
-                           // plain single step; a two-step pass and a measured step write the other)
+    void* pp[2];           // ping-pong blocks of phi_re, phi_im, A0, A1, A2; counter[2] names the current one
+    void* mom[2];          // blocks of Pi_re, Pi_im, E0, E1, E2; counter[3] names the current one (updated in place
+                           // by a plain single step; a two-step pass and a measured step write the other)
+    int64_t fs;            // values from one field of a block to the next
     const double* coef;    // (nsteps + 1) rows of kCoefStride doubles
     int64_t* counter;      // kCounterWords words: local step k, measurements taken, phi/A buffer, Pi/E buffer
     double* partials;      // diagnostics records of this lattice

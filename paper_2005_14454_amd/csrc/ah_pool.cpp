@@ -694,16 +694,9 @@ int ah_pool_submit(ah_pool* P, const ah_params* p, uint64_t seed, int64_t nsteps
         char* base = (char*)P->arena + off;
         PoolLattice& d = s.d;
         std::memset(&d, 0, sizeof(d));
-        for (int b = 0; b < 2; ++b)
-            for (int c = 0; c < 5; ++c) {
-                d.pp[b][c] = base;
-                base += fp.field;
-            }
-        for (int b = 0; b < 2; ++b)
-            for (int c = 0; c < 5; ++c) {
-                d.mom[b][c] = base;
-                base += fp.field;
-            }
+        for (int b = 0; b < 2; ++b, base += 5 * fp.field) d.pp[b] = base;
+        for (int b = 0; b < 2; ++b, base += 5 * fp.field) d.mom[b] = base;
+        d.fs = (int64_t)(fp.field / (p->precision == AH_FP64 ? 8 : 4));
         d.partials = (double*)base;
         base += fp.partials;
         double* coef = (double*)base;
@@ -740,20 +733,12 @@ int ah_pool_submit(ah_pool* P, const ah_params* p, uint64_t seed, int64_t nsteps
         hipError_t e = stage_upload(P, coef, rows.data(), rows.size() * sizeof(double));
         if (e == hipSuccess) e = hipMemsetAsync(d.counter, 0, kCounterWords * sizeof(int64_t), P->stream);
         if (e == hipSuccess) {
-            Fields<double> f64;
-            Fields<float> f32;
-            if (p->precision == AH_FP64) {
-                f64 = Fields<double>{(double*)d.pp[0][0], (double*)d.pp[0][1], (double*)d.mom[0][0],
-                                     (double*)d.mom[0][1], (double*)d.pp[0][2], (double*)d.pp[0][3],
-                                     (double*)d.pp[0][4], (double*)d.mom[0][2], (double*)d.mom[0][3],
-                                     (double*)d.mom[0][4]};
-                e = launch_init<double>(f64, p->N, d.P, p->sigma, seed, P->stream);
-            } else {
-                f32 = Fields<float>{(float*)d.pp[0][0], (float*)d.pp[0][1], (float*)d.mom[0][0], (float*)d.mom[0][1],
-                                    (float*)d.pp[0][2], (float*)d.pp[0][3], (float*)d.pp[0][4], (float*)d.mom[0][2],
-                                    (float*)d.mom[0][3], (float*)d.mom[0][4]};
-                e = launch_init<float>(f32, p->N, d.P, p->sigma, seed, P->stream);
-            }
+            if (p->precision == AH_FP64)
+                e = launch_init<double>(fields_at<double>(d.pp[0], d.mom[0], fp.field), p->N, d.P, p->sigma, seed,
+                                        P->stream);
+            else
+                e = launch_init<float>(fields_at<float>(d.pp[0], d.mom[0], fp.field), p->N, d.P, p->sigma, seed,
+                                       P->stream);
         }
         if (e != hipSuccess) {
             arena_free(P, s.off, s.bytes);
@@ -900,9 +885,10 @@ int ah_pool_get_state(ah_pool* P, int64_t id, double* host_soa, int64_t* step)
         const int cur = (int)c[2], curm = (int)c[3];  // the buffers of snapshot k
         const size_t V = (size_t)s->p.N * s->p.N * s->p.N;
         const size_t rb = s->p.precision == AH_FP64 ? 8 : 4;
-        void* const* m = s->d.mom[curm];
-        void* comps[10] = {s->d.pp[cur][0], s->d.pp[cur][1], m[0], m[1], s->d.pp[cur][2],
-                           s->d.pp[cur][3], s->d.pp[cur][4], m[2], m[3], m[4]};
+        const size_t fs = (size_t)s->d.fs * rb;
+        char *q = (char*)s->d.pp[cur], *m = (char*)s->d.mom[curm];
+        void* comps[10] = {q,          q + fs,     m,          m + fs,     q + 2 * fs,
+                           q + 3 * fs, q + 4 * fs, m + 2 * fs, m + 3 * fs, m + 4 * fs};
         std::vector<float> tmp(rb == 4 ? V : 0);
         for (int cc = 0; cc < 10; ++cc) {
             double* dst = host_soa + cc * V;

@@ -370,7 +370,7 @@ int auto_zchunk(int kernel, int precision, int N, int tx, int ty, bool measured)
 
 // Any tile shape computes the same fields bit for bit, so the measured march
 // may run another shape than the plain step: the fastest measured march
-// (measured_tile: FP32 64 x 8, FP64 32 x 8), with the step's z-chunk when
+// (measured_tile: 32 x 8), with the step's z-chunk when
 // the step runs that shape too, else the automatic z-chunk of the measured
 // march but no shorter than the step's (a pool's floor of 16 planes then
 // holds for its measured node too).  A lattice of the site kernel takes the
@@ -381,7 +381,7 @@ TileConfig measured_tiling(const ah_params& p, const ah_step_config& cfg)
 {
     int tx = cfg.tile_x, ty = cfg.tile_y;
     const bool tiled = cfg.kernel == AH_KERNEL_TILE || cfg.kernel == AH_KERNEL_TILE2;
-    if (!measured_tile(p.precision, &tx, &ty) && tiled) return TileConfig{tx, ty, cfg.zchunk};
+    if (!measured_tile(&tx, &ty) && tiled) return TileConfig{tx, ty, cfg.zchunk};
     int zc = auto_zchunk(AH_KERNEL_TILE, p.precision, p.N, tx, ty, true);
     if (tiled && cfg.zchunk > zc) zc = std::min(cfg.zchunk, p.N);
     return TileConfig{tx, ty, zc};

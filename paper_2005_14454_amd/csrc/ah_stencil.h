@@ -15,6 +15,19 @@
 #pragma clang fp contract(off)
 
 namespace ah {
+
+// A buffer descriptor (raw buffer, stride 0) and the buffer instructions on
+// it.  The descriptor is written out word by word: a device address has no
+// bits above 47, so its words are the address, the length and the format, and
+// stepping to the next field is one 64-bit scalar addition.
+typedef int Rsrc __attribute__((ext_vector_type(4)));
+typedef float Float2 __attribute__((ext_vector_type(2)));
+extern __device__ float buf_load_f32(Rsrc r, int voff, int soff, int aux) __asm("llvm.amdgcn.raw.buffer.load.f32");
+extern __device__ Float2 buf_load_2f32(Rsrc r, int voff, int soff, int aux) __asm("llvm.amdgcn.raw.buffer.load.v2f32");
+extern __device__ void buf_store_f32(float v, Rsrc r, int voff, int soff, int aux) __asm("llvm.amdgcn.raw.buffer.store.f32");
+extern __device__ void buf_store_2f32(Float2 v, Rsrc r, int voff, int soff, int aux) __asm("llvm.amdgcn.raw.buffer.store.v2f32");
+constexpr int kBufNt = 2;  // aux: non-temporal
+
 namespace {
 
 __device__ inline float fm(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
@@ -35,28 +48,53 @@ __device__ inline T uniform(T v)
 }
 __device__ inline double fm(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// Streaming accesses: Pi and E are read and written once per step at their
-// own site, phi and A are written once into the other ping-pong buffer; none
-// of it is reused from cache within a step, so they bypass it and leave L2 to
-// the phi / A halo lines that neighbouring tiles read again.
-template <typename R>
-__device__ inline R ld_stream(const R* p)
-{
-    return __builtin_nontemporal_load(p);
-}
-template <typename R>
-__device__ inline void st_stream(R* p, R v)
-{
-    __builtin_nontemporal_store(v, p);
-}
+// Access to one plane of a field through a buffer descriptor of exactly that
+// plane: its base in scalar registers and a 32-bit byte offset per lane, so an
+// access costs no vector address arithmetic and holds no 64-bit vector
+// addresses (the FP64 step march takes 150 registers rather than 186).  An
+// offset of kNoSite is past the plane's end: the store is dropped.  That keeps
+// lanes without a site from storing with no branch, which matters for the
+// waits: loads and stores share one in-order counter, and behind a store that
+// may have been skipped the compiler can only wait for everything, i.e. each
+// plane of a march would wait for its own streaming stores to reach memory.
+//
+// Pi and E are read and written once per step at their own site, phi and A
+// are written once into the other ping-pong buffer; none of it is reused from
+// cache within a step, so those accesses (STREAM) are non-temporal and leave
+// L2 to the phi / A halo lines that neighbouring tiles read again.
+constexpr uint32_t kNoSite = 0xffffffffu;
 
-// base[plane + xy] with a uniform plane offset and a 32-bit in-plane index:
-// the load adds the plane base, held in scalar registers, and one vector
-// offset, with no 64-bit address arithmetic per access.
+// s_waitcnt operand (gfx9 encoding): vmcnt(0), the other counters unconstrained
+constexpr int kWaitVm0 = 0x0f70;
+
+enum { B_PHR = 0, B_PHI = 1, B_PIR = 0, B_PII = 1, B_A = 2, B_E = 2 };
+
+// Descriptors of one plane of the five fields of a block; `bytes`: the
+// plane's length, at most 4096 x 4096 x 8.
+struct PlaneBufs {
+    Rsrc f[5];
+};
 template <typename R>
-__device__ inline R at(const R* base, int64_t plane, uint32_t xy)
+__device__ inline PlaneBufs plane_bufs(const R* block, int64_t fs, int64_t plane, uint32_t bytes)
 {
-    return (base + plane)[xy];
+    PlaneBufs b;
+    uint64_t q = (uint64_t)(block + plane);
+    for (int k = 0; k < 5; ++k, q += (uint64_t)fs * sizeof(R))
+        b.f[k] = Rsrc{(int)(uint32_t)q, (int)(uint32_t)(q >> 32), (int)bytes, 0x00020000};  // 32-bit data
+    return b;
+}
+template <typename R, bool STREAM = false>
+__device__ inline R ld_plane(Rsrc r, uint32_t off)
+{
+    if constexpr (sizeof(R) == 4)
+        return buf_load_f32(r, (int)off, 0, STREAM ? kBufNt : 0);
+    else
+        return __builtin_bit_cast(R, buf_load_2f32(r, (int)off, 0, STREAM ? kBufNt : 0));
+}
+__device__ inline void st_plane(Rsrc r, uint32_t off, float v) { buf_store_f32(v, r, (int)off, 0, kBufNt); }
+__device__ inline void st_plane(Rsrc r, uint32_t off, double v)
+{
+    buf_store_2f32(__builtin_bit_cast(Float2, v), r, (int)off, 0, kBufNt);
 }
 
 template <typename R>
@@ -74,58 +112,65 @@ __device__ inline Cx<R> cmulc(Cx<R> a, Cx<R> b)  // conj(a) * b
     return {fm(a.r, b.r, a.i * b.i), fm(a.r, b.i, -(a.i * b.r))};
 }
 
-// FP64 links: the reduced-range sincos (accurate to ~2 ulp for |x| <= 1e9),
-// the library routine beyond that (out of line: a link phase past 1e9 is a
-// lattice long blown up, and inlined it would cost the march registers)
+// Links U_j = exp(-i dx A_j) = (cos(dx A_j), -sin(dx A_j)) of K values of A.
+//
+// FP64: the reduced-range sincos (accurate to ~2 ulp for |x| <= 1e9), the
+// library routine beyond that (out of line, with the in-range ones of the K
+// left as they are: a link phase past 1e9 is a lattice long blown up, and
+// inlined it would cost the march registers).
 __device__ __noinline__ double2 sincos_far(double x)
 {
     double2 v;
     sincos(x, &v.x, &v.y);
     return v;
 }
-__device__ inline void sincos_t(double x, double* s, double* c)
+template <int K>
+__device__ inline void links(double dx, const double (&a)[K], Cx<double> (&u)[K])
 {
-    if (fabs(x) <= 1e9) {
-        sincos_reduced(x, s, c);
-    } else {
-        const double2 v = sincos_far(x);
-        *s = v.x;
-        *c = v.y;
+    double x[K], far = 0.0;
+    for (int d = 0; d < K; ++d) {
+        x[d] = dx * a[d];
+        double s, c;
+        sincos_reduced(x[d], &s, &c);
+        u[d] = {c, -s};
+        far = fmax(far, fabs(x[d]));
     }
+    // one test for all of them (a NaN, which either way gives NaN, passes)
+    if (far > 1e9)
+        for (int d = 0; d < K; ++d)
+            if (fabs(x[d]) > 1e9) {
+                const double2 v = sincos_far(x[d]);
+                u[d] = {v.y, -v.x};
+            }
 }
-// FP32 links: the argument is reduced by whole turns with 2 pi split in
-// three parts (Cody and Waite; the first two, 6.28125 and 1.9378662109375e-3,
-// have at most 8 significant bits, so k times them is exact for |k| < 2^16
-// turns), the remainder in [-pi, pi] is converted to turns and given to the
-// hardware sine and cosine of one turn.  Within about 3e-7 of the FP64 sine
-// and cosine of the same FP32 argument for |x| < 4e5 (the library sincosf is
-// within 7e-8 but costs three times the instructions).  Beyond that (a link
-// phase that large is a lattice long blown up) the turns are split off in
-// FP64.
-__device__ inline void sincos_t(float x, float* s, float* c)
+// FP32: the argument is reduced by whole turns with 2 pi split in three parts
+// (Cody and Waite; the first two, 6.28125 and 1.9378662109375e-3, have at
+// most 8 significant bits, so k times them is exact for |k| < 2^16 turns),
+// the remainder in [-pi, pi] is converted to turns and given to the hardware
+// sine and cosine of one turn.  Within about 3e-7 of the FP64 sine and cosine
+// of the same FP32 argument for |x| < 4e5 (the library sincosf is within 7e-8
+// but costs three times the instructions).  Beyond that (a link phase that
+// large is a lattice long blown up) the turns are split off in FP64.
+template <int K>
+__device__ inline void links(float dx, const float (&a)[K], Cx<float> (&u)[K])
 {
-    float t;
-    if (fabsf(x) < 4.0e5f) {
-        const float k = __builtin_rintf(x * 0.15915494309189535f);
-        float r = fm(-k, 6.28125f, x);
+    float x[K], t[K], far = 0.f;
+    for (int d = 0; d < K; ++d) {
+        x[d] = dx * a[d];
+        const float k = __builtin_rintf(x[d] * 0.15915494309189535f);
+        float r = fm(-k, 6.28125f, x[d]);
         r = fm(-k, 1.9378662109375e-3f, r);
         r = fm(-k, -2.5590314e-6f, r);
-        t = r * 0.15915494309189535f;
-    } else {
-        const double u = (double)x * 0.15915494309189535;
-        t = (float)(u - __builtin_rint(u));
+        t[d] = r * 0.15915494309189535f;
+        far = fmaxf(far, fabsf(x[d]));
     }
-    *s = __builtin_amdgcn_sinf(t);
-    *c = __builtin_amdgcn_cosf(t);
-}
-
-// link U = exp(-i dx A) = (cos(dx A), -sin(dx A))
-template <typename R>
-__device__ inline Cx<R> link(R dx, R a)
-{
-    R s, c;
-    sincos_t(dx * a, &s, &c);
-    return {c, -s};
+    if (far >= 4.0e5f)
+        for (int d = 0; d < K; ++d)
+            if (fabsf(x[d]) >= 4.0e5f) {
+                const double w = (double)x[d] * 0.15915494309189535;
+                t[d] = (float)(w - __builtin_rint(w));
+            }
+    for (int d = 0; d < K; ++d) u[d] = {__builtin_amdgcn_cosf(t[d]), -__builtin_amdgcn_sinf(t[d])};
 }
 
 // -Im(p conj(q)) with p = U_i^x U_j^{x+i}, q = U_i^{x+j} U_j^x: sin(Theta_ij)
@@ -137,6 +182,12 @@ __device__ inline R plaq_sin(Cx<R> ui_x, Cx<R> uj_xi, Cx<R> ui_xj, Cx<R> uj_x)
     return fm(p.r, q.i, -(p.i * q.r));
 }
 
+// Periodic image in [0, N) of a plane within N of that range.
+__device__ inline int wrapz(int z, int N)
+{
+    if (z < 0) return z + N;
+    return z < N ? z : z - N;
+}
 __device__ inline int wrapi(int v, int N)
 {
     // v in [-2, 2N + TX]: periodic image in [0, N)

@@ -40,7 +40,7 @@ struct Geom2 {
     static constexpr int NRING = S1 - NT;                         // R1 ring sites
     static constexpr int NTH = NT + (NRING + 63) / 64 * 64;       // threads (ring in whole waves)
     static constexpr int NOUT = S2 - S1;                          // R2 outer ring sites
-    static_assert(NOUT <= NTH, "one outer-ring site per thread at most");
+    static_assert(NOUT <= NTH - NT, "one outer-ring site per ring thread at most");
 };
 
 // LDS of one workgroup.  Stage-1 links and phi live on R2, stage-2 ones on
@@ -58,8 +58,7 @@ struct Shared2 {
 
 template <typename R>
 struct Step2Args {
-    Fields<R> in;   // snapshot n
-    Fields<R> out;  // snapshot n+2
+    Blocks<R> b;  // snapshots n (read) and n+2 (written)
     int N, P;  // side, row pitch: site (x, y, z) at x + P (y + N z)
     SiteCoef<R> k0, k1;  // coefficients of steps n and n+1
     R dx;
@@ -103,34 +102,37 @@ constexpr int kStep2Threads = Geom2<TX, TY>::NTH;
 template <typename R, int TX, int TY>
 constexpr int kStep2MinWaves = sizeof(R) == 8 ? 2 : (Geom2<TX, TY>::NTH <= 384 ? 4 : 3);
 
-// Two steps of planes [z0, z1) of the tile whose lower corner is (x0, y0).
-// All threads of the workgroup call this with the same arguments.
-template <typename R, int TX, int TY>
-__device__ __forceinline__ void march2(Shared2<R, TX, TY>& sh, const Step2Args<R>& a, int x0, int y0, int z0, int z1)
+// Two steps of planes [z0, z1) of the tile whose lower corner is (x0, y0), as
+// the waves that own tile sites (TILE) or ring sites run them.  All threads of
+// the workgroup call this with the same arguments but TILE, which is the same
+// for every lane of a wave; both kinds pass the same barriers.
+template <typename R, int TX, int TY, bool TILE>
+__device__ __forceinline__ void march2_role(Shared2<R, TX, TY>& sh, const Step2Args<R>& a, int x0, int y0, int z0,
+                                            int z1)
 {
     using G = Geom2<TX, TY>;
     constexpr int W1 = G::W1, H1 = G::H1, W2 = G::W2, H2 = G::H2, NT = G::NT;
 
     const int N = a.N, P = a.P;
     const int64_t NN = (int64_t)N * P;  // plane stride
+    const uint32_t pb = (uint32_t)NN * (uint32_t)sizeof(R);  // bytes of a plane (N P < 2^28)
     const R dx = a.dx;
-    const Fields<R>& f = a.in;
     // 1/dx and 1/dx^2 formed on the device as the single-step march forms them
     SiteCoef<R> k0 = a.k0, k1 = a.k1;
     k0.inv_dx = k1.inv_dx = R(1) / dx;
     k0.inv_dx2 = k1.inv_dx2 = k0.inv_dx * k0.inv_dx;
 
-    // ---- roles: R1 position (stage 1) of every thread that has one; tile
-    //      threads also own a stage-2 site; threads < NOUT one R2 outer site
+    // ---- roles: every thread has an R1 position (stage 1); a tile thread
+    //      also owns the stage-2 site there, a ring thread also one R2 outer
+    //      site.  The lanes left over in the last ring wave repeat its last
+    //      sites (the same values into the same slots).
     const int tid = threadIdx.x;
-    const bool is_tile = tid < NT;
-    int rx = 0, ry = 0;
-    bool has1 = true;
-    if (is_tile) {
+    int rx, ry, ox = 0, oy = 0;
+    if constexpr (TILE) {
         rx = tid % TX + 1;
         ry = tid / TX + 1;
     } else {
-        const int r = tid - NT;
+        const int r = min(tid - NT, G::NRING - 1);
         if (r < W1) {
             rx = r;
             ry = 0;
@@ -140,51 +142,50 @@ __device__ __forceinline__ void march2(Shared2<R, TX, TY>& sh, const Step2Args<R
         } else if (r < 2 * W1 + TY) {
             rx = 0;
             ry = 1 + (r - 2 * W1);
-        } else if (r < G::NRING) {
+        } else {
             rx = W1 - 1;
             ry = 1 + (r - 2 * W1 - TY);
-        } else {
-            has1 = false;  // padding lane of the last ring wave
         }
-    }
-    const bool has_out = tid < G::NOUT;
-    int ox = 0, oy = 0;
-    if (has_out) {
-        if (tid < W2) {
-            ox = tid;
+        const int o = min(tid - NT, G::NOUT - 1);
+        if (o < W2) {
+            ox = o;
             oy = 0;
-        } else if (tid < 2 * W2) {
-            ox = tid - W2;
+        } else if (o < 2 * W2) {
+            ox = o - W2;
             oy = H2 - 1;
-        } else if (tid < 2 * W2 + (H2 - 2)) {
+        } else if (o < 2 * W2 + (H2 - 2)) {
             ox = 0;
-            oy = 1 + (tid - 2 * W2);
+            oy = 1 + (o - 2 * W2);
         } else {
             ox = W2 - 1;
-            oy = 1 + (tid - 2 * W2 - (H2 - 2));
+            oy = 1 + (o - 2 * W2 - (H2 - 2));
         }
     }
     const int c1 = rx + W1 * ry;              // R1 index of the stage-1 site
     const int c2 = (rx + 1) + W2 * (ry + 1);  // its R2 index
     const int co = ox + W2 * oy;              // R2 index of the outer site
-    const int64_t xy1 = has1 ? (int64_t)wrapi(x0 - 1 + rx, N) + (int64_t)P * wrapi(y0 - 1 + ry, N) : 0;
-    const int64_t xyo = (int64_t)wrapi(x0 - 2 + ox, N) + (int64_t)P * wrapi(y0 - 2 + oy, N);
-    const int gx = x0 + rx - 1, gy = y0 + ry - 1;
-    const bool active = is_tile && gx < N && gy < N;
-    const int64_t own_xy = xy1;
+    // byte offsets in a plane: of the stage-1 site, of the outer site, and for
+    // the stores (kNoSite for lanes past a ragged edge)
+    const uint32_t ob = ((uint32_t)wrapi(x0 - 1 + rx, N) + (uint32_t)P * (uint32_t)wrapi(y0 - 1 + ry, N)) *
+                        (uint32_t)sizeof(R);
+    const uint32_t oo = ((uint32_t)wrapi(x0 - 2 + ox, N) + (uint32_t)P * (uint32_t)wrapi(y0 - 2 + oy, N)) *
+                        (uint32_t)sizeof(R);
+    const uint32_t so = x0 + rx - 1 < N && y0 + ry - 1 < N ? ob : kNoSite;
 
-    auto plane_of = [&](int z) -> int64_t { return (int64_t)wrapi(z, N) * NN; };
-    const R* A[3] = {f.a0, f.a1, f.a2};
+    auto plane_of = [&](int z) -> int64_t { return (int64_t)wrapz(z, N) * NN; };
+    auto in_p = [&](int64_t plane) { return plane_bufs(a.b.ip, a.b.fs, plane, pb); };
+    auto in_m = [&](int64_t plane) { return plane_bufs(a.b.im, a.b.fs, plane, pb); };
+    auto ld = [](Rsrc r, uint32_t off) -> R { return ld_plane<R>(r, off); };
 
     // ---- stage-1 column state (snapshot n at the stage-1 site).  The
     //      site's own links of planes p and p+1 are read back from LDS.
-    R ac[3], ap[3];          // A at planes p, p+1
-    Cx<R> upz;               // U_z at plane p+1 (into LDS once plane p is done)
-    Cx<R> uz_m;              // U_z at plane p-1
-    R fxz_m = 0, fyz_m = 0;  // F_xz, F_yz at plane p-1
-    Cx<R> phm, phc, php;     // phi at planes p-1, p, p+1
-    R pr, pi, e[3];          // Pi, E at plane p
-    Cx<R> uo_z;              // outer site: U_z of the plane above the one in u0z
+    R ac[3], ap[3];      // A at planes p, p+1
+    Cx<R> upz;           // U_z at plane p+1 (into LDS once plane p is done)
+    Cx<R> uz_m;          // U_z at plane p-1
+    R fxz_m, fyz_m;      // F_xz, F_yz at plane p-1
+    Cx<R> phm, phc, php; // phi at planes p-1, p, p+1
+    R pr, pi, e[3];      // Pi, E at plane p
+    Cx<R> uo_z = {};     // outer site: U_z of the plane above the one in u0z
     // ---- stage-2 column state (snapshot n+1 at the tile site); the site's
     //      Pi, E and A come from stage 1 through LDS
     Cx<R> vz_m = {};         // U_z^{n+1} at q-1
@@ -194,109 +195,109 @@ __device__ __forceinline__ void march2(Shared2<R, TX, TY>& sh, const Step2Args<R
     // plane p-1 (its x, y links go there at once)
     Cx<R> s1phi = {}, s1z = {};
 
+    // Operands loaded one iteration ahead: A of plane p+2 (stage-1 site and
+    // outer site), phi of plane p+2 (stage-1 site) and p+1 (outer site), Pi
+    // and E of plane p+1 (stage-1 site).
+    R na[3], noa[3] = {0, 0, 0}, npr, npi, ne[3];
+    Cx<R> nph, noph = {};
+    auto prefetch = [&](int p) {
+        const int64_t p1 = plane_of(p + 1);
+        const PlaneBufs f2 = in_p(plane_of(p + 2));
+        for (int d = 0; d < 3; ++d) na[d] = ld(f2.f[B_A + d], ob);
+        if constexpr (!TILE) {
+            for (int d = 0; d < 3; ++d) noa[d] = ld(f2.f[B_A + d], oo);
+            const PlaneBufs f1 = in_p(p1);
+            noph = Cx<R>{ld(f1.f[B_PHR], oo), ld(f1.f[B_PHI], oo)};
+        }
+        nph = Cx<R>{ld(f2.f[B_PHR], ob), ld(f2.f[B_PHI], ob)};
+        const PlaneBufs m1 = in_m(p1);
+        npr = ld(m1.f[B_PIR], ob);
+        npi = ld(m1.f[B_PII], ob);
+        for (int d = 0; d < 3; ++d) ne[d] = ld(m1.f[B_E + d], ob);
+    };
+
     // ------------------------------------------------------------ prologue
-    // plane zm = z0-2: U_z on R2 into u0z (for F^n at z0-2), own x, y links
+    // Every load of the prologue, and those of the first iteration, are
+    // issued before its first barrier: a chunk then starts with one round of
+    // memory latency.
     {
         const int64_t pm2 = plane_of(z0 - 2), pm1 = plane_of(z0 - 1), p0 = plane_of(z0);
-        Cx<R> um2[3];
-        if (has1) {
-            for (int d = 0; d < 3; ++d) um2[d] = link(dx, A[d][pm2 + own_xy]);
-            sh.u0z[c2] = um2[2];
-            uz_m = um2[2];
+        R am2[3], om[7] = {0, 0, 0, 0, 0, 0, 0};  // om: A_z at z0-2, A at z0-1, A at z0 of the outer site
+        Cx<R> oph = {};
+        const PlaneBufs fm2 = in_p(pm2), fm1 = in_p(pm1), f0 = in_p(p0), mm1 = in_m(pm1);
+        for (int d = 0; d < 3; ++d) am2[d] = ld(fm2.f[B_A + d], ob);
+        for (int d = 0; d < 3; ++d) ac[d] = ld(fm1.f[B_A + d], ob);
+        for (int d = 0; d < 3; ++d) ap[d] = ld(f0.f[B_A + d], ob);
+        if constexpr (!TILE) {
+            om[0] = ld(fm2.f[B_A + 2], oo);
+            for (int d = 0; d < 3; ++d) om[1 + d] = ld(fm1.f[B_A + d], oo);
+            for (int d = 0; d < 3; ++d) om[4 + d] = ld(f0.f[B_A + d], oo);
+            oph = Cx<R>{ld(fm1.f[B_PHR], oo), ld(fm1.f[B_PHI], oo)};
         }
-        if (has_out) sh.u0z[co] = link(dx, A[2][pm2 + xyo]);
-        // plane z0-1 links: x, y into their slot, z held
+        phm = Cx<R>{ld(fm2.f[B_PHR], ob), ld(fm2.f[B_PHI], ob)};
+        phc = Cx<R>{ld(fm1.f[B_PHR], ob), ld(fm1.f[B_PHI], ob)};
+        php = Cx<R>{ld(f0.f[B_PHR], ob), ld(f0.f[B_PHI], ob)};
+        pr = ld(mm1.f[B_PIR], ob);
+        pi = ld(mm1.f[B_PII], ob);
+        for (int d = 0; d < 3; ++d) e[d] = ld(mm1.f[B_E + d], ob);
+        prefetch(z0 - 1);
+
+        // plane z0-2: U_z on R2 into u0z (for F^n at z0-2), own x, y links;
+        // plane z0-1: x, y links into their slot, z held, phi
         const int s_m1 = (z0 - 1) & 1, s_0 = z0 & 1;
-        Cx<R> uc[3];
-        if (has1) {
-            for (int d = 0; d < 3; ++d) {
-                ac[d] = A[d][pm1 + own_xy];
-                uc[d] = link(dx, ac[d]);
-            }
-            sh.u0x[s_m1][c2] = uc[0];
-            sh.u0y[s_m1][c2] = uc[1];
-            phm = Cx<R>{f.phr[pm2 + own_xy], f.phi[pm2 + own_xy]};
-            phc = Cx<R>{f.phr[pm1 + own_xy], f.phi[pm1 + own_xy]};
-            php = Cx<R>{f.phr[p0 + own_xy], f.phi[p0 + own_xy]};
-            sh.p0[c2] = phc;
+        Cx<R> um2[3], uc[3], up[3], uo[7];
+        links(dx, am2, um2);
+        sh.u0z[c2] = um2[2];
+        uz_m = um2[2];
+        links(dx, ac, uc);
+        sh.u0x[s_m1][c2] = uc[0];
+        sh.u0y[s_m1][c2] = uc[1];
+        sh.p0[c2] = phc;
+        if constexpr (!TILE) {
+            links(dx, om, uo);
+            sh.u0z[co] = uo[0];
+            sh.u0x[s_m1][co] = uo[1];
+            sh.u0y[s_m1][co] = uo[2];
+            sh.p0[co] = oph;
         }
-        Cx<R> uo_m1z = {};
-        if (has_out) {
-            sh.u0x[s_m1][co] = link(dx, A[0][pm1 + xyo]);
-            sh.u0y[s_m1][co] = link(dx, A[1][pm1 + xyo]);
-            uo_m1z = link(dx, A[2][pm1 + xyo]);
-            sh.p0[co] = Cx<R>{f.phr[pm1 + xyo], f.phi[pm1 + xyo]};
-        }
+        links(dx, ap, up);
         __syncthreads();
         // F^n_xz, F^n_yz at z0-2 of the stage-1 site
-        if (has1) {
-            fxz_m = plaq_sin(um2[0], sh.u0z[c2 + 1], uc[0], um2[2]) * k0.inv_dx2;
-            fyz_m = plaq_sin(um2[1], sh.u0z[c2 + W2], uc[1], um2[2]) * k0.inv_dx2;
-        }
+        fxz_m = plaq_sin(um2[0], sh.u0z[c2 + 1], uc[0], um2[2]) * k0.inv_dx2;
+        fyz_m = plaq_sin(um2[1], sh.u0z[c2 + W2], uc[1], um2[2]) * k0.inv_dx2;
         __syncthreads();
         // U_z of z0-1 into u0z; plane z0 links: x, y into their slot, z held
-        if (has1) {
-            sh.u0z[c2] = uc[2];
-            for (int d = 0; d < 3; ++d) ap[d] = A[d][p0 + own_xy];
-            sh.u0x[s_0][c2] = link(dx, ap[0]);
-            sh.u0y[s_0][c2] = link(dx, ap[1]);
-            upz = link(dx, ap[2]);
-            pr = f.pir[pm1 + own_xy];
-            pi = f.pii[pm1 + own_xy];
-            e[0] = f.e0[pm1 + own_xy];
-            e[1] = f.e1[pm1 + own_xy];
-            e[2] = f.e2[pm1 + own_xy];
-        }
-        if (has_out) {
-            sh.u0z[co] = uo_m1z;
-            sh.u0x[s_0][co] = link(dx, A[0][p0 + xyo]);
-            sh.u0y[s_0][co] = link(dx, A[1][p0 + xyo]);
-            uo_z = link(dx, A[2][p0 + xyo]);
+        sh.u0z[c2] = uc[2];
+        sh.u0x[s_0][c2] = up[0];
+        sh.u0y[s_0][c2] = up[1];
+        upz = up[2];
+        if constexpr (!TILE) {
+            sh.u0z[co] = uo[3];
+            sh.u0x[s_0][co] = uo[4];
+            sh.u0y[s_0][co] = uo[5];
+            uo_z = uo[6];
         }
         __syncthreads();
     }
 
-    // Operands loaded one iteration ahead: A of plane p+2 (stage-1 site and
-    // outer site), phi of plane p+2 (stage-1 site) and p+1 (outer site), Pi
-    // and E of plane p+1 (stage-1 site).
-    R na[3] = {0, 0, 0}, noa[3] = {0, 0, 0}, npr = 0, npi = 0, ne[3] = {0, 0, 0};
-    Cx<R> nph = {}, noph = {};
-
     for (int p = z0 - 1; p <= z1; ++p) {
         const bool more = p < z1;
-        if (more) {
-            const int64_t p2 = plane_of(p + 2), p1 = plane_of(p + 1);
-            if (has1) {
-                for (int d = 0; d < 3; ++d) na[d] = A[d][p2 + own_xy];
-                nph = Cx<R>{f.phr[p2 + own_xy], f.phi[p2 + own_xy]};
-                npr = f.pir[p1 + own_xy];
-                npi = f.pii[p1 + own_xy];
-                ne[0] = f.e0[p1 + own_xy];
-                ne[1] = f.e1[p1 + own_xy];
-                ne[2] = f.e2[p1 + own_xy];
-            }
-            if (has_out) {
-                for (int d = 0; d < 3; ++d) noa[d] = A[d][p2 + xyo];
-                noph = Cx<R>{f.phr[p1 + xyo], f.phi[p1 + xyo]};
-            }
-        }
+        if (more && p > z0 - 1) prefetch(p);
         const int sp = p & 1, sq = sp ^ 1;  // LDS slots of planes p (and p+2) and p+1 (and p-1)
 
         // ---- (a) stage 1 at plane p; the previous plane's phi and U_z of
         //      snapshot n+1 go into LDS first (stage 2 reads them this time)
-        if (has1) {
-            if (p > z0 - 1) {
-                if (is_tile) chm = sh.p1[c1];  // phi^{n+1} of plane p-2, before it is replaced
-                sh.p1[c1] = s1phi;
-                sh.u1z[c1] = s1z;
-            }
+        {
+            if (TILE) chm = sh.p1[c1];  // phi^{n+1} of plane p-2, before it is replaced
+            sh.p1[c1] = s1phi;
+            sh.u1z[c1] = s1z;
             const Cx<R> uc[3] = {sh.u0x[sp][c2], sh.u0y[sp][c2], sh.u0z[c2]};
             const SiteNbr<R> nb = gather_nbr<R, W2>(c2, sh.u0x[sp], sh.u0y[sp], sh.u0z, sh.p0, sh.u0x[sq], sh.u0y[sq]);
             const SiteOut<R> o = site_update(k0, nb, phm, phc, php, uc, sh.u0x[sq][c2], sh.u0y[sq][c2], uz_m, fxz_m,
                                              fyz_m, pr, pi, e, ac);
             fxz_m = o.fxz;
             fyz_m = o.fyz;
-            if (is_tile) {
+            if constexpr (TILE) {
                 R* h = &sh.h1[sp][0][tid];
                 h[0 * NT] = o.pr;
                 h[1 * NT] = o.pi;
@@ -306,79 +307,85 @@ __device__ __forceinline__ void march2(Shared2<R, TX, TY>& sh, const Step2Args<R
                 }
             }
             s1phi = o.phi;
-            sh.u1x[sp][c1] = link(dx, o.a[0]);
-            sh.u1y[sp][c1] = link(dx, o.a[1]);
-            s1z = link(dx, o.a[2]);
+            Cx<R> u1[3];
+            links(dx, o.a, u1);
+            sh.u1x[sp][c1] = u1[0];
+            sh.u1y[sp][c1] = u1[1];
+            s1z = u1[2];
         }
         __syncthreads();
 
-        // ---- (c) stage 2 at plane q = p-1 on the tile
-        if (is_tile && p >= z0) {
-            const int q = p - 1;
-            const int c = c1;
-            const Cx<R> vc[3] = {sh.u1x[sq][c], sh.u1y[sq][c], sh.u1z[c]};
-            if (p == z0) {
-                // plane z0-1 is not stepped here: its F^{n+1}_xz, F^{n+1}_yz
-                // start the stage-2 carry
-                gxz_m = plaq_sin(vc[0], sh.u1z[c + 1], sh.u1x[sp][c], vc[2]) * k1.inv_dx2;
-                gyz_m = plaq_sin(vc[1], sh.u1z[c + W1], sh.u1y[sp][c], vc[2]) * k1.inv_dx2;
-            } else {
+        // ---- (c) stage 2 at plane q = p-1 on the tile.  The step of plane
+        //      z0-1 only starts the carry (F^{n+1}_xz, F^{n+1}_yz, U_z): its
+        //      stores are dropped, as are those of the iteration before it, so
+        //      that every iteration issues the same ones.
+        if constexpr (TILE) {
+            SiteOut<R> o = {};
+            if (p >= z0) {
+                const int c = c1;
+                const Cx<R> vc[3] = {sh.u1x[sq][c], sh.u1y[sq][c], sh.u1z[c]};
                 const R* h = &sh.h1[sq][0][tid];
                 const R qe[3] = {h[2 * NT], h[3 * NT], h[4 * NT]};
                 const R bc[3] = {h[5 * NT], h[6 * NT], h[7 * NT]};
                 const SiteNbr<R> nb = gather_nbr<R, W1>(c, sh.u1x[sq], sh.u1y[sq], sh.u1z, sh.p1, sh.u1x[sp], sh.u1y[sp]);
-                const SiteOut<R> o = site_update(k1, nb, chm, sh.p1[c], s1phi, vc, sh.u1x[sp][c], sh.u1y[sp][c], vz_m,
-                                                 gxz_m, gyz_m, h[0], h[NT], qe, bc);
+                o = site_update(k1, nb, chm, sh.p1[c], s1phi, vc, sh.u1x[sp][c], sh.u1y[sp][c], vz_m, gxz_m, gyz_m,
+                                h[0], h[NT], qe, bc);
                 gxz_m = o.fxz;
                 gyz_m = o.fyz;
-                if (active) {
-                    const int64_t oq = (int64_t)q * NN + own_xy;
-                    const Fields<R>& w = a.out;
-                    st_stream(w.pir + oq, o.pr);
-                    st_stream(w.pii + oq, o.pi);
-                    st_stream(w.e0 + oq, o.e[0]);
-                    st_stream(w.e1 + oq, o.e[1]);
-                    st_stream(w.e2 + oq, o.e[2]);
-                    st_stream(w.phr + oq, o.phi.r);
-                    st_stream(w.phi + oq, o.phi.i);
-                    st_stream(w.a0 + oq, o.a[0]);
-                    st_stream(w.a1 + oq, o.a[1]);
-                    st_stream(w.a2 + oq, o.a[2]);
-                }
+                vz_m = vc[2];
             }
-            vz_m = vc[2];
+            const int64_t oq = (int64_t)(p > z0 ? p - 1 : z0) * NN;
+            const uint32_t sq_o = p > z0 ? so : kNoSite;
+            const PlaneBufs wm = plane_bufs(a.b.om, a.b.fs, oq, pb), wp = plane_bufs(a.b.op, a.b.fs, oq, pb);
+            st_plane(wm.f[B_PIR], sq_o, o.pr);
+            st_plane(wm.f[B_PII], sq_o, o.pi);
+            for (int d = 0; d < 3; ++d) st_plane(wm.f[B_E + d], sq_o, o.e[d]);
+            st_plane(wp.f[B_PHR], sq_o, o.phi.r);
+            st_plane(wp.f[B_PHI], sq_o, o.phi.i);
+            for (int d = 0; d < 3; ++d) st_plane(wp.f[B_A + d], sq_o, o.a[d]);
         }
         if (!more) break;
 
         // ---- stage-1 operands of plane p+1: U_z of p+1 and phi of p+1 into
         //      LDS, links of plane p+2 (x, y into slot sp, z held)
-        if (has1) {
-            uz_m = sh.u0z[c2];
-            sh.u0z[c2] = upz;
-            sh.p0[c2] = php;
-            for (int d = 0; d < 3; ++d) {
-                ac[d] = ap[d];
-                ap[d] = na[d];
-            }
-            sh.u0x[sp][c2] = link(dx, na[0]);
-            sh.u0y[sp][c2] = link(dx, na[1]);
-            upz = link(dx, na[2]);
-            phm = phc;
-            phc = php;
-            php = nph;
-            pr = npr;
-            pi = npi;
-            for (int d = 0; d < 3; ++d) e[d] = ne[d];
-        }
-        if (has_out) {
+        uz_m = sh.u0z[c2];
+        sh.u0z[c2] = upz;
+        sh.p0[c2] = php;
+        Cx<R> un[3];
+        links(dx, na, un);
+        sh.u0x[sp][c2] = un[0];
+        sh.u0y[sp][c2] = un[1];
+        upz = un[2];
+        if constexpr (!TILE) {
             sh.u0z[co] = uo_z;
             sh.p0[co] = noph;
-            sh.u0x[sp][co] = link(dx, noa[0]);
-            sh.u0y[sp][co] = link(dx, noa[1]);
-            uo_z = link(dx, noa[2]);
+            links(dx, noa, un);
+            sh.u0x[sp][co] = un[0];
+            sh.u0y[sp][co] = un[1];
+            uo_z = un[2];
         }
+        for (int d = 0; d < 3; ++d) {
+            ac[d] = ap[d];
+            ap[d] = na[d];
+            e[d] = ne[d];
+        }
+        phm = phc;
+        phc = php;
+        php = nph;
+        pr = npr;
+        pi = npi;
         __syncthreads();
     }
+}
+
+template <typename R, int TX, int TY>
+__device__ __forceinline__ void march2(Shared2<R, TX, TY>& sh, const Step2Args<R>& a, int x0, int y0, int z0, int z1)
+{
+    static_assert(Geom2<TX, TY>::NT % 64 == 0, "a wave is of one kind");
+    if (uniform((int)threadIdx.x) < Geom2<TX, TY>::NT)
+        march2_role<R, TX, TY, true>(sh, a, x0, y0, z0, z1);
+    else
+        march2_role<R, TX, TY, false>(sh, a, x0, y0, z0, z1);
 }
 
 // One lattice: tile t = xcd_tile(b) (tx fastest, then ty, then z-chunk).
@@ -413,11 +420,7 @@ __global__ void __launch_bounds__((kStep2Threads<TX, TY>), (kStep2MinWaves<R, TX
     if (!two_step_due(L, k)) return;  // uniform across the block
     const int cur = (int)L.counter[2], curm = (int)L.counter[3];
     Step2Args<R> a;
-    a.in = Fields<R>{(R*)L.pp[cur][0], (R*)L.pp[cur][1], (R*)L.mom[curm][0], (R*)L.mom[curm][1], (R*)L.pp[cur][2],
-                     (R*)L.pp[cur][3], (R*)L.pp[cur][4], (R*)L.mom[curm][2], (R*)L.mom[curm][3], (R*)L.mom[curm][4]};
-    const int o = cur ^ 1, om = curm ^ 1;
-    a.out = Fields<R>{(R*)L.pp[o][0], (R*)L.pp[o][1], (R*)L.mom[om][0], (R*)L.mom[om][1], (R*)L.pp[o][2],
-                      (R*)L.pp[o][3], (R*)L.pp[o][4], (R*)L.mom[om][2], (R*)L.mom[om][3], (R*)L.mom[om][4]};
+    a.b = Blocks<R>{(const R*)L.pp[cur], (const R*)L.mom[curm], (R*)L.pp[cur ^ 1], (R*)L.mom[curm ^ 1], L.fs};
     a.N = L.N;
     a.P = L.P;
     a.dx = (R)L.dx;
@@ -452,8 +455,7 @@ hipError_t launch_step2_tile(const Fields<R>& in, const Fields<R>& out, const La
 {
     const int N = L.N;
     Step2Args<R> a;
-    a.in = in;
-    a.out = out;
+    if (!blocks_of(in, out, &a.b)) return hipErrorInvalidValue;
     a.N = N;
     a.P = L.P;
     a.dx = (R)L.dx;

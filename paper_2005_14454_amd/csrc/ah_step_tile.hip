@@ -2,10 +2,11 @@
 // action), for one lattice and for a pool of lattices.
 //
 // One workgroup owns a TX x TY tile of the (x0, x1) plane and a chunk of
-// x2-planes ("z").  It walks the chunk plane by plane.  For every incoming
-// plane it loads A and phi of the tile plus a one-site halo ring once,
-// turns A into link variables U_j = exp(-i dx A_j) (one sincos per link,
-// shared by all users through LDS), and then updates its own sites:
+// x2-planes ("z").  It walks the chunk in phases of one plane and one barrier:
+// phase z turns A of plane z+2 (the tile plus a one-site halo ring, loaded
+// during the phase before) into link variables U_j = exp(-i dx A_j), one sincos
+// per link, shared by all users through LDS, and updates the own sites of
+// plane z:
 //   - covariant Laplacian and current from U and phi (section 2);
 //   - lattice curl from plaquettes formed as products of four links,
 //     F_ij = -Im(U_i^x U_j^{x+i} conj(U_i^{x+j}) conj(U_j^x)) / dx^2, which
@@ -17,6 +18,16 @@
 // above (phi, U_z, F_xz, F_yz) are carried in registers.  Workgroups are
 // placed so that each XCD gets a contiguous band of tiles, which keeps halo
 // reads inside one L2.
+//
+// What bounds it: memory for the plain march of a large lattice (512^3 on
+// MI355X: FP32 128 x 4 2.00 ms a step, 5.4 TB/s of algorithmic bytes; FP64
+// 64 x 8 4.49 ms, 4.8 TB/s; a copy reaches 5.5 TB/s); the latency of a chunk's
+// first loads and barriers for a small one (64^3 FP64, 2-plane chunks: 13.0
+// us); instruction issue and latency for the measured march (512^3: FP32 3.65
+// ms, FP64 6.2 ms).  Links in three slots, so that one barrier a plane is
+// enough, and every load of a chunk's start issued before its first barrier
+// took the measured march from 3.74 and 7.3 ms and the 64^3 step from 16.4 us
+// (two barriers a plane, three rounds of loads at the start of a chunk).
 //
 // Floating-point contraction is off in this file and every fused multiply-add
 // is written out, so each site is computed by the same sequence of roundings
@@ -45,19 +56,9 @@ struct TileGeom {
 // Per-launch constants of one lattice step (coefficients rounded to R).
 template <typename R>
 struct StepArgs {
-    Fields<R> f;
-    R* ophr;
-    R* ophi;
-    R* oa0;
-    R* oa1;
-    R* oa2;
-    // Pi and E outputs: f's own arrays for an update in place (the measured
-    // march needs other ones)
-    R* opr;
-    R* opi;
-    R* oe0;
-    R* oe1;
-    R* oe2;
+    // phi and A go to other buffers; Pi and E may be written in place, but not
+    // by the measured march
+    Blocks<R> b;
     int N, P;  // side, row pitch: site (x, y, z) at x + P (y + N z)
     R dx, sigma2, cP1, cP2, cE1, cE2, lamh, kappa, deta;
 };
@@ -73,21 +74,22 @@ struct MeasArgs {
 template <typename R, int TX, int TY>
 struct TileShared {
     static constexpr int RS = TileGeom<R, TX, TY>::RS;
-    Cx<R> U[2][3][RS];  // links of planes z and z+1 (ring)
-    Cx<R> Phi[RS];      // phi of plane z
+    // x and y links of planes z and z+1, which the update of plane z reads,
+    // and of plane z+2, which the same phase writes; z links and phi of planes
+    // z (read) and z+1 (written)
+    Cx<R> Uxy[3][2][RS];
+    Cx<R> Uz[2][RS];
+    Cx<R> Phi[2][RS];
 };
 
 template <typename R, int TX, int TY>
 struct MeasShared {
     static constexpr int RS = (TX + 2) * (TY + 2);
-    R A[2][3][RS];                      // stored A of the link planes held in the U ring
-    float Y[2][3][RS];                  // link phases of planes z (ring of two)
-    // FP32 lattices: E_x, E_y of plane z (own sites, and the -x / -y halo)
-    // for the Gauss residual
-    R E[2][sizeof(R) == 4 ? RS : 1];
-    // FP64 lattices: each thread's running diagnostics sums (kept here rather
-    // than in registers, which the FP64 measured march runs out of)
-    double acc[kMarchSums][sizeof(R) == 8 ? TX * TY : 1];
+    R A[2][3][RS];      // stored A of planes z (read) and z+1 (written)
+    float Y[2][3][RS];  // link phases of planes z (written) and z-1 (read)
+    // FP32 lattices: E_x, E_y of planes z (read) and z+1 (written; own sites,
+    // and the -x / -y halo) for the Gauss residual
+    R E[2][2][sizeof(R) == 4 ? RS : 1];
     double red[TX * TY / 64][M_COUNT];  // block reduction
 };
 
@@ -136,9 +138,9 @@ __device__ inline float link_phase(double pr, double pim, Cx<double> U, double v
     double zi = pr * wi - pim * wr;
     zi = (zi == 0.0) ? 0.0 : zi;
     const double mz = fmax(fabs(zr), fabs(zi));
-    if (mz == 0.0) return signbit(zr) ? 3.14159265358979f : 0.0f;
     const int e = ilogb(mz);
-    return atan2_fast((float)ldexp(zi, -e), (float)ldexp(zr, -e));
+    const float y = atan2_fast((float)ldexp(zi, -e), (float)ldexp(zr, -e));
+    return mz == 0.0 ? (signbit(zr) ? 3.14159265358979f : 0.0f) : y;
 }
 
 // The FP64 evaluation for an FP32 lattice's link near the cut.  It runs for a
@@ -159,32 +161,82 @@ __device__ __attribute__((noinline)) float link_phase_near_cut(Cx<float> ph, Cx<
 // FP32 keeps its relative precision (or is not finite), and where |dx A|
 // exceeds 1e5 (so that four phases stay well within pi of the FP64 sum), the
 // FP64 evaluation above decides from the stored A.
-__device__ inline float link_phase_f(Cx<float> z, Cx<float> ph, Cx<float> pn, float a, double dx)
+//
+// The K phases of a site are taken side by side, with one test for all of
+// them: a branch apiece would leave a chain of some forty dependent
+// instructions at a time in flight, at two waves per SIMD.
+template <int K>
+__device__ inline void link_phases_f(const Cx<float> (&z)[K], Cx<float> ph, const Cx<float> (&pn)[K],
+                                     const float (&a)[K], double dx, float (&y)[K])
 {
-    const float mz = fmaxf(fabsf(z.r), fabsf(z.i));
-    const float dxa = fabsf((float)dx * a);
-    if (mz > 1e-30f && mz < 1e30f && dxa < 1e5f) {
-        const float y = atan2_fast(z.i, z.r);
-        if (3.14159265f - fabsf(y) > 1e-5f + 2.4e-7f * dxa) return y;
+    bool ok[K], all = true;
+    for (int d = 0; d < K; ++d) {
+        const float mz = fmaxf(fabsf(z[d].r), fabsf(z[d].i));
+        const float dxa = fabsf((float)dx * a[d]);
+        y[d] = atan2_fast(z[d].i, z[d].r);
+        ok[d] = mz > 1e-30f && mz < 1e30f && dxa < 1e5f && 3.14159265f - fabsf(y[d]) > 1e-5f + 2.4e-7f * dxa;
+        all = all && ok[d];
     }
-    return link_phase_near_cut(ph, pn, a, dx);
+    if (!all)
+        for (int d = 0; d < K; ++d)
+            if (!ok[d]) y[d] = link_phase_near_cut(ph, pn[d], a[d], dx);
 }
 
-// Winding of a plaquette from its four link phases and its angle (FP64): the
-// angle is wrapped to (-pi, pi] by the nearest multiple of 2 pi that the
-// division th / 2 pi rounds to (a product with 1 / 2 pi gives the same
-// multiple unless the quotient is close to a half turn, where the division
-// itself is taken); the total is then within ~1e-5 of a multiple of 2 pi.
+// The multiple of 2 pi that wraps a plaquette angle to (-pi, pi]: the nearest
+// one that the division th / 2 pi rounds to (a product with 1 / 2 pi gives the
+// same multiple unless the quotient is close to a half turn, where the
+// division itself is taken).
+__device__ inline double turns_of(double th)
+{
+    const double two_pi = 6.283185307179586;
+    const double q = th * (1.0 / two_pi);
+    const double r = rint(q);
+    return fabs(q - r) < 0.49 && fabs(q) < 1e12 ? r : rint(th / two_pi);
+}
+
+// Angles dx (((a + b) - c) - d) of a site's plaquettes as their windings take
+// them: FP64
+// lattices the angle itself, FP32 ones the wrapped angle in FP32.
+//
+// In FP32 the angle of |A| dx < 100 is within 1.2e-4 of its FP64 value (five
+// roundings of at most 400), 2e-5 turns, so unless it lies within 1e-4 turns
+// of a half turn the multiple that wraps it is the FP64 one; the winding only
+// needs the wrapped angle to well below pi.  Otherwise FP64 decides.
+__device__ inline void plaq_angles(double dx, double, const double (&q)[3][4], double (&th)[3])
+{
+    for (int k = 0; k < 3; ++k) th[k] = dx * (((q[k][0] + q[k][1]) - q[k][2]) - q[k][3]);
+}
+__device__ inline void plaq_angles(double dx, float dxf, const float (&q)[3][4], float (&th)[3])
+{
+    bool ok[3];
+    for (int k = 0; k < 3; ++k) {
+        const float big = fmaxf(fmaxf(fabsf(q[k][0]), fabsf(q[k][1])), fmaxf(fabsf(q[k][2]), fabsf(q[k][3])));
+        th[k] = dxf * (((q[k][0] + q[k][1]) - q[k][2]) - q[k][3]);
+        const float t = th[k] * 0.15915494309189535f;
+        const float r = __builtin_rintf(t);
+        th[k] = fm(-6.2831853071795865f, r, th[k]);
+        ok[k] = fabsf(t - r) < 0.4999f && dxf * big < 100.f;
+    }
+    if (!(ok[0] && ok[1] && ok[2]))
+        for (int k = 0; k < 3; ++k)
+            if (!ok[k]) {
+                const double t = dx * ((((double)q[k][0] + (double)q[k][1]) - (double)q[k][2]) - (double)q[k][3]);
+                th[k] = (float)(t - 6.283185307179586 * turns_of(t));
+            }
+}
+
+// Winding of a plaquette from its four link phases and its angle (plaq_angles):
+// their sum is within ~1e-3 of a multiple of 2 pi.
 __device__ inline int winding_of(float y1, float y2, float y3, float y4, double th)
 {
     const double two_pi = 6.283185307179586;
-    const double inv_two_pi = 1.0 / two_pi;
-    const double q = th * inv_two_pi;
-    double r = rint(q);
-    if (!(fabs(q - r) < 0.49 && fabs(q) < 1e12)) r = rint(th / two_pi);
-    const double thw = th - two_pi * r;
+    const double thw = th - two_pi * turns_of(th);
     const double sum = ((((double)y1 + (double)y2) - (double)y3) - (double)y4) + thw;
-    return (int)rint(sum * inv_two_pi);
+    return (int)rint(sum * (1.0 / two_pi));
+}
+__device__ inline int winding_of(float y1, float y2, float y3, float y4, float thw)
+{
+    return (int)__builtin_rintf(((((y1 + y2) - y3) - y4) + thw) * 0.15915494309189535f);
 }
 
 // 1 - cos(Theta) of a plaquette from its four links, without cancellation
@@ -217,7 +269,7 @@ __device__ inline double wave_max(double v)
 // sums to `record`.  The Gauss residual
 // reads E at the -x and -y neighbours, which a neighbouring workgroup of a
 // pass that updated E in place could already have overwritten, so a measured
-// march that steps writes Pi and E out of place (a.opr .. a.oe2).  E_z of the
+// march that steps writes Pi and E out of place (a.b.om).  E_z of the
 // plane below is carried in a register; FP32 passes E_x and E_y of each plane
 // through LDS, FP64 (whose LDS holds two workgroups per CU only without that
 // exchange) loads the two neighbours with the plane's Pi and E.
@@ -231,43 +283,34 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
     using G = TileGeom<R, TX, TY>;
     constexpr int RW = G::RW, H = G::H, NT = G::NT;
     static_assert(G::HPT == 1, "halo must fit one extra site per thread");
-    auto& sU = sh.U;
-    auto& sPhi = sh.Phi;
-    const Fields<R>& f = a.f;
-    R* __restrict__ ophr = a.ophr;
-    R* __restrict__ ophi = a.ophi;
-    R* __restrict__ oa0 = a.oa0;
-    R* __restrict__ oa1 = a.oa1;
-    R* __restrict__ oa2 = a.oa2;
     const int N = a.N;
     const R dx = a.dx, sigma2 = a.sigma2, cP1 = a.cP1, cP2 = a.cP2, cE1 = a.cE1, cE2 = a.cE2;
     const R lamh = a.lamh, kappa = a.kappa, deta = a.deta;
     constexpr bool GAUSS = MEAS;                  // Gauss residual in this march
     constexpr bool GLDS = GAUSS && sizeof(R) == 4;  // its -x / -y E through LDS (FP64: loads)
-    R* wpr = a.opr;
-    R* wpi = a.opi;
-    R* we0 = a.oe0;
-    R* we1 = a.oe1;
-    R* we2 = a.oe2;
 
     const R inv_dx = R(1) / dx;
     const R inv_dx2 = inv_dx * inv_dx;
     const int P = a.P;
     const int64_t NN = (int64_t)N * P;  // plane stride
+    const uint32_t pb = (uint32_t)NN * (uint32_t)sizeof(R);  // bytes of a plane (N P < 2^28)
 
     const int tid = threadIdx.x;
     const int lx = tid % TX, ly = tid / TX;
     const int gx = x0 + lx, gy = y0 + ly;
     const bool active = gx < N && gy < N;
     const int gxw = wrapi(gx, N), gyw = wrapi(gy, N);
-    const int64_t own_xy = (int64_t)gxw + (int64_t)P * gyw;
-    const uint32_t ob = (uint32_t)own_xy;  // 32-bit in-plane offset (N P < 2^32)
-    const int ro = (ly + 1) * RW + (lx + 1);  // own region slot
+    // byte offsets in a plane: of the own site, and for the stores (kNoSite for
+    // the lanes past a ragged edge and for a pass that only measures)
+    const uint32_t ob = ((uint32_t)gxw + (uint32_t)P * (uint32_t)gyw) * (uint32_t)sizeof(R);
+    const uint32_t so = write && active ? ob : kNoSite;
+    int ro = (ly + 1) * RW + (lx + 1);  // own region slot
 
     // halo ring site of this thread (if any)
     const bool has_halo = tid < H;
+    const bool halo_wave = uniform(tid & ~63) < H;  // a wave with halo sites
     int rh = 0, hrx = 0, hry = 0;
-    int64_t halo_xy = 0;
+    uint32_t hb = kNoSite;
     if (has_halo) {
         if (tid < RW) {
             hrx = tid;
@@ -283,61 +326,76 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
             hry = 1 + (tid - 2 * RW - TY);
         }
         rh = hry * RW + hrx;
-        halo_xy = (int64_t)wrapi(x0 - 1 + hrx, N) + (int64_t)P * wrapi(y0 - 1 + hry, N);
+        hb = ((uint32_t)wrapi(x0 - 1 + hrx, N) + (uint32_t)P * (uint32_t)wrapi(y0 - 1 + hry, N)) * (uint32_t)sizeof(R);
     }
-    const uint32_t hb = (uint32_t)halo_xy;
-    // halo sites whose link phases the windings of the tile read
-    const bool halo_top = has_halo && hry == TY + 1 && hrx >= 1 && hrx <= TX;    // Y_x, Y_z
-    const bool halo_right = has_halo && hrx == TX + 1 && hry >= 1 && hry <= TY;  // Y_y, Y_z
+    // Link phases on the halo that the windings of the tile read: Y_x and Y_z
+    // of the +y row, Y_y and Y_z of the +x column.  Each is one evaluation of
+    // some fifty instructions; a wave that made two of them on top of its halo
+    // links would hold every barrier up, so they are dealt out one to a thread
+    // from the last thread down, away from the waves with the halo sites.
+    static_assert(2 * (TX + TY) <= NT, "a halo link phase per thread at most");
+    const int ph_t = NT - 1 - tid;
+    const bool has_ph = MEAS && ph_t < 2 * (TX + TY);
+    const bool ph_wave = MEAS && uniform(NT - 1 - (tid | 63)) < 2 * (TX + TY);
+    const bool ph_row = ph_t < 2 * TX;
+    const bool ph_z = ph_row ? ph_t >= TX : ph_t >= 2 * TX + TY;        // Y_z
+    const int ph_k = ph_row ? ph_t % TX : (ph_t - 2 * TX) % TY;         // place in the row / column
+    const int ph_x = ph_row ? 1 + ph_k : TX + 1, ph_y = ph_row ? TY + 1 : 1 + ph_k;
+    const int ph_d = ph_z ? 2 : (ph_row ? 0 : 1);
+    const int ph_r = has_ph ? ph_y * RW + ph_x : 0;                     // region slot
+    const int ph_n = ph_r + (ph_row ? 1 : RW);                          // that of the neighbour (not for Y_z)
+    const uint32_t ph_b = has_ph && ph_z ? ((uint32_t)wrapi(x0 - 1 + ph_x, N) + (uint32_t)P * (uint32_t)wrapi(y0 - 1 + ph_y, N)) *
+                                       (uint32_t)sizeof(R)
+                                         : kNoSite;
     // halo sites whose E the Gauss residual of the tile reads: E_x on the -x
     // column, E_y on the -y row
     const bool halo_ex = has_halo && hrx == 0 && hry >= 1 && hry <= TY;
     const bool halo_ey = has_halo && hry == 0 && hrx >= 1 && hrx <= TX;
     const bool halo_e = GLDS && (halo_ex || halo_ey);
-    const R* hE = halo_ex ? f.e0 : f.e1;
+    const uint32_t hbx = halo_ex ? hb : kNoSite, hby = halo_ey ? hb : kNoSite;
     const int hEc = halo_ex ? 0 : 1;
 
-    // neighbour slots in the region
-    const int rxm = ro - 1, rxp = ro + 1, rym = ro - RW, ryp = ro + RW;
-    const int rxm_yp = ro - 1 + RW, rxp_ym = ro + 1 - RW;
+    auto plane_of = [&](int z) -> int64_t { return (int64_t)wrapz(z, N) * NN; };
+    auto in_p = [&](int64_t plane) { return plane_bufs(a.b.ip, a.b.fs, plane, pb); };
+    auto in_m = [&](int64_t plane) { return plane_bufs(a.b.im, a.b.fs, plane, pb); };
+    auto ld = [](Rsrc r, uint32_t off) -> R { return ld_plane<R>(r, off); };
+    auto ld_nt = [](Rsrc r, uint32_t off) -> R { return ld_plane<R, true>(r, off); };
 
-    auto plane_of = [&](int z) -> int64_t { return (int64_t)wrapi(z, N) * NN; };
-
-    // ---------------------------------------------------------------- prologue
-    // U(z0-1) of the region into slot 1, U(z0) into slot 0, phi(z0) into sPhi.
-    // The FP64 plain march reads its own links of planes z and z+1 from LDS
-    // where it uses them rather than carrying them from plane to plane in
-    // registers (186 rather than 202 registers on 64 x 8, 1% faster).
+    // The FP64 marches read the site's own links of planes z and z+1 from LDS
+    // where they use them rather than carrying them from plane to plane in
+    // registers, but for U_z of plane z+1.
     constexpr bool ULDS = sizeof(R) == 8;
     Cx<R> Uc[3], Up[3];
     R Ac[3], Ap[3];
     Cx<R> phi_c, phi_p;
+    R pr_c, pi_c, e_c[3];
     Cx<R> bz_m;  // conj(U_z) phi of the own site one plane below
     R fxz_m, fyz_m;
-    // diagnostics state (MEAS): the (x, z) and (y, z) windings of plane z need
-    // Y_x, Y_y of plane z+1, so they are completed one plane later from the own
-    // link phases of plane z (_b) and the two plaquette angles of plane z
+    // halo site: U_z and (MEAS) A of plane z+1, into LDS during phase z
+    Cx<R> huz = {};
+    R ha1[3] = {0, 0, 0};
+    // diagnostics state (MEAS): the windings of plane z need its halo's link
+    // phases, and those of the (x, z) and (y, z) plaquettes Y_x, Y_y of plane
+    // z+1, so they are completed one plane later from the own link phases (_b)
+    // and the plaquette angles of plane z
     float yx_b = 0.f, yy_b = 0.f, yz_b = 0.f;
-    double thxz_b = 0.0, thyz_b = 0.0;
+    R th_b[3] = {0, 0, 0};  // (x, y), (x, z), (y, z)
     // link phase of a link U = exp(-i dx a) between phi values ph and pn
     auto phase = [&](Cx<R> ph, Cx<R> U, Cx<R> pn, R av) -> float {
         if constexpr (sizeof(R) == 8)
             return link_phase(ph.r, ph.i, U, pn.r, pn.i);
-        else
-            return link_phase_f(cmulc(ph, cmul(U, pn)), ph, pn, av, ma.dx);
+        else {
+            float y[1];
+            link_phases_f<1>({cmulc(ph, cmul(U, pn))}, ph, {pn}, {av}, ma.dx, y);
+            return y[0];
+        }
     };
     // sums of the march: M_KIN .. M_RHOL (kMarchSums slots, FP64) and the
     // exact counts M_WABS, M_NONFIN (integers); the Gauss sums follow
-    double acc_reg[kMarchSums];
-    auto acc = [&](int k) -> double& {
-        if constexpr (sizeof(R) == 8)
-            return mx->acc[k][tid];
-        else
-            return acc_reg[k];
-    };
+    double acc[kMarchSums];
     int wabs = 0, nonfin = 0;
     if constexpr (MEAS)
-        for (int k = 0; k < kMarchSums; ++k) acc(k) = 0.0;
+        for (int k = 0; k < kMarchSums; ++k) acc[k] = 0.0;
     // Gauss residual (GAUSS): sums of G^2, (div E)^2, (c rho)^2, max |G|, and
     // E_z of the own site one plane below
     double g2 = 0.0, d2 = 0.0, c2 = 0.0, gmax = 0.0;
@@ -345,162 +403,151 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
     // FP64: E_x at x - kx and E_y at x - ky of plane z, loaded with the plane's
     // Pi and E (Pi and E go to other buffers, so these are the snapshot's)
     R ex_xm = R(0), ey_ym = R(0);
-    const uint32_t ob_xm = gxw == 0 ? ob + (uint32_t)(N - 1) : ob - 1u;
-    const uint32_t ob_ym = gyw == 0 ? ob + (uint32_t)(N - 1) * (uint32_t)P : ob - (uint32_t)P;
+    const uint32_t row = (uint32_t)P * (uint32_t)sizeof(R);
+    const uint32_t ob_xm = gxw == 0 ? ob + (uint32_t)(N - 1) * (uint32_t)sizeof(R) : ob - (uint32_t)sizeof(R);
+    const uint32_t ob_ym = gyw == 0 ? ob + (uint32_t)(N - 1) * row : ob - row;
     const double inv_dx64 = 1.0 / ma.dx;
-    {
-        const int64_t pm = plane_of(z0 - 1), p0 = plane_of(z0);
-        const R* A[3] = {f.a0, f.a1, f.a2};
-        Cx<R> um[3];
-        for (int d = 0; d < 3; ++d) {
-            um[d] = link(dx, at(A[d], pm, ob));
-            sU[1][d][ro] = um[d];
-            Ac[d] = at(A[d], p0, ob);
-            Uc[d] = link(dx, Ac[d]);
-            sU[0][d][ro] = Uc[d];
-        }
-        if (has_halo)
-            for (int d = 0; d < 3; ++d) {
-                sU[1][d][rh] = link(dx, at(A[d], pm, hb));
-                const R ah = at(A[d], p0, hb);
-                sU[0][d][rh] = link(dx, ah);
-                if constexpr (MEAS) mx->A[0][d][rh] = ah;
-            }
-        if constexpr (MEAS)
-            for (int d = 0; d < 3; ++d) mx->A[0][d][ro] = Ac[d];
-        const Cx<R> phi_m{at(f.phr, pm, ob), at(f.phi, pm, ob)};
-        phi_c = {at(f.phr, p0, ob), at(f.phi, p0, ob)};
-        sPhi[ro] = phi_c;
-        if (has_halo) sPhi[rh] = Cx<R>{at(f.phr, p0, hb), at(f.phi, p0, hb)};
-        if constexpr (GAUSS) ezm = at(f.e2, pm, ob);
-        if constexpr (GLDS) {
-            mx->E[0][ro] = at(f.e0, p0, ob);
-            mx->E[1][ro] = at(f.e1, p0, ob);
-            if (halo_e) mx->E[hEc][rh] = at(hE, p0, hb);
-        }
-
-        bz_m = cmulc(um[2], phi_m);
-        __syncthreads();
-        // F_xz, F_yz of the own column at plane z0-1
-        fxz_m = plaq_sin(um[0], sU[1][2][rxp], Uc[0], um[2]) * inv_dx2;
-        fyz_m = plaq_sin(um[1], sU[1][2][ryp], Uc[1], um[2]) * inv_dx2;
-        __syncthreads();
-        // U(z0+1) into slot 1
-        const int64_t p1 = plane_of(z0 + 1);
-        for (int d = 0; d < 3; ++d) {
-            Ap[d] = at(A[d], p1, ob);
-            Up[d] = link(dx, Ap[d]);
-            sU[1][d][ro] = Up[d];
-        }
-        if (has_halo)
-            for (int d = 0; d < 3; ++d) {
-                const R ah = at(A[d], p1, hb);
-                sU[1][d][rh] = link(dx, ah);
-                if constexpr (MEAS) mx->A[1][d][rh] = ah;
-            }
-        if constexpr (MEAS)
-            for (int d = 0; d < 3; ++d) mx->A[1][d][ro] = Ap[d];
-        phi_p = {at(f.phr, p1, ob), at(f.phi, p1, ob)};
-        __syncthreads();
-    }
-
-    const int64_t pz0 = (int64_t)z0 * NN;
-    R pr_c = ld_stream(f.pir + pz0 + ob), pi_c = ld_stream(f.pii + pz0 + ob);
-    R e_c[3] = {ld_stream(f.e0 + pz0 + ob), ld_stream(f.e1 + pz0 + ob), ld_stream(f.e2 + pz0 + ob)};
-    if constexpr (GAUSS && !GLDS) {
-        ex_xm = at(f.e0, pz0, ob_xm);
-        ey_ym = at(f.e1, pz0, ob_ym);
-    }
-
-    // Operands prefetched for iteration t: A of plane t+2 (own and halo), phi
-    // of plane t+1 (halo) and t+2 (own), Pi and E of plane t+1 (own).  The
-    // plain march loads them one iteration ahead.  The measured march of FP32
-    // lattices holds fewer waves per SIMD (it needs more registers), so it
-    // loads them two iterations ahead to keep as many loads in flight; it
-    // loads every iteration's operands, the last ones of a chunk from wrapped
-    // planes that it does not use.  The FP64 measured march has no registers
-    // to hold them across the plane's arithmetic and loads them (LATE) just
-    // before they are used, which keeps it at two waves per SIMD.
-    constexpr bool D2 = MEAS && sizeof(R) == 4;
-    constexpr bool LATE = MEAS && sizeof(R) == 8;
+    // Operands of phase t, loaded during the phase before it: A of plane t+2
+    // (own and halo), phi of plane t+1 (halo) and t+2 (own), Pi and E of plane
+    // t+1 (own).
     struct Pre {
         R a[3], ha[3];
         Cx<R> hphi, phi2;
         R pr, pi, e[3];
-        R he;          // GLDS: the halo E of plane t+1
+        Cx<R> he;      // GLDS: E_x, E_y of plane t+1 at the halo site (it needs one of them)
+        Cx<R> pphi;    // phi of plane t+1 at the halo link phase's site
         R exm, eym;    // FP64 Gauss: E_x at x - kx, E_y at x - ky of plane t+1
     };
+    // The halo loads come first: only some waves make them, and what follows
+    // them is the same for every wave, so that the waits can count it.
     auto prefetch = [&](int t, Pre& q) {
-        const int64_t p2 = plane_of(t + 2), p1 = plane_of(t + 1);
-        q.a[0] = at(f.a0, p2, ob);
-        q.a[1] = at(f.a1, p2, ob);
-        q.a[2] = at(f.a2, p2, ob);
-        if (has_halo) {
-            q.ha[0] = at(f.a0, p2, hb);
-            q.ha[1] = at(f.a1, p2, hb);
-            q.ha[2] = at(f.a2, p2, hb);
-            q.hphi = {at(f.phr, p1, hb), at(f.phi, p1, hb)};
+        const int64_t p1 = plane_of(t + 1);
+        const PlaneBufs f2 = in_p(plane_of(t + 2)), m1 = in_m(p1);
+        if (halo_wave) {
+            for (int d = 0; d < 3; ++d) q.ha[d] = ld(f2.f[B_A + d], hb);
+            const PlaneBufs f1 = in_p(p1);
+            q.hphi = {ld(f1.f[B_PHR], hb), ld(f1.f[B_PHI], hb)};
+            if constexpr (GLDS) q.he = {ld(m1.f[B_E], hbx), ld(m1.f[B_E + 1], hby)};
         }
-        if constexpr (GLDS)
-            if (halo_e) q.he = at(hE, p1, hb);
+        if constexpr (MEAS)
+            if (ph_wave) {
+                const PlaneBufs f1 = in_p(p1);
+                q.pphi = {ld(f1.f[B_PHR], ph_b), ld(f1.f[B_PHI], ph_b)};
+            }
+        for (int d = 0; d < 3; ++d) q.a[d] = ld(f2.f[B_A + d], ob);
         if constexpr (GAUSS && !GLDS) {
-            q.exm = at(f.e0, p1, ob_xm);
-            q.eym = at(f.e1, p1, ob_ym);
+            q.exm = ld(m1.f[B_E], ob_xm);
+            q.eym = ld(m1.f[B_E + 1], ob_ym);
         }
-        q.phi2 = {at(f.phr, p2, ob), at(f.phi, p2, ob)};
-        q.pr = ld_stream(f.pir + p1 + ob);
-        q.pi = ld_stream(f.pii + p1 + ob);
-        q.e[0] = ld_stream(f.e0 + p1 + ob);
-        q.e[1] = ld_stream(f.e1 + p1 + ob);
-        q.e[2] = ld_stream(f.e2 + p1 + ob);
+        q.phi2 = {ld(f2.f[B_PHR], ob), ld(f2.f[B_PHI], ob)};
+        q.pr = ld_nt(m1.f[B_PIR], ob);
+        q.pi = ld_nt(m1.f[B_PII], ob);
+        for (int d = 0; d < 3; ++d) q.e[d] = ld_nt(m1.f[B_E + d], ob);
     };
-    Pre q1, q2;
-    if constexpr (D2) prefetch(z0, q1);
+    Pre q;
+    {
+        // Every load of the prologue, and those of the first phase, are issued
+        // before its first barrier: a chunk then starts with one round of
+        // memory latency.
+        const int64_t pm = plane_of(z0 - 1), p0 = plane_of(z0), p1 = plane_of(z0 + 1);
+        const PlaneBufs fm = in_p(pm), f0 = in_p(p0), f1 = in_p(p1), m0 = in_m(p0);
+        R am[3], hm[1] = {0}, h0[3] = {0, 0, 0};
+        Cx<R> hph0 = {}, he0 = {};
+        if (halo_wave) {
+            hm[0] = ld(fm.f[B_A + 2], hb);
+            for (int d = 0; d < 3; ++d) h0[d] = ld(f0.f[B_A + d], hb);
+            for (int d = 0; d < 3; ++d) ha1[d] = ld(f1.f[B_A + d], hb);
+            hph0 = Cx<R>{ld(f0.f[B_PHR], hb), ld(f0.f[B_PHI], hb)};
+            if constexpr (GLDS) he0 = {ld(m0.f[B_E], hbx), ld(m0.f[B_E + 1], hby)};
+        }
+        for (int d = 0; d < 3; ++d) am[d] = ld(fm.f[B_A + d], ob);
+        for (int d = 0; d < 3; ++d) Ac[d] = ld(f0.f[B_A + d], ob);
+        for (int d = 0; d < 3; ++d) Ap[d] = ld(f1.f[B_A + d], ob);
+        const Cx<R> phi_m{ld(fm.f[B_PHR], ob), ld(fm.f[B_PHI], ob)};
+        phi_c = {ld(f0.f[B_PHR], ob), ld(f0.f[B_PHI], ob)};
+        phi_p = {ld(f1.f[B_PHR], ob), ld(f1.f[B_PHI], ob)};
+        pr_c = ld_nt(m0.f[B_PIR], ob);
+        pi_c = ld_nt(m0.f[B_PII], ob);
+        for (int d = 0; d < 3; ++d) e_c[d] = ld_nt(m0.f[B_E + d], ob);
+        if constexpr (GAUSS) ezm = ld(in_m(pm).f[B_E + 2], ob);
+        if constexpr (GAUSS && !GLDS) {
+            ex_xm = ld(m0.f[B_E], ob_xm);
+            ey_ym = ld(m0.f[B_E + 1], ob_ym);
+        }
+        if (MEAS || z0 + 1 < z1) prefetch(z0, q);
 
-    int cur = 0;
-    for (int z = z0; z < z1; ++z) {
-        const int nxt = cur ^ 1;
-        const bool more = z + 1 < z1;  // is there a next iteration?
-        const int zs = (z - z0) & 1;   // link-phase slot of plane z
-        // ---- 0. issue the loads of the operands prefetched for the coming
-        //         iterations (q1 holds those of this one)
-        if constexpr (D2)
-            prefetch(z + 1, q2);
-        else if (!LATE && more)
-            prefetch(z, q1);
-        const R* rA = q1.a;  // read at step 3, after the late loads
-        const R* hA = q1.ha;
-        Cx<R> hphi = q1.hphi;
-        if constexpr (LATE) {
-            // the halo phi of plane z+1 is needed before the late loads (by the
-            // halo link phases of this plane), so it is loaded here
-            if (has_halo) {
-                const int64_t p1 = plane_of(z + 1);
-                hphi = Cx<R>{at(f.phr, p1, hb), at(f.phi, p1, hb)};
-            }
+        // planes z0 and z0+1: x, y links into slots 0 and 1; U_z of z0 into
+        // slot 0, of z0-1 (for F there) into slot 1
+        Cx<R> um[3], uh[3], uhm[1];
+        links(dx, am, um);
+        links(dx, Ac, Uc);
+        links(dx, Ap, Up);
+        sh.Uz[1][ro] = um[2];
+        sh.Uz[0][ro] = Uc[2];
+        for (int d = 0; d < 2; ++d) {
+            sh.Uxy[0][d][ro] = Uc[d];
+            sh.Uxy[1][d][ro] = Up[d];
         }
-        const Cx<R> rphi = phi_p;
-        float yx_c = 0.f, yy_c = 0.f, yz_c = 0.f;
-        double th_xy = 0.0;
-        if constexpr (MEAS) {
-            // ---- link phases of plane z on the +x / +y halo
-            auto& sY = mx->Y[zs];
-            if (halo_top || halo_right) {
-                const Cx<R> ph = sPhi[rh];
-                const auto& sA = mx->A[cur];
-                if (halo_top) sY[0][rh] = phase(ph, sU[cur][0][rh], sPhi[rh + 1], sA[0][rh]);
-                if (halo_right) sY[1][rh] = phase(ph, sU[cur][1][rh], sPhi[rh + RW], sA[1][rh]);
-                sY[2][rh] = phase(ph, sU[cur][2][rh], hphi, sA[2][rh]);
-            }
+        sh.Phi[0][ro] = phi_c;
+        if constexpr (MEAS)
+            for (int d = 0; d < 3; ++d) mx->A[0][d][ro] = Ac[d];
+        if (has_halo) {
+            links(dx, hm, uhm);
+            sh.Uz[1][rh] = uhm[0];
+            links(dx, h0, uh);
+            sh.Uz[0][rh] = uh[2];
+            for (int d = 0; d < 2; ++d) sh.Uxy[0][d][rh] = uh[d];
+            links(dx, ha1, uh);
+            for (int d = 0; d < 2; ++d) sh.Uxy[1][d][rh] = uh[d];
+            huz = uh[2];
+            sh.Phi[0][rh] = hph0;
+            if constexpr (MEAS)
+                for (int d = 0; d < 3; ++d) mx->A[0][d][rh] = h0[d];
         }
+        if constexpr (GLDS) {
+            mx->E[0][0][ro] = e_c[0];
+            mx->E[0][1][ro] = e_c[1];
+            if (halo_e) mx->E[0][hEc][rh] = halo_ex ? he0.r : he0.i;
+        }
+        bz_m = cmulc(um[2], phi_m);
+        __syncthreads();
+        // F_xz, F_yz of the own column at plane z0-1
+        fxz_m = plaq_sin(um[0], sh.Uz[1][ro + 1], Uc[0], um[2]) * inv_dx2;
+        fyz_m = plaq_sin(um[1], sh.Uz[1][ro + RW], Uc[1], um[2]) * inv_dx2;
+        __syncthreads();
+        // wait here for the loads that the first plane takes from registers,
+        // rather than on every pass through the loop that it enters
+        asm volatile("" : "+v"(pr_c), "+v"(pi_c), "+v"(e_c[0]), "+v"(e_c[1]), "+v"(e_c[2]));
+        if constexpr (GAUSS) asm volatile("" : "+v"(ezm));
+        if constexpr (GAUSS && !GLDS) asm volatile("" : "+v"(ex_xm), "+v"(ey_ym));
+    }
+
+    // The march, a phase and a barrier per plane: phase z updates plane z and
+    // forms the links of plane z+2.  What it writes to LDS, no wave reads
+    // before the barrier that ends it.
+    int s0 = 0, s1 = 1, s2 = 2;  // slots of the x, y links of planes z, z+1, z+2
+    for (int z = z0, b = 0;; ++z, b ^= 1) {
+        const bool more = z + 1 < z1;  // there is a next plane to update
+        // neighbour slots in the region
+        const int rxm = ro - 1, rxp = ro + 1, rym = ro - RW, ryp = ro + RW;
+        const int rxm_yp = ro - 1 + RW, rxp_ym = ro + 1 - RW;
+        const Cx<R> *ux = sh.Uxy[s0][0], *uy = sh.Uxy[s0][1], *uz = sh.Uz[b], *uxp = sh.Uxy[s1][0], *uyp = sh.Uxy[s1][1];
+        const Cx<R>* sPhi = sh.Phi[b];
+        if constexpr (MEAS)
+            if (has_ph) {
+                const Cx<R> u = (ph_z ? uz : (ph_row ? ux : uy))[ph_r], nb = sPhi[ph_n], up = q.pphi;
+                mx->Y[b][ph_d][ph_r] = phase(sPhi[ph_r], u, ph_z ? up : nb, mx->A[b][ph_d][ph_r]);
+            }
 
         // ---- 1. update of the own site at plane z
         {
-            if constexpr (ULDS)
-                for (int d = 0; d < 3; ++d) {
-                    Uc[d] = sU[cur][d][ro];
-                    Up[d] = sU[nxt][d][ro];
-                }
+            if constexpr (ULDS) {
+                Uc[0] = ux[ro];
+                Uc[1] = uy[ro];
+                Uc[2] = uz[ro];
+                Up[0] = uxp[ro];
+                Up[1] = uyp[ro];
+            }
             if constexpr (GAUSS && !GLDS) {
                 // FP64: the Gauss residual of the site first, while few values
                 // are live (FP32 forms it with the other diagnostics below)
@@ -518,8 +565,8 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
                 }
             }
             const Cx<R> ph_xm = sPhi[rxm], ph_xp = sPhi[rxp], ph_ym = sPhi[rym], ph_yp = sPhi[ryp];
-            const Cx<R> ux_xm = sU[cur][0][rxm];  // U_x^{x-kx}
-            const Cx<R> uy_ym = sU[cur][1][rym];  // U_y^{x-ky}
+            const Cx<R> ux_xm = ux[rxm];  // U_x^{x-kx}
+            const Cx<R> uy_ym = uy[rym];  // U_y^{x-ky}
             // covariant Laplacian: sum_j U_j^x phi^{x+j} + conj(U_j^{x-j}) phi^{x-j} - 2 phi^x
             const Cx<R> fx = cmul(Uc[0], ph_xp), fy = cmul(Uc[1], ph_yp), fz = cmul(Uc[2], phi_p);
             const Cx<R> bx = cmulc(ux_xm, ph_xm), by = cmulc(uy_ym, ph_ym), bz = bz_m;
@@ -532,35 +579,45 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
             if constexpr (MEAS) {
                 // own link phases of plane z (FP32 lattices: z = conj(phi) U phi^{x+j}
                 // is the forward product of the Laplacian)
+                float yx_c, yy_c, yz_c;
                 if constexpr (sizeof(R) == 8) {
                     yx_c = link_phase(phi_c.r, phi_c.i, Uc[0], ph_xp.r, ph_xp.i);
                     yy_c = link_phase(phi_c.r, phi_c.i, Uc[1], ph_yp.r, ph_yp.i);
                     yz_c = link_phase(phi_c.r, phi_c.i, Uc[2], phi_p.r, phi_p.i);
                 } else {
-                    yx_c = link_phase_f(cmulc(phi_c, fx), phi_c, ph_xp, Ac[0], ma.dx);
-                    yy_c = link_phase_f(cmulc(phi_c, fy), phi_c, ph_yp, Ac[1], ma.dx);
-                    yz_c = link_phase_f(cmulc(phi_c, fz), phi_c, phi_p, Ac[2], ma.dx);
+                    float y[3];
+                    link_phases_f<3>({cmulc(phi_c, fx), cmulc(phi_c, fy), cmulc(phi_c, fz)}, phi_c,
+                                     {ph_xp, ph_yp, phi_p}, Ac, ma.dx, y);
+                    yx_c = y[0];
+                    yy_c = y[1];
+                    yz_c = y[2];
                 }
-                auto& sY = mx->Y[zs];
+                auto& sY = mx->Y[b];
                 sY[0][ro] = yx_c;
                 sY[1][ro] = yy_c;
                 sY[2][ro] = yz_c;
-                // the (x, z), (y, z) windings at x, plane z-1, now that Y_x, Y_y
-                // of plane z are known
-                if (active && z > z0) {
-                    const auto& sYb = mx->Y[zs ^ 1];
-                    wabs += abs(winding_of(yx_b, sYb[2][rxp], yx_c, yz_b, thxz_b)) +
-                            abs(winding_of(yy_b, sYb[2][ryp], yy_c, yz_b, thyz_b));
+                // the windings at x, plane z-1, now that its link phases are all
+                // there and Y_x, Y_y of plane z are known
+                const auto& sYb = mx->Y[b ^ 1];
+                if (z > z0) {
+                    const int w = abs(winding_of(yx_b, sYb[1][rxp], sYb[0][ryp], yy_b, th_b[0])) +
+                                  abs(winding_of(yx_b, sYb[2][rxp], yx_c, yz_b, th_b[1])) +
+                                  abs(winding_of(yy_b, sYb[2][ryp], yy_c, yz_b, th_b[2]));
+                    wabs += active ? w : 0;
                 }
+                yx_b = yx_c;
+                yy_b = yy_c;
+                yz_b = yz_c;
                 // plaquette angles at x, plane z, from the stored A
-                const auto& sA = mx->A[cur];
-                th_xy = ma.dx * ((((double)Ac[0] + (double)sA[1][rxp]) - (double)sA[0][ryp]) - (double)Ac[1]);
-                thxz_b = ma.dx * ((((double)Ac[0] + (double)sA[2][rxp]) - (double)Ap[0]) - (double)Ac[2]);
-                thyz_b = ma.dx * ((((double)Ac[1] + (double)sA[2][ryp]) - (double)Ap[1]) - (double)Ac[2]);
+                const auto& sA = mx->A[b];
+                const R q4[3][4] = {{Ac[0], sA[1][rxp], sA[0][ryp], Ac[1]},
+                                    {Ac[0], sA[2][rxp], Ap[0], Ac[2]},
+                                    {Ac[1], sA[2][ryp], Ap[1], Ac[2]}};
+                plaq_angles(ma.dx, dx, q4, th_b);
             }
             // plaquettes at x (F_ij^x, i<j)
-            const Cx<R> uy_xp = sU[cur][1][rxp], ux_yp = sU[cur][0][ryp];
-            const Cx<R> uz_xp = sU[cur][2][rxp], uz_yp = sU[cur][2][ryp];
+            const Cx<R> uy_xp = uy[rxp], ux_yp = ux[ryp];
+            const Cx<R> uz_xp = uz[rxp], uz_yp = uz[ryp];
             R sxy, sxz, syz, oxy = 0, oxz = 0, oyz = 0;
             if constexpr (MEAS) {
                 oxy = plaq_omc(Uc[0], uy_xp, ux_yp, Uc[1], &sxy);
@@ -575,9 +632,9 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
             const R fxz = sxz * inv_dx2;
             const R fyz = syz * inv_dx2;
             // plaquettes at x - kx and x - ky
-            const Cx<R> ux_xm_yp = sU[cur][0][rxm_yp], uy_xm = sU[cur][1][rxm], uz_xm = sU[cur][2][rxm];
-            const Cx<R> ux_ym = sU[cur][0][rym], uy_xp_ym = sU[cur][1][rxp_ym], uz_ym = sU[cur][2][rym];
-            const Cx<R> ux_xm_zp = sU[nxt][0][rxm], uy_ym_zp = sU[nxt][1][rym];
+            const Cx<R> ux_xm_yp = ux[rxm_yp], uy_xm = uy[rxm], uz_xm = uz[rxm];
+            const Cx<R> ux_ym = ux[rym], uy_xp_ym = uy[rxp_ym], uz_ym = uz[rym];
+            const Cx<R> ux_xm_zp = uxp[rxm], uy_ym_zp = uyp[rym];
             const R fxy_xm = plaq_sin(ux_xm, Uc[1], ux_xm_yp, uy_xm) * inv_dx2;
             const R fxy_ym = plaq_sin(ux_ym, uy_xp_ym, Uc[0], uy_ym) * inv_dx2;
             const R fxz_xm = plaq_sin(ux_xm, Uc[2], ux_xm_zp, uz_xm) * inv_dx2;
@@ -594,27 +651,30 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
             const R ne0 = fm(cE1, e_c[0], cE2 * fm(kappa, jx, -cx));
             const R ne1 = fm(cE1, e_c[1], cE2 * fm(kappa, jy, -cy));
             const R ne2 = fm(cE1, e_c[2], cE2 * fm(kappa, jz, -cz));
-            if (write && active) {
-                const int64_t o = (int64_t)z * NN;  // plane offset (uniform); + ob: the site
-                st_stream(wpr + o + ob, npr);
-                st_stream(wpi + o + ob, npi);
-                st_stream(we0 + o + ob, ne0);
-                st_stream(we1 + o + ob, ne1);
-                st_stream(we2 + o + ob, ne2);
-                st_stream(ophr + o + ob, fm(deta, npr, phi_c.r));
-                st_stream(ophi + o + ob, fm(deta, npi, phi_c.i));
-                st_stream(oa0 + o + ob, fm(deta, ne0, Ac[0]));
-                st_stream(oa1 + o + ob, fm(deta, ne1, Ac[1]));
-                st_stream(oa2 + o + ob, fm(deta, ne2, Ac[2]));
-            }
+            const int64_t o = (int64_t)z * NN;
+            const PlaneBufs wm = plane_bufs(a.b.om, a.b.fs, o, pb), wp = plane_bufs(a.b.op, a.b.fs, o, pb);
+            st_plane(wm.f[B_PIR], so, npr);
+            st_plane(wm.f[B_PII], so, npi);
+            st_plane(wm.f[B_E], so, ne0);
+            st_plane(wm.f[B_E + 1], so, ne1);
+            st_plane(wm.f[B_E + 2], so, ne2);
+            st_plane(wp.f[B_PHR], so, fm(deta, npr, phi_c.r));
+            st_plane(wp.f[B_PHI], so, fm(deta, npi, phi_c.i));
+            st_plane(wp.f[B_A], so, fm(deta, ne0, Ac[0]));
+            st_plane(wp.f[B_A + 1], so, fm(deta, ne1, Ac[1]));
+            st_plane(wp.f[B_A + 2], so, fm(deta, ne2, Ac[2]));
             if constexpr (MEAS) {
                 if (active) {
                     // site densities with centred momenta (average of the stored
                     // half step and the kick), summed in FP64
                     const R v[10] = {phi_c.r, phi_c.i, pr_c, pi_c, Ac[0], Ac[1], Ac[2], e_c[0], e_c[1], e_c[2]};
-                    bool bad = false;
-                    for (int k = 0; k < 10; ++k) bad |= !isfinite(v[k]);
-                    nonfin += bad ? 1 : 0;
+                    // 0 v is 0 for a finite v, else NaN
+                    R bad0 = 0, bad1 = 0;
+                    for (int k = 0; k < 5; ++k) {
+                        bad0 = fm(v[k], R(0), bad0);
+                        bad1 = fm(v[5 + k], R(0), bad1);
+                    }
+                    nonfin += bad0 + bad1 == R(0) ? 0 : 1;
                     const R pbr = R(0.5) * (pr_c + npr), pbi = R(0.5) * (pi_c + npi);
                     const double kin = (double)fm(pbr, pbr, pbi * pbi);
                     const R d0r = fx.r - phi_c.r, d0i = fx.i - phi_c.i;
@@ -629,23 +689,23 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
                     const double el = (double)(eb0 * eb0 + eb1 * eb1 + eb2 * eb2) * ma.inv_2e2f;
                     const double mag = (double)(R(2) * (oxy + oxz + oyz) * (inv_dx2 * inv_dx2)) * ma.inv_2e2f;
                     const double L = kin - grad - pot_e + el - mag;
-                    acc(M_KIN) += kin;
-                    acc(M_GRAD) += grad;
-                    acc(M_POT) += pot_e;
-                    acc(M_EL) += el;
-                    acc(M_MAG) += mag;
-                    acc(M_KINL) += kin * L;
-                    acc(M_GRADL) += grad * L;
+                    acc[M_KIN] += kin;
+                    acc[M_GRAD] += grad;
+                    acc[M_POT] += pot_e;
+                    acc[M_EL] += el;
+                    acc[M_MAG] += mag;
+                    acc[M_KINL] += kin * L;
+                    acc[M_GRADL] += grad * L;
                     // pressure and energy density for the equation-of-state estimator
                     const double pres = (kin - pot_e) + ((el + mag) - grad) * (1.0 / 3.0);
                     const double rho = ((kin + grad) + pot_e) + (el + mag);
-                    acc(M_PL) += pres * L;
-                    acc(M_RHOL) += rho * L;
+                    acc[M_PL] += pres * L;
+                    acc[M_RHOL] += rho * L;
                     if constexpr (GLDS) {
                         // G = sum_i (E_i^x - E_i^{x-i}) / dx - c Im[conj(phi) Pi] of the
                         // snapshot, in FP64 from the exactly widened stored values
-                        const double dv = (((double)e_c[0] - (double)mx->E[0][rxm]) * inv_dx64 +
-                                           ((double)e_c[1] - (double)mx->E[1][rym]) * inv_dx64) +
+                        const double dv = (((double)e_c[0] - (double)mx->E[b][0][rxm]) * inv_dx64 +
+                                           ((double)e_c[1] - (double)mx->E[b][1][rym]) * inv_dx64) +
                                           ((double)e_c[2] - (double)ezm) * inv_dx64;
                         const double crho = ma.gauss_c * ((double)phi_c.r * (double)pi_c -
                                                           (double)phi_c.i * (double)pr_c);
@@ -661,86 +721,83 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
             fyz_m = fyz;
             bz_m = cmulc(Uc[2], phi_c);  // for plane z+1
         }
+
         if (!MEAS && !more) break;
-        __syncthreads();  // all reads of slot cur and of sPhi (plane z) are done
 
-        if constexpr (MEAS) {
-            // winding of the (x, y) plaquette at x, plane z
-            if (active) {
-                const auto& sY = mx->Y[zs];
-                wabs += abs(winding_of(yx_c, sY[1][rxp], sY[0][ryp], yy_c, th_xy));
-            }
-            yx_b = yx_c;
-            yy_b = yy_c;
-            yz_b = yz_c;
-        }
-
-        if constexpr (LATE) prefetch(z, q1);
-        // ---- 3. plane z+2 links into slot cur, plane z+1 phi into sPhi
-        Cx<R> Upp[3];
-        if (more) {
-            for (int d = 0; d < 3; ++d) {
-                Upp[d] = link(dx, rA[d]);
-                sU[cur][d][ro] = Upp[d];
-                if constexpr (MEAS) mx->A[cur][d][ro] = rA[d];
-            }
-            if (has_halo) {
+        // ---- 2. planes z+1 and z+2 into LDS: phi and U_z of plane z+1 (U_z held
+        //         since the phase before), x and y links of plane z+2
+        sh.Phi[b ^ 1][ro] = phi_p;
+        if (has_halo) sh.Phi[b ^ 1][rh] = q.hphi;
+        if (!more) break;
+        Cx<R> u2[3];
+        if (has_halo) {
+            sh.Uz[b ^ 1][rh] = huz;
+            links(dx, q.ha, u2);
+            for (int d = 0; d < 2; ++d) sh.Uxy[s2][d][rh] = u2[d];
+            huz = u2[2];
+            if constexpr (MEAS)
                 for (int d = 0; d < 3; ++d) {
-                    sU[cur][d][rh] = link(dx, hA[d]);
-                    if constexpr (MEAS) mx->A[cur][d][rh] = hA[d];
+                    mx->A[b ^ 1][d][rh] = ha1[d];
+                    ha1[d] = q.ha[d];
                 }
-                sPhi[rh] = hphi;
-            }
-            sPhi[ro] = rphi;
-            if constexpr (GLDS) {
-                mx->E[0][ro] = q1.e[0];
-                mx->E[1][ro] = q1.e[1];
-                if (halo_e) mx->E[hEc][rh] = q1.he;
-            }
-        } else if constexpr (MEAS) {
-            if (has_halo) sPhi[rh] = hphi;
-            sPhi[ro] = rphi;
+            if constexpr (GLDS)
+                if (halo_e) mx->E[b ^ 1][hEc][rh] = halo_ex ? q.he.r : q.he.i;
         }
-        __syncthreads();
-
-        if (!more) {
-            if constexpr (MEAS) {
-                // own Y_x, Y_y of plane z1 complete the (x, z), (y, z) windings
-                // of the chunk's last plane
-                const Cx<R> px = sPhi[rxp], py = sPhi[ryp];
-                const Cx<R> ux_n = ULDS ? sU[nxt][0][ro] : Up[0], uy_n = ULDS ? sU[nxt][1][ro] : Up[1];
-                const float yx_n = phase(phi_p, ux_n, px, Ap[0]);
-                const float yy_n = phase(phi_p, uy_n, py, Ap[1]);
-                if (active) {
-                    const auto& sYb = mx->Y[zs];
-                    wabs += abs(winding_of(yx_b, sYb[2][rxp], yx_n, yz_b, thxz_b)) +
-                            abs(winding_of(yy_b, sYb[2][ryp], yy_n, yz_b, thyz_b));
-                }
-            }
-            break;
+        sh.Uz[b ^ 1][ro] = Up[2];
+        links(dx, q.a, u2);
+        for (int d = 0; d < 2; ++d) sh.Uxy[s2][d][ro] = u2[d];
+        if constexpr (MEAS)
+            for (int d = 0; d < 3; ++d) mx->A[b ^ 1][d][ro] = Ap[d];
+        if constexpr (GLDS) {
+            mx->E[b ^ 1][0][ro] = q.e[0];
+            mx->E[b ^ 1][1][ro] = q.e[1];
         }
 
-        // ---- 5. rotate the own-column registers
+        // ---- 3. rotate the own-column registers, and issue the loads of the
+        //         next phase
         if constexpr (GAUSS) ezm = e_c[2];
         if constexpr (GAUSS && !GLDS) {
-            ex_xm = q1.exm;
-            ey_ym = q1.eym;
+            ex_xm = q.exm;
+            ey_ym = q.eym;
         }
         for (int d = 0; d < 3; ++d) {
-            if constexpr (!ULDS) {
-                Uc[d] = Up[d];
-                Up[d] = Upp[d];
-            }
+            if constexpr (!ULDS) Uc[d] = Up[d];
+            if (!ULDS || d == 2) Up[d] = u2[d];
             Ac[d] = Ap[d];
-            Ap[d] = q1.a[d];
-            e_c[d] = q1.e[d];
+            Ap[d] = q.a[d];
+            e_c[d] = q.e[d];
         }
         phi_c = phi_p;
-        phi_p = q1.phi2;
-        pr_c = q1.pr;
-        pi_c = q1.pi;
-        if constexpr (D2) q1 = q2;
-        cur = nxt;
+        phi_p = q.phi2;
+        pr_c = q.pr;
+        pi_c = q.pi;
+        // Measured march: issued before the barrier, which hides more of their
+        // latency.  Plain march, which memory bounds: after it, and with the
+        // plane's stores complete, so that the workgroups that share an L2 stay
+        // within a plane of each other and their halo reads hit it.
+        if constexpr (MEAS) prefetch(z + 1, q);
+        if constexpr (!MEAS) __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        __syncthreads();
+        if constexpr (!MEAS)
+            if (z + 2 < z1) prefetch(z + 1, q);
+        const int t = s0;
+        s0 = s1;
+        s1 = s2;
+        s2 = t;
+    }
+    if constexpr (MEAS) {
+        // own Y_x, Y_y of plane z1 complete the windings of the chunk's last plane
+        __syncthreads();
+        const int b = (z1 - 1 - z0) & 1, rxp = ro + 1, ryp = ro + RW;
+        const Cx<R>* sPhi = sh.Phi[b ^ 1];
+        const float yx_n = phase(phi_p, Up[0], sPhi[rxp], Ap[0]);
+        const float yy_n = phase(phi_p, Up[1], sPhi[ryp], Ap[1]);
+        if (active) {
+            const auto& sYb = mx->Y[b];
+            wabs += abs(winding_of(yx_b, sYb[1][rxp], sYb[0][ryp], yy_b, th_b[0])) +
+                    abs(winding_of(yx_b, sYb[2][rxp], yx_n, yz_b, th_b[1])) +
+                    abs(winding_of(yy_b, sYb[2][ryp], yy_n, yz_b, th_b[2]));
+        }
     }
 
     if constexpr (MEAS) {
@@ -749,7 +806,7 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
         auto& red = mx->red;
         const int lane = tid & 63, wv = tid >> 6;
         for (int k = 0; k < kMarchSums; ++k) {
-            const double r = wave_sum(acc(k));
+            const double r = wave_sum(acc[k]);
             if (lane == 0) red[wv][k] = r;
         }
         const double rw = wave_sum((double)wabs), rn = wave_sum((double)nonfin);
@@ -781,26 +838,14 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
 
 // Waves per SIMD the compiler must leave room for.  The plain FP32 march
 // fits in 128 registers, i.e. four waves per SIMD: two 512-thread workgroups
-// per CU, so one can load while the other waits at a barrier.  Left to itself
-// the compiler may take a few more registers, which drops a 512-thread tile
-// to one workgroup per CU.  FP64 fits two waves per SIMD (its measured march
-// only with its sums in LDS and its loads issued late).  Three waves of the
-// plain FP64 march on 256-thread tiles, which fit 168 registers only with
-// late loads (or spill with early ones), ran slower than two on 64 x 8.  The
-// FP32 measured march needs more than 128 registers and is left free.
+// per CU, so one can load while the other waits at a barrier.  FP64 fits two
+// (its measured march takes 255 registers).  The FP32 measured march takes 176
+// and runs two; held to 168 for three it spills, and runs 30% slower.
 template <typename R, bool MEAS>
 constexpr int kMinWaves = sizeof(R) == 8 ? 2 : (MEAS ? 1 : 4);
 
-// Tile shapes with a measured instance.  Lattices are measured on 64 x 8
-// (FP32) and 32 x 8 (FP64) tiles; pool lattices, whose one shape serves both
-// nodes, run FP32 shapes of up to 512 threads and FP64 on 32 x 8.  (The
-// 1024-thread FP32 shapes would spill; the FP64 measured march fits two
-// waves per SIMD only on 32 x 8.)
-template <typename R>
-constexpr bool has_measured(int tx, int ty)
-{
-    return sizeof(R) == 8 ? (tx == 32 && ty == 8) : tx * ty <= 512;
-}
+// The tile shape of the measured march (measured_tile).
+constexpr bool has_measured(int tx, int ty) { return tx == 32 && ty == 8; }
 
 // One lattice: block b owns tile t = xcd_tile(b) (tx fastest, then ty, then
 // z-chunk); with MEAS it writes diagnostics record t, so the records are in
@@ -853,20 +898,9 @@ __global__ void __launch_bounds__(TX* TY, (kMinWaves<R, MEAS>)) k_step_batch(con
     const double* row = L.coef + k * kCoefStride;
     const int cur = (int)L.counter[2], curm = (int)L.counter[3];
     StepArgs<R> a;
-    a.f = Fields<R>{(R*)L.pp[cur][0], (R*)L.pp[cur][1], (R*)L.mom[curm][0], (R*)L.mom[curm][1], (R*)L.pp[cur][2],
-                    (R*)L.pp[cur][3], (R*)L.pp[cur][4], (R*)L.mom[curm][2], (R*)L.mom[curm][3], (R*)L.mom[curm][4]};
-    a.ophr = (R*)L.pp[cur ^ 1][0];
-    a.ophi = (R*)L.pp[cur ^ 1][1];
-    a.oa0 = (R*)L.pp[cur ^ 1][2];
-    a.oa1 = (R*)L.pp[cur ^ 1][3];
-    a.oa2 = (R*)L.pp[cur ^ 1][4];
     // Pi and E in place, but out of place for the measured march
-    const int om = MEAS ? curm ^ 1 : curm;
-    a.opr = (R*)L.mom[om][0];
-    a.opi = (R*)L.mom[om][1];
-    a.oe0 = (R*)L.mom[om][2];
-    a.oe1 = (R*)L.mom[om][3];
-    a.oe2 = (R*)L.mom[om][4];
+    a.b = Blocks<R>{(const R*)L.pp[cur], (const R*)L.mom[curm], (R*)L.pp[cur ^ 1],
+                    (R*)L.mom[MEAS ? curm ^ 1 : curm], L.fs};
     a.N = L.N;
     a.P = L.P;
     a.dx = (R)L.dx;
@@ -955,17 +989,7 @@ hipError_t launch_step_tile(const Fields<R>& in, const Fields<R>& out, const Lat
                         out.e2 == in.e2))
         return hipErrorInvalidValue;
     StepArgs<R> a;
-    a.f = in;
-    a.ophr = out.phr;
-    a.ophi = out.phi;
-    a.oa0 = out.a0;
-    a.oa1 = out.a1;
-    a.oa2 = out.a2;
-    a.opr = out.pir;
-    a.opi = out.pii;
-    a.oe0 = out.e0;
-    a.oe1 = out.e1;
-    a.oe2 = out.e2;
+    if (!blocks_of(in, out, &a.b)) return hipErrorInvalidValue;
     a.N = N;
     a.P = L.P;
     a.dx = (R)L.dx;
@@ -1000,10 +1024,10 @@ hipError_t launch_step_tile(const Fields<R>& in, const Fields<R>& out, const Lat
         }                                                                                                          \
         return hipGetLastError();                                                                                 \
     }
-    AH_TILE_CASE(64, 8, has_measured<R>(64, 8))
-    AH_TILE_CASE(64, 4, has_measured<R>(64, 4))
-    AH_TILE_CASE(32, 8, has_measured<R>(32, 8))
-    AH_TILE_CASE(128, 4, has_measured<R>(128, 4))
+    AH_TILE_CASE(64, 8, has_measured(64, 8))
+    AH_TILE_CASE(64, 4, has_measured(64, 4))
+    AH_TILE_CASE(32, 8, has_measured(32, 8))
+    AH_TILE_CASE(128, 4, has_measured(128, 4))
     if constexpr (sizeof(R) == 4) {
         AH_TILE_CASE(64, 16, false)
         AH_TILE_CASE(128, 8, false)
@@ -1025,13 +1049,8 @@ hipError_t launch_step_batch(const PoolLattice* lat, const WorkItem* work, int n
     // plain node: the shapes of batch_tile_supported; measured node: the
     // measured march's shape (measured_tile)
     if (measured) {
-        int mx = 0, my = 0;
-        (void)measured_tile(sizeof(R) == 8 ? AH_FP64 : AH_FP32, &mx, &my);
-        if (tx != mx || ty != my) return hipErrorInvalidValue;
-        if constexpr (sizeof(R) == 8)
-            hipLaunchKernelGGL((k_step_batch<R, 32, 8, true>), dim3(grid), dim3(256), 0, s, lat, work, nwork);
-        else
-            hipLaunchKernelGGL((k_step_batch<R, 64, 8, true>), dim3(grid), dim3(512), 0, s, lat, work, nwork);
+        if (!has_measured(tx, ty)) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((k_step_batch<R, 32, 8, true>), dim3(grid), dim3(256), 0, s, lat, work, nwork);
         return hipGetLastError();
     }
     if (!batch_tile_supported(sizeof(R) == 8 ? AH_FP64 : AH_FP32, tx, ty)) return hipErrorInvalidValue;
