@@ -10,12 +10,22 @@
 // (region R1, (TX+2) x (TY+2)), which needs links and phi of snapshot n on a
 // two-site ring (region R2, (TX+4) x (TY+4)).  Step n+1 -> n+2 ("stage 2")
 // is computed on the tile from stage 1's values in LDS.  The workgroup walks
-// its z-chunk plane by plane with stage 2 one plane behind stage 1:
-//   (a) stage 1 at plane p on R1 (tile threads and ring threads);
-//   (b) barrier;
-//   (c) stage 2 at plane p-1 on the tile, stores of snapshot n+2;
-//       links of plane p+2 and phi of plane p+1 for stage 1 into LDS;
-//   (d) barrier.
+// its z-chunk in phases of one plane and one barrier.  Phase p is
+//   - stage 1 at plane p on R1 (tile waves and ring waves);
+//   - stage 2 at plane p-2 on the tile, stores of snapshot n+2;
+//   - links of plane p+2 and phi of plane p+1 of snapshot n into LDS,
+// with enough slots in LDS that nothing a phase writes is read before its
+// barrier.  The two stages of a phase are then independent instructions of
+// one wave.
+//
+// What bounds it: instruction issue and latency (512^3 FP32 on 64 x 8 tiles,
+// one 11-wave workgroup per CU: vector ALU busy 67%; HBM 3.7 TB/s).  MI355X,
+// us per step, against stage 2 one plane behind stage 1 with a barrier behind
+// each of them (half the LDS, two barriers a plane): 512^3 FP32 64 x 8 1468
+// against 1677, FP64 32 x 8 3774 against 4420; 64^3 FP32 7.7 against 8.4, FP64
+// 14.9 against 16.1.  Running stage 2 before stage 1 within a phase: 1513 and
+// 4103 at 512^3.
+//
 // Stage 1 reads Pi and E of snapshot n on the ring too, which the
 // neighbouring workgroups' stage 2 would overwrite in place, so Pi and E are
 // double-buffered: the pass reads (phi, A, Pi, E) from one set of buffers
@@ -26,6 +36,8 @@
 // to two single steps.
 #include "ah_internal.h"
 #include "ah_stencil.h"
+
+#include <type_traits>
 
 #pragma clang fp contract(off)
 
@@ -44,16 +56,19 @@ struct Geom2 {
 };
 
 // LDS of one workgroup.  Stage-1 links and phi live on R2, stage-2 ones on
-// R1.  x and y links are kept for two planes (p and p+1: the plaquettes at
-// x-kx and x-ky reach one plane up), z links and phi for one.
+// R1.  x and y links are kept for three planes (a phase reads two, as the
+// plaquettes at x-kx and x-ky reach one plane up, and writes the third), z
+// links and phi for two.
 template <typename R, int TX, int TY>
 struct Shared2 {
     using G = Geom2<TX, TY>;
-    Cx<R> u0x[2][G::S2], u0y[2][G::S2], u0z[G::S2], p0[G::S2];
-    Cx<R> u1x[2][G::S1], u1y[2][G::S1], u1z[G::S1], p1[G::S1];
-    // stage-1 results at the tile sites that stage 2 takes one plane later
-    // (Pi, E of snapshot n+1/2 and A of snapshot n+1), by plane parity
-    R h1[2][8][G::NT];
+    Cx<R> u0x[3][G::S2], u0y[3][G::S2], u0z[2][G::S2], p0[2][G::S2];
+    Cx<R> u1x[3][G::S1], u1y[3][G::S1], u1z[2][G::S1], p1[2][G::S1];
+    // FP64, where they fit: stage 1's Pi, E and A of a tile site for stage 2
+    // two planes later (registers otherwise)
+    static constexpr bool HELD =
+        sizeof(R) == 8 && sizeof(Cx<R>) * 10 * (G::S1 + G::S2) + sizeof(R) * 16 * G::NT <= 160 * 1024;
+    R h[2][8][HELD ? G::NT : 1];
 };
 
 template <typename R>
@@ -94,13 +109,11 @@ __device__ __forceinline__ SiteNbr<R> gather_nbr(int c, const Cx<R>* ux, const C
 
 template <int TX, int TY>
 constexpr int kStep2Threads = Geom2<TX, TY>::NTH;
-// Waves per SIMD the register allocation leaves room for: FP64 two (its
-// stage state needs up to 256 registers); FP32 three (168 registers: one
-// 11-wave 64 x 8 or two 7-wave 64 x 4 workgroups per CU), four for the
-// 6-wave 32 x 8 workgroup (128 registers; the pool's instance then spills
-// a few bytes and still runs faster).
+// Waves per SIMD the register allocation leaves room for: FP64 two (it takes
+// 253 registers on 32 x 8); FP32 three (143 registers: one 11-wave 64 x 8 or
+// 7-wave 64 x 4, or two 6-wave 32 x 8 workgroups per CU).
 template <typename R, int TX, int TY>
-constexpr int kStep2MinWaves = sizeof(R) == 8 ? 2 : (Geom2<TX, TY>::NTH <= 384 ? 4 : 3);
+constexpr int kStep2MinWaves = sizeof(R) == 8 ? 2 : 3;
 
 // Two steps of planes [z0, z1) of the tile whose lower corner is (x0, y0), as
 // the waves that own tile sites (TILE) or ring sites run them.  All threads of
@@ -161,8 +174,8 @@ __device__ __forceinline__ void march2_role(Shared2<R, TX, TY>& sh, const Step2A
             oy = 1 + (o - 2 * W2 - (H2 - 2));
         }
     }
-    const int c1 = rx + W1 * ry;              // R1 index of the stage-1 site
-    const int c2 = (rx + 1) + W2 * (ry + 1);  // its R2 index
+    int c1 = rx + W1 * ry;                    // R1 index of the stage-1 site
+    int c2 = (rx + 1) + W2 * (ry + 1);        // its R2 index
     const int co = ox + W2 * oy;              // R2 index of the outer site
     // byte offsets in a plane: of the stage-1 site, of the outer site, and for
     // the stores (kNoSite for lanes past a ragged edge)
@@ -180,19 +193,24 @@ __device__ __forceinline__ void march2_role(Shared2<R, TX, TY>& sh, const Step2A
     // ---- stage-1 column state (snapshot n at the stage-1 site).  The
     //      site's own links of planes p and p+1 are read back from LDS.
     R ac[3], ap[3];      // A at planes p, p+1
-    Cx<R> upz;           // U_z at plane p+1 (into LDS once plane p is done)
+    Cx<R> upz;           // U_z at plane p+1 (into LDS during phase p)
     Cx<R> uz_m;          // U_z at plane p-1
     R fxz_m, fyz_m;      // F_xz, F_yz at plane p-1
     Cx<R> phm, phc, php; // phi at planes p-1, p, p+1
     R pr, pi, e[3];      // Pi, E at plane p
-    Cx<R> uo_z = {};     // outer site: U_z of the plane above the one in u0z
-    // ---- stage-2 column state (snapshot n+1 at the tile site); the site's
-    //      Pi, E and A come from stage 1 through LDS
+    Cx<R> uo_z = {};     // outer site: U_z of plane p+1
+    // ---- stage-2 column state (snapshot n+1 at the tile site)
+    R hr[2][8];              // Pi, E, A of planes p-1, p-2, by parity
+    auto h = [&](int b, int k) -> R& {
+        if constexpr (Shared2<R, TX, TY>::HELD)
+            return sh.h[b][k][TILE ? tid : 0];
+        else
+            return hr[b][k];
+    };
     Cx<R> vz_m = {};         // U_z^{n+1} at q-1
     R gxz_m = 0, gyz_m = 0;  // F^{n+1}_xz, F^{n+1}_yz at q-1
     Cx<R> chm = {};          // phi^{n+1} at q-1
-    // stage-1 phi and U_z of plane p, into LDS when stage 2 has finished with
-    // plane p-1 (its x, y links go there at once)
+    // stage-1 phi and U_z of plane p-1, into LDS during phase p
     Cx<R> s1phi = {}, s1z = {};
 
     // Operands loaded one iteration ahead: A of plane p+2 (stage-1 site and
@@ -242,139 +260,161 @@ __device__ __forceinline__ void march2_role(Shared2<R, TX, TY>& sh, const Step2A
         for (int d = 0; d < 3; ++d) e[d] = ld(mm1.f[B_E + d], ob);
         prefetch(z0 - 1);
 
-        // plane z0-2: U_z on R2 into u0z (for F^n at z0-2), own x, y links;
-        // plane z0-1: x, y links into their slot, z held, phi
-        const int s_m1 = (z0 - 1) & 1, s_0 = z0 & 1;
-        Cx<R> um2[3], uc[3], up[3], uo[7];
+        // planes z0-1 and z0: x, y links into slots 0 and 1; U_z and phi of
+        // z0-1 into slot 0, U_z of z0-2 (for F^n there) into slot 1
+        Cx<R> um2[3], uc[3], up[3];
         links(dx, am2, um2);
-        sh.u0z[c2] = um2[2];
+        sh.u0z[1][c2] = um2[2];
         uz_m = um2[2];
         links(dx, ac, uc);
-        sh.u0x[s_m1][c2] = uc[0];
-        sh.u0y[s_m1][c2] = uc[1];
-        sh.p0[c2] = phc;
-        if constexpr (!TILE) {
-            links(dx, om, uo);
-            sh.u0z[co] = uo[0];
-            sh.u0x[s_m1][co] = uo[1];
-            sh.u0y[s_m1][co] = uo[2];
-            sh.p0[co] = oph;
-        }
+        sh.u0x[0][c2] = uc[0];
+        sh.u0y[0][c2] = uc[1];
+        sh.u0z[0][c2] = uc[2];
+        sh.p0[0][c2] = phc;
         links(dx, ap, up);
-        __syncthreads();
-        // F^n_xz, F^n_yz at z0-2 of the stage-1 site
-        fxz_m = plaq_sin(um2[0], sh.u0z[c2 + 1], uc[0], um2[2]) * k0.inv_dx2;
-        fyz_m = plaq_sin(um2[1], sh.u0z[c2 + W2], uc[1], um2[2]) * k0.inv_dx2;
-        __syncthreads();
-        // U_z of z0-1 into u0z; plane z0 links: x, y into their slot, z held
-        sh.u0z[c2] = uc[2];
-        sh.u0x[s_0][c2] = up[0];
-        sh.u0y[s_0][c2] = up[1];
+        sh.u0x[1][c2] = up[0];
+        sh.u0y[1][c2] = up[1];
         upz = up[2];
         if constexpr (!TILE) {
-            sh.u0z[co] = uo[3];
-            sh.u0x[s_0][co] = uo[4];
-            sh.u0y[s_0][co] = uo[5];
+            Cx<R> uo[7];
+            links(dx, om, uo);
+            sh.u0z[1][co] = uo[0];
+            sh.u0x[0][co] = uo[1];
+            sh.u0y[0][co] = uo[2];
+            sh.u0z[0][co] = uo[3];
+            sh.p0[0][co] = oph;
+            sh.u0x[1][co] = uo[4];
+            sh.u0y[1][co] = uo[5];
             uo_z = uo[6];
         }
         __syncthreads();
+        // F^n_xz, F^n_yz at z0-2 of the stage-1 site
+        fxz_m = plaq_sin(um2[0], sh.u0z[1][c2 + 1], uc[0], um2[2]) * k0.inv_dx2;
+        fyz_m = plaq_sin(um2[1], sh.u0z[1][c2 + W2], uc[1], um2[2]) * k0.inv_dx2;
+        __syncthreads();
     }
 
-    for (int p = z0 - 1; p <= z1; ++p) {
-        const bool more = p < z1;
-        if (more && p > z0 - 1) prefetch(p);
-        const int sp = p & 1, sq = sp ^ 1;  // LDS slots of planes p (and p+2) and p+1 (and p-1)
+    // Slots of the x and y links: planes p, p+1 and p+2 of snapshot n, and
+    // planes p, p-2 and p-1 of snapshot n+1.
+    int sa = 0, sb = 1, sc = 2;
 
-        // ---- (a) stage 1 at plane p; the previous plane's phi and U_z of
-        //      snapshot n+1 go into LDS first (stage 2 reads them this time)
-        {
-            if (TILE) chm = sh.p1[c1];  // phi^{n+1} of plane p-2, before it is replaced
-            sh.p1[c1] = s1phi;
-            sh.u1z[c1] = s1z;
-            const Cx<R> uc[3] = {sh.u0x[sp][c2], sh.u0y[sp][c2], sh.u0z[c2]};
-            const SiteNbr<R> nb = gather_nbr<R, W2>(c2, sh.u0x[sp], sh.u0y[sp], sh.u0z, sh.p0, sh.u0x[sq], sh.u0y[sq]);
-            const SiteOut<R> o = site_update(k0, nb, phm, phc, php, uc, sh.u0x[sq][c2], sh.u0y[sq][c2], uz_m, fxz_m,
-                                             fyz_m, pr, pi, e, ac);
-            fxz_m = o.fxz;
-            fyz_m = o.fyz;
-            if constexpr (TILE) {
-                R* h = &sh.h1[sp][0][tid];
-                h[0 * NT] = o.pr;
-                h[1 * NT] = o.pi;
-                for (int d = 0; d < 3; ++d) {
-                    h[(2 + d) * NT] = o.e[d];
-                    h[(5 + d) * NT] = o.a[d];
-                }
-            }
-            s1phi = o.phi;
-            Cx<R> u1[3];
-            links(dx, o.a, u1);
-            sh.u1x[sp][c1] = u1[0];
-            sh.u1y[sp][c1] = u1[1];
+    // Phase p: stage 1 at plane p (S1), stage 2 at plane q = p-2 (S2).  What
+    // it writes to LDS, no wave reads before the barrier that ends it.
+    // `par`: the parity of p - (z0-1), the slot of planes p and p-2 where
+    // there are two.
+    auto phase = [&](auto par, auto s1, auto s2, int p) __attribute__((always_inline)) {
+        constexpr int b = decltype(par)::value;
+        constexpr bool S1 = decltype(s1)::value, S2 = decltype(s2)::value && TILE;
+        const bool more = p < z1;  // there is a stage 1 in the next phase
+        // the LDS addresses anew in each phase, rather than some thirty of
+        // them held in registers through the march (143 registers, not spills)
+        asm volatile("" : "+v"(c1), "+v"(c2));
+        if (S1 && more && p > z0 - 1) prefetch(p);
+
+        const Cx<R> phq = s1phi;  // phi^{n+1} of plane p-1 = q+1
+        sh.p1[b ^ 1][c1] = s1phi;
+        sh.u1z[b ^ 1][c1] = s1z;
+        SiteOut<R> o1 = {}, o2 = {};
+        Cx<R> u1[3];
+        if constexpr (S1) {
+            const Cx<R> *ux = sh.u0x[sa], *uy = sh.u0y[sa], *uz = sh.u0z[b], *uxp = sh.u0x[sb], *uyp = sh.u0y[sb];
+            const Cx<R> uc[3] = {ux[c2], uy[c2], uz[c2]};
+            const SiteNbr<R> nb = gather_nbr<R, W2>(c2, ux, uy, uz, sh.p0[b], uxp, uyp);
+            o1 = site_update(k0, nb, phm, phc, php, uc, uxp[c2], uyp[c2], uz_m, fxz_m, fyz_m, pr, pi, e, ac);
+            fxz_m = o1.fxz;
+            fyz_m = o1.fyz;
+            uz_m = uc[2];
+            links(dx, o1.a, u1);
+            sh.u1x[sa][c1] = u1[0];
+            sh.u1y[sa][c1] = u1[1];
+            s1phi = o1.phi;
             s1z = u1[2];
         }
-        __syncthreads();
-
-        // ---- (c) stage 2 at plane q = p-1 on the tile.  The step of plane
-        //      z0-1 only starts the carry (F^{n+1}_xz, F^{n+1}_yz, U_z): its
-        //      stores are dropped, as are those of the iteration before it, so
-        //      that every iteration issues the same ones.
-        if constexpr (TILE) {
-            SiteOut<R> o = {};
-            if (p >= z0) {
-                const int c = c1;
-                const Cx<R> vc[3] = {sh.u1x[sq][c], sh.u1y[sq][c], sh.u1z[c]};
-                const R* h = &sh.h1[sq][0][tid];
-                const R qe[3] = {h[2 * NT], h[3 * NT], h[4 * NT]};
-                const R bc[3] = {h[5 * NT], h[6 * NT], h[7 * NT]};
-                const SiteNbr<R> nb = gather_nbr<R, W1>(c, sh.u1x[sq], sh.u1y[sq], sh.u1z, sh.p1, sh.u1x[sp], sh.u1y[sp]);
-                o = site_update(k1, nb, chm, sh.p1[c], s1phi, vc, sh.u1x[sp][c], sh.u1y[sp][c], vz_m, gxz_m, gyz_m,
-                                h[0], h[NT], qe, bc);
-                gxz_m = o.fxz;
-                gyz_m = o.fyz;
-                vz_m = vc[2];
-            }
-            const int64_t oq = (int64_t)(p > z0 ? p - 1 : z0) * NN;
-            const uint32_t sq_o = p > z0 ? so : kNoSite;
+        if constexpr (S2) {
+            const Cx<R> *ux = sh.u1x[sb], *uy = sh.u1y[sb], *uz = sh.u1z[b], *uxp = sh.u1x[sc], *uyp = sh.u1y[sc];
+            const Cx<R> vc[3] = {ux[c1], uy[c1], uz[c1]}, chc = sh.p1[b][c1];
+            const R qe[3] = {h(b, 2), h(b, 3), h(b, 4)}, qa[3] = {h(b, 5), h(b, 6), h(b, 7)};
+            const SiteNbr<R> nb = gather_nbr<R, W1>(c1, ux, uy, uz, sh.p1[b], uxp, uyp);
+            o2 = site_update(k1, nb, chm, chc, phq, vc, uxp[c1], uyp[c1], vz_m, gxz_m, gyz_m, h(b, 0), h(b, 1), qe, qa);
+            gxz_m = o2.fxz;
+            gyz_m = o2.fyz;
+            vz_m = vc[2];
+            chm = chc;
+            // plane z0-1 only starts the carry (F^{n+1}_xz, F^{n+1}_yz, U_z,
+            // phi): its stores are dropped
+            const int q = p - 2 < z0 ? z0 : p - 2;
+            const uint32_t off = p - 2 < z0 ? kNoSite : so;
+            const int64_t oq = (int64_t)q * NN;
             const PlaneBufs wm = plane_bufs(a.b.om, a.b.fs, oq, pb), wp = plane_bufs(a.b.op, a.b.fs, oq, pb);
-            st_plane(wm.f[B_PIR], sq_o, o.pr);
-            st_plane(wm.f[B_PII], sq_o, o.pi);
-            for (int d = 0; d < 3; ++d) st_plane(wm.f[B_E + d], sq_o, o.e[d]);
-            st_plane(wp.f[B_PHR], sq_o, o.phi.r);
-            st_plane(wp.f[B_PHI], sq_o, o.phi.i);
-            for (int d = 0; d < 3; ++d) st_plane(wp.f[B_A + d], sq_o, o.a[d]);
+            st_plane(wm.f[B_PIR], off, o2.pr);
+            st_plane(wm.f[B_PII], off, o2.pi);
+            for (int d = 0; d < 3; ++d) st_plane(wm.f[B_E + d], off, o2.e[d]);
+            st_plane(wp.f[B_PHR], off, o2.phi.r);
+            st_plane(wp.f[B_PHI], off, o2.phi.i);
+            for (int d = 0; d < 3; ++d) st_plane(wp.f[B_A + d], off, o2.a[d]);
         }
-        if (!more) break;
-
-        // ---- stage-1 operands of plane p+1: U_z of p+1 and phi of p+1 into
-        //      LDS, links of plane p+2 (x, y into slot sp, z held)
-        uz_m = sh.u0z[c2];
-        sh.u0z[c2] = upz;
-        sh.p0[c2] = php;
-        Cx<R> un[3];
-        links(dx, na, un);
-        sh.u0x[sp][c2] = un[0];
-        sh.u0y[sp][c2] = un[1];
-        upz = un[2];
-        if constexpr (!TILE) {
-            sh.u0z[co] = uo_z;
-            sh.p0[co] = noph;
-            links(dx, noa, un);
-            sh.u0x[sp][co] = un[0];
-            sh.u0y[sp][co] = un[1];
-            uo_z = un[2];
+        if constexpr (S1) {
+            if constexpr (TILE) {
+                h(b, 0) = o1.pr;
+                h(b, 1) = o1.pi;
+                for (int d = 0; d < 3; ++d) {
+                    h(b, 2 + d) = o1.e[d];
+                    h(b, 5 + d) = o1.a[d];
+                }
+            }
+            if (more) {
+                // stage-1 operands of the next phase: U_z and phi of plane
+                // p+1, links of plane p+2 (U_z held)
+                sh.u0z[b ^ 1][c2] = upz;
+                sh.p0[b ^ 1][c2] = php;
+                Cx<R> un[3];
+                links(dx, na, un);
+                sh.u0x[sc][c2] = un[0];
+                sh.u0y[sc][c2] = un[1];
+                upz = un[2];
+                if constexpr (!TILE) {
+                    sh.u0z[b ^ 1][co] = uo_z;
+                    sh.p0[b ^ 1][co] = noph;
+                    links(dx, noa, un);
+                    sh.u0x[sc][co] = un[0];
+                    sh.u0y[sc][co] = un[1];
+                    uo_z = un[2];
+                }
+                for (int d = 0; d < 3; ++d) {
+                    ac[d] = ap[d];
+                    ap[d] = na[d];
+                    e[d] = ne[d];
+                }
+                phm = phc;
+                phc = php;
+                php = nph;
+                pr = npr;
+                pi = npi;
+            }
+            __syncthreads();
+            const int t = sa;
+            sa = sb;
+            sb = sc;
+            sc = t;
         }
-        for (int d = 0; d < 3; ++d) {
-            ac[d] = ap[d];
-            ap[d] = na[d];
-            e[d] = ne[d];
+    };
+    const std::integral_constant<int, 0> even;
+    const std::integral_constant<int, 1> odd;
+    const std::true_type yes;
+    const std::false_type no;
+    phase(even, yes, no, z0 - 1);
+    phase(odd, yes, no, z0);
+    for (int p = z0 + 1;; p += 2) {
+        phase(even, yes, yes, p);
+        if (p == z1) {
+            phase(odd, no, yes, p + 1);
+            break;
         }
-        phm = phc;
-        phc = php;
-        php = nph;
-        pr = npr;
-        pi = npi;
-        __syncthreads();
+        phase(odd, yes, yes, p + 1);
+        if (p + 1 == z1) {
+            phase(even, no, yes, p + 2);
+            break;
+        }
     }
 }
 
