@@ -203,7 +203,10 @@ int ah_measure(ah_handle* h, ah_measurement* out);
 int ah_get_winding(ah_handle* h, int8_t* host_w);
 
 /* ------------------------------------------------------ step kernel choice */
-#define AH_KERNEL_AUTO 0 /* tiled kernel for the compact action, site kernel otherwise */
+#define AH_KERNEL_AUTO 0 /* tiled kernel for the compact action, site kernel otherwise; with the tiling left
+                          * automatic too, two plain steps that follow each other run as one pass
+                          * (AH_KERNEL_TILE2) where that is faster (N > 64), except while the stream is
+                          * being captured; ah_get_step_config reports the one-step tiling */
 #define AH_KERNEL_SITE 1 /* one thread per site, every neighbour read from global memory */
 #define AH_KERNEL_TILE 2 /* z-marching tiles with links shared through LDS (compact action only) */
 #define AH_KERNEL_TILE2 3 /* as AH_KERNEL_TILE, with two steps per pass over the fields wherever two plain
@@ -224,9 +227,9 @@ typedef struct ah_step_config {
                              * highest measured rate once the idle lanes of a ragged last tile are
                              * counted (one step), (32,8) (two steps) */
     int32_t zchunk;         /* x2-planes per workgroup of the tiled kernel; 0 = automatic: equal chunks,
-                             * the count that minimises (rounds of resident workgroups) x (planes per
-                             * chunk + 2); else >= 2 for N <= 128 and >= 8 above (the last chunk of a
-                             * column may be shorter) */
+                             * the count of the least estimated time (rounds of resident workgroups x
+                             * planes of a chunk and its start); else >= 2 for N <= 128 and >= 8 above
+                             * (the last chunk of a column may be shorter) */
 } ah_step_config;
 
 /* Select the step kernel; AH_E_INVAL for an unsupported combination. */
@@ -289,10 +292,10 @@ int ah_tune_load(const char* path);
  * forms every diagnostic, the Gauss residual included) and its fixed-order
  * fold, the plain step of every other active lattice (one kernel node per precision and
  * tile shape, one block per (lattice, tile) work item) and a counter update;
- * an FP32 lattice whose next two snapshots are both not due takes a
- * two-step pass instead (AH_KERNEL_TILE2; 64 x 8 unless its tuning entry
- * names another two-step shape), which advances it by two steps in that
- * replay.  Pool lattices run the tuned one-step (else the default) tile
+ * a lattice (FP64: with N > 64 or a two-step tuning entry) whose next two
+ * snapshots are both not due takes a two-step pass instead (AH_KERNEL_TILE2;
+ * FP32 64 x 8, FP64 32 x 8, unless its tuning entry names another two-step
+ * shape), which advances it by two steps in that replay.  Pool lattices run the tuned one-step (else the default) tile
  * shape with z-chunks of at least 16 planes (ah_pool_step_config reports
  * them), and their measured steps the measured march's tiling, as a lattice
  * alone does.  Every lattice takes the coefficients of its own step from its own

@@ -175,6 +175,9 @@ bool default_tile(int precision, int N, int* tx, int* ty);
 int resident_per_cu(int kernel, int precision, int tx, int ty, bool measured);
 // Automatic z-chunk of a tiled launch.
 int auto_zchunk(int kernel, int precision, int N, int tx, int ty, bool measured);
+// Tiling of the two-step passes of an automatic configuration; false if it
+// takes none.
+bool default_two(int precision, int N, TileConfig* two);
 // Tiling of the measured march of a lattice stepped with cfg (resolved).
 TileConfig measured_tiling(const ah_params& p, const ah_step_config& cfg);
 

@@ -596,12 +596,12 @@ int ah_pool_create(size_t hbm_budget, int32_t max_slots, void* hip_stream, ah_po
 // the pool's step is built for its shape (a two-step entry lends its tile
 // shape, with the automatic z-chunk), else the default, as for a lattice run
 // alone; z-chunks of at least 16 planes.  The measured node runs the
-// measured march's tiling (measured_tiling), as a lattice alone does.  FP32
-// lattices also take two-step passes wherever neither of two snapshots is
-// due (two): on the tuned two-step tile shape, else 64 x 8, with the
-// automatic z-chunk of at least 16 planes; on MI355X the pass beats the
-// single step at every FP32 size measured (65 .. 512) and loses at every
-// FP64 size.
+// measured march's tiling (measured_tiling), as a lattice alone does.
+// Lattices also take two-step passes wherever neither of two snapshots is
+// due (two), with the automatic z-chunk of at least 16 planes, on the tuned
+// two-step tile shape, else 64 x 8 for FP32 and 32 x 8 for FP64; FP64 ones
+// from N = 65 on (default_two; in a pool the pass does not lose below that
+// for FP32, as other lattices fill the chip).
 // The pool supplies much of the parallelism that short z-chunks buy a
 // lattice run alone; 16 planes keep enough work items for ensembles of small
 // lattices (measured on MI355X: 128 lattices of N in {32, 48, 64} run 11%
@@ -610,12 +610,14 @@ int ah_pool_create(size_t hbm_budget, int32_t max_slots, void* hip_stream, ah_po
 static int pool_config(const ah_params& p, ah_step_config* cfg, TileConfig* two, std::string* why)
 {
     ah_step_config t{AH_KERNEL_TILE, 0, 0, 0};
-    int two_tx = 64, two_ty = 8;
+    int two_tx = p.precision == AH_FP64 ? 32 : 64, two_ty = 8;
+    bool take_two = p.precision == AH_FP32 || p.N > 64;
     if (tuned_config(p, &t)) {
         if (t.kernel == AH_KERNEL_TILE2) {
             two_tx = t.tile_x;
             two_ty = t.tile_y;
             t.zchunk = 0;
+            take_two = true;
         }
         t.kernel = AH_KERNEL_TILE;
         if (!batch_tile_supported(p.precision, t.tile_x, t.tile_y)) t = ah_step_config{AH_KERNEL_TILE, 0, 0, 0};
@@ -625,7 +627,7 @@ static int pool_config(const ah_params& p, ah_step_config* cfg, TileConfig* two,
     auto floor16 = [&](int zc) { return std::min(std::max(zc, 16), p.N); };
     cfg->zchunk = floor16(cfg->zchunk);
     *two = TileConfig{0, 0, 0};
-    if (p.precision == AH_FP32 && tile2_supported(p.precision, two_tx, two_ty))
+    if (take_two && tile2_supported(p.precision, two_tx, two_ty))
         *two = TileConfig{two_tx, two_ty, floor16(auto_zchunk(AH_KERNEL_TILE2, p.precision, p.N, two_tx, two_ty, false))};
     return AH_OK;
 }

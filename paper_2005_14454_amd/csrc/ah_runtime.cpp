@@ -46,6 +46,7 @@ struct ah_handle {
     std::vector<hipEvent_t> ev;  // start/stop pairs
     size_t ev_used = 0;
     ah_step_config cfg{AH_KERNEL_AUTO, 0, 0, 0};
+    TileConfig two{};  // tiling of the two-step passes an automatic configuration takes (zchunk 0: none)
     int64_t measured_launches = 0;  // timed launches that also formed diagnostics
     std::vector<char> ev_measured;  // per event pair: 1 if that launch formed diagnostics
     std::vector<char> ev_steps;     // per event pair: steps the launch advanced (1 or 2)
@@ -300,7 +301,7 @@ struct ShapeRate {
     double fp32, fp64;
 };
 constexpr ShapeRate kShapeRates[] = {
-    {128, 4, 65.9, 0.0}, {128, 8, 64.7, 0.0}, {64, 8, 61.2, 28.3}, {64, 4, 60.8, 27.1}, {32, 8, 59.0, 27.7},
+    {128, 4, 67.0, 0.0}, {128, 8, 65.8, 0.0}, {64, 8, 65.8, 30.2}, {64, 4, 61.3, 29.7}, {32, 8, 60.2, 29.8},
 };
 }  // namespace
 
@@ -327,7 +328,7 @@ int resident_per_cu(int kernel, int precision, int tx, int ty, bool measured)
 {
     if (kernel == AH_KERNEL_TILE2) {
         // waves per SIMD at the pass's registers: FP32 3, FP64 2; the FP64
-        // pass's LDS (over 100 KB) admits one workgroup per CU
+        // pass's LDS (over 150 KB) admits one workgroup per CU
         if (precision == AH_FP64) return 1;
         const int nt = tx * ty, ring = (tx + 2) * (ty + 2) - nt;
         const int waves = (nt + (ring + 63) / 64 * 64) / 64;
@@ -339,26 +340,53 @@ int resident_per_cu(int kernel, int precision, int tx, int ty, bool measured)
     return std::max(1, (precision == AH_FP64 || measured ? 8 : 16) / waves);
 }
 
+namespace {
+
+// Estimated time of a tiled launch with z-chunks of zc planes, in units of
+// the time a workgroup that has its CU to itself takes for a plane.
+//
+// Workgroups run in rounds of (CUs x resident workgroups), each as long as
+// a chunk's planes and its start, `ramp` planes more.  A round in which all
+// of a CU's places are taken lasts `full` times as long as one in which a
+// workgroup has its CU to itself.  Both fitted to a sweep on MI355X (27 sizes
+// of 24 .. 640, seven kernel and tile shapes in both precisions, up to 16
+// z-chunks each): the z-chunk chosen by it is within 0.6% of the fastest
+// on average (3% for the plain FP32 march on its smallest tiles), where
+// rounds x (planes + 2) with no `full` was up to 9% (two-step 32 x 8, which
+// then put two workgroups on some CUs of a 48^3 lattice and ran at 10.6
+// rather than 7.0 us per step).
+double launch_estimate(int kernel, int precision, int N, int tx, int ty, bool measured, int zc, int64_t* nblocks)
+{
+    constexpr int kCUs = 256;
+    const int res = resident_per_cu(kernel, precision, tx, ty, measured);
+    const bool two = kernel == AH_KERNEL_TILE2;
+    const double full = res == 1 ? 1.0 : two ? 2.0 : (precision == AH_FP64 || measured ? 1.6 : (res == 2 ? 1.4 : 1.8));
+    const int ramp = !two ? 1 : (tx * ty > 256 ? 4 : 3);
+    const int64_t nb = (int64_t)((N + tx - 1) / tx) * ((N + ty - 1) / ty) * ((N + zc - 1) / zc);
+    const int64_t slots = (int64_t)kCUs * res;
+    const int64_t left = (nb % slots + kCUs - 1) / kCUs;  // workgroups per CU of the last round
+    double rounds = (double)(nb / slots) * full;
+    if (left > 0) rounds += res == 1 ? 1.0 : 1.0 + (full - 1.0) * (double)(left - 1) / (res - 1);
+    if (nblocks) *nblocks = nb;
+    return rounds * (zc + ramp);
+}
+
+}  // namespace
+
 int auto_zchunk(int kernel, int precision, int N, int tx, int ty, bool measured)
 {
-    // Workgroups run in rounds of (CUs x resident workgroups); a launch
-    // takes about rounds x (planes per chunk + 2), the 2 for a chunk's
-    // prologue.  The z-chunks are equal (a short last chunk would leave most
-    // of its round idle); among equal estimates the one with more
-    // workgroups, which spread more evenly over the XCDs.  Chosen on MI355X
-    // over a sweep of N in 65 .. 512 and five tile shapes: within 2% of the
-    // best measured z-chunk on average.
-    constexpr int kCUs = 256;
-    const int64_t per_chunk = (int64_t)((N + tx - 1) / tx) * ((N + ty - 1) / ty);
-    const int64_t slots = (int64_t)kCUs * resident_per_cu(kernel, precision, tx, ty, measured);
+    // Equal chunks (a short last one would leave most of its round idle), of
+    // the least estimated time; among equal estimates the one with more
+    // workgroups, which spread more evenly over the XCDs.
     const int zmin = std::min(min_zchunk(N), N);
     int best_zc = N;
-    int64_t best_t = -1, best_nb = 0;
+    double best_t = -1.0;
+    int64_t best_nb = 0;
     for (int nz = 1; nz <= N / zmin; ++nz) {
         const int zc = (N + nz - 1) / nz;
         if (zc < zmin) break;
-        const int64_t nb = per_chunk * ((N + zc - 1) / zc);
-        const int64_t t = (nb + slots - 1) / slots * (zc + 2);
+        int64_t nb = 0;
+        const double t = launch_estimate(kernel, precision, N, tx, ty, measured, zc, &nb);
         if (best_t < 0 || t < best_t || (t == best_t && nb > best_nb)) {
             best_t = t;
             best_nb = nb;
@@ -366,6 +394,31 @@ int auto_zchunk(int kernel, int precision, int N, int tx, int ty, bool measured)
         }
     }
     return best_zc;
+}
+
+// Two-step passes of an automatic configuration: from N = 65 on, where they
+// are the faster way to take two plain steps in both precisions (MI355X, us
+// per step, two-step / single: FP32 75^3 13.5 / 13.6, 96^3 17.3 / 20.7, 200^3
+// 122 / 159, 512^3 1468 / 2002; FP64 75^3 25.8 / 27.2, 200^3 300 / 329, 512^3
+// 3783 / 4450; but 64^3 FP32 8.1 / 7.6, FP64 15.0 / 13.9: the pass's longer
+// start is not paid for by two planes a chunk).  FP64 on 32 x 8 (64 x 4
+// spills); FP32 on 64 x 8 or 32 x 8, whichever the estimate says is faster (a
+// plane takes a workgroup alone on its CU 2.85 and 1.9 us).
+bool default_two(int precision, int N, TileConfig* two)
+{
+    *two = TileConfig{0, 0, 0};
+    if (N <= 64) return false;
+    double best = 0.0;
+    for (const int tx : {64, 32}) {
+        if (!tile2_supported(precision, tx, 8)) continue;
+        const int zc = auto_zchunk(AH_KERNEL_TILE2, precision, N, tx, 8, false);
+        const double t = launch_estimate(AH_KERNEL_TILE2, precision, N, tx, 8, false, zc, nullptr) * (tx == 64 ? 2.85 : 1.9);
+        if (two->zchunk == 0 || t < best) {
+            best = t;
+            *two = TileConfig{tx, 8, zc};
+        }
+    }
+    return true;
 }
 
 // Any tile shape computes the same fields bit for bit, so the measured march
@@ -482,12 +535,18 @@ void to_measurement(const ah_params& p, int64_t step, const double* r, int64_t V
 
 namespace {
 
-int resolve_config(const ah_params& p, const ah_step_config& in, ah_step_config* out, std::string* why)
+// A handle's configuration; one that leaves everything automatic takes the
+// tuned one, or else two-step passes where they are faster (two).
+int resolve_config(const ah_params& p, const ah_step_config& in, ah_step_config* out, TileConfig* two,
+                   std::string* why)
 {
-    ah_step_config tuned;
+    *two = TileConfig{0, 0, 0};
     if (in.kernel == AH_KERNEL_AUTO && in.tile_x == 0 && in.tile_y == 0 && in.zchunk == 0 &&
-        p.gauge_action == AH_COMPACT && tuned_config(p, &tuned))
-        return resolve_step_config(p, tuned, out, why);
+        p.gauge_action == AH_COMPACT) {
+        ah_step_config tuned;
+        if (tuned_config(p, &tuned)) return resolve_step_config(p, tuned, out, why);
+        (void)default_two(p.precision, p.N, two);
+    }
     return resolve_step_config(p, in, out, why);
 }
 
@@ -617,10 +676,10 @@ hipError_t do_step(ah_handle* h)
     return hipSuccess;
 }
 
-// Two steps in one pass (kernel AH_KERNEL_TILE2): reads snapshot n from the
+// Two steps in one pass on tiling tc: reads snapshot n from the
 // current buffers and writes snapshot n+2 into the other phi/A and Pi/E ones.
 template <typename R>
-hipError_t do_step2(ah_handle* h)
+hipError_t do_step2(ah_handle* h, const TileConfig& tc)
 {
     Fields<R> in = fields_of<R>(h, h->cur);
     Fields<R> out = fields_of<R>(h, h->cur ^ 1);
@@ -631,7 +690,6 @@ hipError_t do_step2(ah_handle* h)
     out.e1 = (R*)h->mom[om][3];
     out.e2 = (R*)h->mom[om][4];
     const StepCoef c0 = coef_at(h->p, h->step), c1 = coef_at(h->p, h->step + 1);
-    const TileConfig tc{h->cfg.tile_x, h->cfg.tile_y, h->cfg.zchunk};
     TimedLaunch t{h, 2};
     hipError_t e = t.begin();
     if (e != hipSuccess) return e;
@@ -646,14 +704,27 @@ hipError_t do_step2(ah_handle* h)
 }
 
 // nsteps plain steps: two-step passes while at least two remain when the
-// handle's kernel is AH_KERNEL_TILE2, single steps otherwise.
+// handle's kernel is AH_KERNEL_TILE2 or its automatic configuration takes
+// them, single steps otherwise.
+//
+// Into a stream that is being captured an automatic configuration records
+// single steps: an even number of them leaves every buffer where it was, so
+// that the graph can be replayed, where a two-step pass swaps them all.
 hipError_t plain_steps(ah_handle* h, int64_t nsteps)
 {
-    const bool two = h->cfg.kernel == AH_KERNEL_TILE2;
+    TileConfig tc = h->two;
+    if (h->cfg.kernel == AH_KERNEL_TILE2) {
+        tc = TileConfig{h->cfg.tile_x, h->cfg.tile_y, h->cfg.zchunk};
+    } else if (tc.zchunk > 0 && nsteps >= 2) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        const hipError_t e = hipStreamIsCapturing(h->stream, &st);
+        if (e != hipSuccess) return e;
+        if (st != hipStreamCaptureStatusNone) tc.zchunk = 0;
+    }
     while (nsteps > 0) {
         hipError_t e;
-        if (two && nsteps >= 2) {
-            e = h->p.precision == AH_FP64 ? do_step2<double>(h) : do_step2<float>(h);
+        if (tc.zchunk > 0 && nsteps >= 2) {
+            e = h->p.precision == AH_FP64 ? do_step2<double>(h, tc) : do_step2<float>(h, tc);
             nsteps -= 2;
         } else {
             e = h->p.precision == AH_FP64 ? do_step<double>(h) : do_step<float>(h);
@@ -781,7 +852,7 @@ int ah_create(const ah_params* p, void* dev_arena, size_t arena_bytes, void* hip
         {
             std::string why2;
             const ah_step_config dflt{AH_KERNEL_AUTO, 0, 0, 0};
-            if (resolve_config(h->p, dflt, &h->cfg, &why2) != AH_OK) {
+            if (resolve_config(h->p, dflt, &h->cfg, &h->two, &why2) != AH_OK) {
                 (void)hipHostFree(h->host_series);
                 if (h->owns_arena) (void)hipFree(h->arena);
                 delete h;
@@ -799,9 +870,11 @@ int ah_set_step_config(ah_handle* h, const ah_step_config* c)
         if (!h || !c) return fail(h, AH_E_INVAL, "ah_set_step_config: bad argument");
         std::string why;
         ah_step_config r;
-        int rc = resolve_config(h->p, *c, &r, &why);
+        TileConfig two;
+        int rc = resolve_config(h->p, *c, &r, &two, &why);
         if (rc != AH_OK) return fail(h, rc, "ah_set_step_config: " + why);
         h->cfg = r;
+        h->two = two;
         return AH_OK;
     });
 }
