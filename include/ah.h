@@ -154,8 +154,9 @@ int ah_get_state(ah_handle* h, double* host_soa, int64_t* step);
 /* Values of the current snapshot at `count` listed site indices (each in
  * [0, N^3), else AH_E_INVAL before any device work): host_out[10*k + c] is
  * component c (state order) of site sites[k], widened to FP64.  For
- * spot-checking lattices too large to download.  Allocates two temporary
- * device buffers (count*8 and count*10*sizeof(real) bytes).  Synchronous. */
+ * spot-checking lattices too large to download.  Goes through the handle's
+ * pinned staging memory (2 MB, allocated by the first call that needs it, as
+ * for the state calls above).  Synchronous. */
 int ah_gather(ah_handle* h, const int64_t* sites, int64_t count, double* host_out);
 
 /* ah_gather without allocation, for callers that cannot allocate device

@@ -242,10 +242,30 @@ constexpr size_t kScratchBytes = (size_t)kGatherMax * sizeof(int64_t) + (size_t)
 // call for that device, with it current).
 hipError_t scratch_ptr(int device, void** out);
 
-// Copies between a dense host array of N^3 values (x fastest) and a stored
-// field of row pitch P, element size rb, enqueued on s (ah_runtime.cpp).
-hipError_t field_upload(void* dev, const void* host, int N, int P, size_t rb, hipStream_t s);
-hipError_t field_download(void* host, const void* dev, int N, int P, size_t rb, hipStream_t s);
+// Pinned host memory that a snapshot passes through on its way between the
+// fields and a caller's array: kIoSlots slots for each host thread that works
+// on it, and an event for every slot.  At most kIoBytes: allocating it takes
+// 0.25 ms per MB, which the first call pays.
+constexpr int kIoThreads = 4, kIoSlots = 3;
+constexpr size_t kIoBytes = 4u << 20;
+struct IoStage {
+    char* host = nullptr;
+    size_t bytes = 0;
+    hipEvent_t ev[kIoThreads * kIoSlots] = {};
+};
+hipError_t io_events(IoStage* st);   // creates those that are missing
+void io_close(IoStage* st);          // destroys them
+// A dense FP64 SoA state (state order, x fastest) into the fields at (pp, mom)
+// (as fields_at takes them), and back; both return when it is done
+// (ah_runtime.cpp).
+template <typename R>
+hipError_t state_upload(void* pp, void* mom, size_t fs, const double* host, int N, int P, const IoStage& st,
+                        hipStream_t s);
+template <typename R>
+hipError_t state_download(void* pp, void* mom, size_t fs, double* host, int N, int P, const IoStage& st,
+                          hipStream_t s);
+// Device bytes (16-byte aligned) to the host in the same way.
+hipError_t bytes_download(const void* dev, void* host, size_t bytes, const IoStage& st, hipStream_t s);
 
 // ---- launchers (ah_kernels.hip, ah_step_tile.hip) -------------------------
 template <typename R>
@@ -295,6 +315,16 @@ hipError_t launch_advance_batch(const PoolLattice* lat, int nlat, hipStream_t s)
 
 template <typename R>
 hipError_t launch_gather(const Fields<R>& f, const int64_t* sites, int64_t count, int N, int P, R* out, hipStream_t s);
+
+// Rows row0 .. row0 + nrows - 1 of a state's 10 N^2 (component, then x2, then
+// x1) between the fields at (pp, mom) and a dense buffer: out of the fields
+// (pack) or into them.  `rows` may be pinned host memory.
+template <typename R>
+hipError_t launch_state_rows(void* pp, void* mom, size_t fs, int N, int P, int64_t row0, int64_t nrows, R* rows, bool pack,
+                             hipStream_t s);
+
+// n bytes from src to dst (pinned host memory).
+hipError_t launch_bytes(const void* src, void* dst, int64_t n, hipStream_t s);
 
 template <typename R>
 hipError_t launch_winding(const Fields<R>& f, const LatticeConst& L, int8_t* w, hipStream_t s);

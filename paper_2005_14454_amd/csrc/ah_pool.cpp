@@ -142,6 +142,7 @@ struct ah_pool {
     bool owns_stream = false;
     hipStream_t side = nullptr;  // series downloads of finished lattices
     char* stage = nullptr;       // pinned staging ring for uploads
+    IoStage io;                  // its start, as ah_pool_get_state uses it when the ring is idle
     size_t stage_head = 0;
     std::deque<StageChunk> stage_busy;
     std::vector<hipEvent_t> free_events;
@@ -885,21 +886,17 @@ int ah_pool_get_state(ah_pool* P, int64_t id, double* host_soa, int64_t* step)
         if (e != hipSuccess) return phip(P, e, "ah_pool_get_state");
         const int64_t k = std::min(c[0], s->nsteps);
         const int cur = (int)c[2], curm = (int)c[3];  // the buffers of snapshot k
-        const size_t V = (size_t)s->p.N * s->p.N * s->p.N;
         const size_t rb = s->p.precision == AH_FP64 ? 8 : 4;
         const size_t fs = (size_t)s->d.fs * rb;
         char *q = (char*)s->d.pp[cur], *m = (char*)s->d.mom[curm];
-        void* comps[10] = {q,          q + fs,     m,          m + fs,     q + 2 * fs,
-                           q + 3 * fs, q + 4 * fs, m + 2 * fs, m + 3 * fs, m + 4 * fs};
-        std::vector<float> tmp(rb == 4 ? V : 0);
-        for (int cc = 0; cc < 10; ++cc) {
-            double* dst = host_soa + cc * V;
-            e = field_download(rb == 8 ? (void*)dst : (void*)tmp.data(), comps[cc], s->p.N, s->d.P, rb, P->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(P->stream);
-            if (e != hipSuccess) return phip(P, e, "ah_pool_get_state copy");
-            if (rb == 4)
-                for (size_t q = 0; q < V; ++q) dst[q] = (double)tmp[q];
-        }
+        // the stream is idle, and so is the staging ring
+        P->io.host = P->stage;
+        P->io.bytes = kIoBytes;
+        e = io_events(&P->io);
+        if (e == hipSuccess)
+            e = rb == 8 ? state_download<double>(q, m, fs, host_soa, s->p.N, s->d.P, P->io, P->stream)
+                        : state_download<float>(q, m, fs, host_soa, s->p.N, s->d.P, P->io, P->stream);
+        if (e != hipSuccess) return phip(P, e, "ah_pool_get_state copy");
         if (step) *step = k;
         return AH_OK;
     });
@@ -996,6 +993,7 @@ int ah_pool_destroy(ah_pool* P)
         if (sn.h) (void)hipHostFree(sn.h);
         if (sn.ev) (void)hipEventDestroy(sn.ev);
     }
+    io_close(&P->io);
     if (P->stage) (void)hipHostFree(P->stage);
     if (P->side) (void)hipStreamDestroy(P->side);
     if (P->exec) (void)hipGraphExecDestroy(P->exec);

@@ -12,6 +12,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 using namespace ah;
@@ -39,6 +40,8 @@ struct ah_handle {
     // the host, so no copy follows it
     double* host_series = nullptr;
     double* series = nullptr;
+    IoStage io;              // state I/O (io_stage)
+    char* io_mem = nullptr;  // its own memory, if it has any
     int cur = 0;
     int64_t step = 0;
     bool ready = false;
@@ -242,36 +245,210 @@ LatticeConst lconst(const ah_params& p)
 
 namespace ah {
 
-hipError_t field_upload(void* dev, const void* host, int N, int P, size_t rb, hipStream_t s)
+hipError_t io_events(IoStage* st)
 {
-    if (P == N) return hipMemcpyAsync(dev, host, (size_t)N * N * N * rb, hipMemcpyHostToDevice, s);
-    return hipMemcpy2DAsync(dev, (size_t)P * rb, host, (size_t)N * rb, (size_t)N * rb, (size_t)N * N,
-                            hipMemcpyHostToDevice, s);
+    for (hipEvent_t& ev : st->ev)
+        if (!ev) {
+            const hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventReleaseToSystem);
+            if (e != hipSuccess) return e;
+        }
+    return hipSuccess;
 }
-hipError_t field_download(void* host, const void* dev, int N, int P, size_t rb, hipStream_t s)
+void io_close(IoStage* st)
 {
-    if (P == N) return hipMemcpyAsync(host, dev, (size_t)N * N * N * rb, hipMemcpyDeviceToHost, s);
-    return hipMemcpy2DAsync(host, (size_t)N * rb, dev, (size_t)P * rb, (size_t)N * rb, (size_t)N * N,
-                            hipMemcpyDeviceToHost, s);
+    for (hipEvent_t& ev : st->ev) {
+        if (ev) (void)hipEventDestroy(ev);
+        ev = nullptr;
+    }
+}
+
+namespace {
+
+// One host thread's share of the staging memory.
+struct IoLane {
+    char *host, *dev;  // kIoSlots slots of `slot` bytes, as the host and as the device know them
+    size_t slot;
+    const hipEvent_t* ev;
+};
+
+// Items [i0, i1) in pieces of `per`, one piece per slot: while the host works
+// on one piece (fill, take) kernels move those of the other slots.
+template <class Fill, class Launch>
+hipError_t pieces_in(const IoLane& l, int64_t i0, int64_t i1, int64_t per, hipStream_t s, Fill fill, Launch launch)
+{
+    int64_t k = 0;
+    for (int64_t i = i0; i < i1; i += per, ++k) {
+        const int j = (int)(k % kIoSlots);
+        const int64_t n = std::min(per, i1 - i);
+        hipError_t e = k >= kIoSlots ? hipEventSynchronize(l.ev[j]) : hipSuccess;
+        if (e != hipSuccess) return e;
+        fill(l.host + j * l.slot, i, n);
+        e = launch(l.dev + j * l.slot, i, n);
+        if (e == hipSuccess) e = hipEventRecord(l.ev[j], s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+template <class Launch, class Take>
+hipError_t pieces_out(const IoLane& l, int64_t i0, int64_t i1, int64_t per, hipStream_t s, Launch launch, Take take)
+{
+    const int64_t pieces = (i1 - i0 + per - 1) / per;
+    for (int64_t k = 0; k < pieces + kIoSlots; ++k) {
+        const int j = (int)(k % kIoSlots);
+        hipError_t e = hipSuccess;
+        if (k >= kIoSlots) {
+            e = hipEventSynchronize(l.ev[j]);
+            if (e != hipSuccess) return e;
+            const int64_t i = i0 + (k - kIoSlots) * per;
+            take(l.host + j * l.slot, i, std::min(per, i1 - i));
+        }
+        if (k < pieces) {
+            const int64_t i = i0 + k * per;
+            e = launch(l.dev + j * l.slot, i, std::min(per, i1 - i));
+            if (e == hipSuccess) e = hipEventRecord(l.ev[j], s);
+            if (e != hipSuccess) return e;
+        }
+        if (k + 1 >= pieces && k + 1 < kIoSlots) k = kIoSlots - 1;  // fewer pieces than slots: on to the waits
+    }
+    return hipSuccess;
+}
+
+// work(lane, i0, i1) over items [0, n), split between up to `most` host threads
+// with a lane each, one for every 16 MB of the caller's array.  A thread
+// converts 20 to 30 GB/s, far less into memory it is the first to touch, where
+// the host link carries 50.  MI355X, one / two / four threads: 160^3 FP64 out
+// 24.0 / 13.6 / 11.3 ms (ten 1-D copies 31.6), 90^3 FP32 out 3.8 / 2.3 / 1.6.
+// The way in stops at two: 160^3 FP64 12.1 / 9.3 / 11.6 ms (four threads' pieces
+// are so small that the launches bound it; copies 12.0), 90^3 FP32 2.0 / 1.4 /
+// 1.3.
+template <class Work>
+hipError_t split_lanes(const IoStage& st, int64_t n, int most, size_t host_bytes, hipStream_t s, Work work)
+{
+    constexpr size_t least = 64u << 10;  // a slot; at least a row of the longest side where there is one lane
+    const size_t lanes = std::min(1 + (host_bytes >> 24), std::max(st.bytes / (kIoSlots * least), (size_t)1));
+    const int T = (int)std::min<int64_t>(most, std::min<int64_t>(n, (int64_t)lanes));
+    void* dev = nullptr;
+    int device = 0;
+    hipError_t e = hipHostGetDevicePointer(&dev, st.host, 0);
+    if (e == hipSuccess) e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
+    const size_t slot = st.bytes / (T * kIoSlots) / 256 * 256;
+    hipError_t err[kIoThreads] = {};
+    auto run = [&](int t) {
+        const IoLane l{st.host + t * kIoSlots * slot, (char*)dev + t * kIoSlots * slot, slot, st.ev + t * kIoSlots};
+        err[t] = work(l, n * t / T, n * (t + 1) / T);
+    };
+    std::thread helpers[kIoThreads];
+    for (int t = 1; t < T; ++t) {
+        try {
+            helpers[t] = std::thread([&, t] {
+                err[t] = hipSetDevice(device);
+                if (err[t] == hipSuccess) run(t);
+            });
+        } catch (...) {
+            run(t);  // no more threads to be had
+        }
+    }
+    run(0);
+    for (int t = 1; t < T; ++t)
+        if (helpers[t].joinable()) helpers[t].join();
+    for (int t = 0; t < T; ++t)
+        if (err[t] != hipSuccess) {
+            (void)hipStreamSynchronize(s);  // nothing uses the staging memory once the call has failed
+            return err[t];
+        }
+    return hipSuccess;
+}
+
+}  // namespace
+
+template <typename R>
+hipError_t state_upload(void* pp, void* mom, size_t fs, const double* host, int N, int P, const IoStage& st, hipStream_t s)
+{
+    const int64_t rows = 10 * (int64_t)N * N;
+    const hipError_t e = split_lanes(st, rows, 2, rows * N * sizeof(double), s, [=](const IoLane& l, int64_t r0, int64_t r1) {
+        const int64_t per = (int64_t)(l.slot / (N * sizeof(R)));
+        if (per < 1) return hipErrorInvalidValue;
+        return pieces_in(
+            l, r0, r1, per, s,
+            [=](char* slot, int64_t r, int64_t n) {
+                const double* src = host + r * N;
+                R* dst = (R*)slot;
+                for (int64_t i = 0; i < n * N; ++i) dst[i] = (R)src[i];
+            },
+            [=](char* slot, int64_t r, int64_t n) {
+                return launch_state_rows<R>(pp, mom, fs, N, P, r, n, (R*)slot, false, s);
+            });
+    });
+    const hipError_t done = hipStreamSynchronize(s);
+    return e != hipSuccess ? e : done;
+}
+template <typename R>
+hipError_t state_download(void* pp, void* mom, size_t fs, double* host, int N, int P, const IoStage& st, hipStream_t s)
+{
+    const int64_t rows = 10 * (int64_t)N * N;
+    return split_lanes(st, rows, kIoThreads, rows * N * sizeof(double), s, [=](const IoLane& l, int64_t r0, int64_t r1) {
+        const int64_t per = (int64_t)(l.slot / (N * sizeof(R)));
+        if (per < 1) return hipErrorInvalidValue;
+        return pieces_out(
+            l, r0, r1, per, s,
+            [=](char* slot, int64_t r, int64_t n) {
+                return launch_state_rows<R>(pp, mom, fs, N, P, r, n, (R*)slot, true, s);
+            },
+            [=](const char* slot, int64_t r, int64_t n) {
+                double* dst = host + r * N;
+                const R* src = (const R*)slot;
+                for (int64_t i = 0; i < n * N; ++i) dst[i] = (double)src[i];
+            });
+    });
+}
+template hipError_t state_upload<double>(void*, void*, size_t, const double*, int, int, const IoStage&, hipStream_t);
+template hipError_t state_upload<float>(void*, void*, size_t, const double*, int, int, const IoStage&, hipStream_t);
+template hipError_t state_download<double>(void*, void*, size_t, double*, int, int, const IoStage&, hipStream_t);
+template hipError_t state_download<float>(void*, void*, size_t, double*, int, int, const IoStage&, hipStream_t);
+
+hipError_t bytes_download(const void* dev, void* host, size_t bytes, const IoStage& st, hipStream_t s)
+{
+    constexpr int64_t block = 256;
+    return split_lanes(st, ((int64_t)bytes + block - 1) / block, kIoThreads, bytes, s, [=](const IoLane& l, int64_t b0, int64_t b1) {
+        auto len = [=](int64_t b, int64_t n) { return std::min(n * block, (int64_t)bytes - b * block); };
+        return pieces_out(
+            l, b0, b1, (int64_t)l.slot / block, s,
+            [=](char* slot, int64_t b, int64_t n) {
+                return launch_bytes((const char*)dev + b * block, slot, len(b, n), s);
+            },
+            [=](const char* slot, int64_t b, int64_t n) { std::memcpy((char*)host + b * block, slot, len(b, n)); });
+    });
 }
 
 }  // namespace ah
 
 namespace {
 
-// component c of the state (order phi_re, phi_im, pi_re, pi_im, A0..2, E0..2)
-void* comp_ptr(ah_handle* h, int c)
+// The handle's staging memory: its own (an eighth of the lattice's state,
+// 512 KB to kIoBytes), allocated at the first use that needs more than the
+// record memory holds and kept until the handle is destroyed; the record
+// memory (idle between calls) where that is enough, or if no more can be had.
+hipError_t io_stage(ah_handle* h, size_t want, IoStage** out)
 {
-    switch (c) {
-    case 0: return h->pp[h->cur][0];
-    case 1: return h->pp[h->cur][1];
-    case 2: return h->mom[h->curm][0];
-    case 3: return h->mom[h->curm][1];
-    case 4: return h->pp[h->cur][2];
-    case 5: return h->pp[h->cur][3];
-    case 6: return h->pp[h->cur][4];
-    default: return h->mom[h->curm][c - 5];
+    constexpr size_t records = (size_t)kSeriesCap * kMeasStride * sizeof(double);
+    *out = &h->io;
+    if (!h->io_mem && want > records) {
+        const size_t state = 10 * (size_t)h->V * h->real_bytes;
+        const size_t n = std::min(kIoBytes, std::max(align_up(state / 8), (size_t)512 << 10));
+        void* m = nullptr;
+        if (hipHostMalloc(&m, n, hipHostMallocDefault) == hipSuccess) {
+            h->io.host = h->io_mem = (char*)m;
+            h->io.bytes = n;
+        } else {
+            (void)hipGetLastError();
+        }
     }
+    if (!h->io.host) {
+        h->io.host = (char*)h->host_series;
+        h->io.bytes = records;
+    }
+    return io_events(&h->io);
 }
 
 struct DeviceGuard {
@@ -355,16 +532,16 @@ namespace {
 // rounds x (planes + 2) with no `full` was up to 9% (two-step 32 x 8, which
 // then put two workgroups on some CUs of a 48^3 lattice and ran at 10.6
 // rather than 7.0 us per step).
-double launch_estimate(int kernel, int precision, int N, int tx, int ty, bool measured, int zc, int64_t* nblocks)
+double launch_estimate(int kernel, int precision, int N, int tx, int ty, bool measured, int zc, int* nblocks)
 {
     constexpr int kCUs = 256;
     const int res = resident_per_cu(kernel, precision, tx, ty, measured);
     const bool two = kernel == AH_KERNEL_TILE2;
     const double full = res == 1 ? 1.0 : two ? 2.0 : (precision == AH_FP64 || measured ? 1.6 : (res == 2 ? 1.4 : 1.8));
     const int ramp = !two ? 1 : (tx * ty > 256 ? 4 : 3);
-    const int64_t nb = (int64_t)((N + tx - 1) / tx) * ((N + ty - 1) / ty) * ((N + zc - 1) / zc);
-    const int64_t slots = (int64_t)kCUs * res;
-    const int64_t left = (nb % slots + kCUs - 1) / kCUs;  // workgroups per CU of the last round
+    const int nb = ((N + tx - 1) / tx) * ((N + ty - 1) / ty) * ((N + zc - 1) / zc);  // < 2^28 for N <= 4096
+    const int slots = kCUs * res;
+    const int left = (nb % slots + kCUs - 1) / kCUs;  // workgroups per CU of the last round
     double rounds = (double)(nb / slots) * full;
     if (left > 0) rounds += res == 1 ? 1.0 : 1.0 + (full - 1.0) * (double)(left - 1) / (res - 1);
     if (nblocks) *nblocks = nb;
@@ -381,11 +558,13 @@ int auto_zchunk(int kernel, int precision, int N, int tx, int ty, bool measured)
     const int zmin = std::min(min_zchunk(N), N);
     int best_zc = N;
     double best_t = -1.0;
-    int64_t best_nb = 0;
-    for (int nz = 1; nz <= N / zmin; ++nz) {
+    int best_nb = 0;
+    for (int nz = 1, last = 0; nz <= N / zmin; ++nz) {
         const int zc = (N + nz - 1) / nz;
         if (zc < zmin) break;
-        int64_t nb = 0;
+        if (zc == last) continue;
+        last = zc;
+        int nb = 0;
         const double t = launch_estimate(kernel, precision, N, tx, ty, measured, zc, &nb);
         if (best_t < 0 || t < best_t || (t == best_t && nb > best_nb)) {
             best_t = t;
@@ -912,21 +1091,13 @@ int ah_set_state(ah_handle* h, const double* host_soa, int64_t step)
         if (e != hipSuccess) return hip_fail(h, e, "ah_set_state sync");
         h->cur = 0;
         h->curm = 0;
-        const size_t V = (size_t)h->V;
-        std::vector<float> tmp;
-        if (h->real_bytes == 4) tmp.resize(V);
-        for (int c = 0; c < 10; ++c) {
-            const double* src = host_soa + (size_t)c * V;
-            if (h->real_bytes == 8) {
-                e = field_upload(comp_ptr(h, c), src, h->p.N, h->P, 8, h->stream);
-            } else {
-                for (size_t i = 0; i < V; ++i) tmp[i] = (float)src[i];
-                e = field_upload(comp_ptr(h, c), tmp.data(), h->p.N, h->P, 4, h->stream);
-            }
-            if (e != hipSuccess) return hip_fail(h, e, "ah_set_state copy");
-            e = hipStreamSynchronize(h->stream);
-            if (e != hipSuccess) return hip_fail(h, e, "ah_set_state sync");
-        }
+        IoStage* st = nullptr;
+        e = io_stage(h, 10 * (size_t)h->V * h->real_bytes, &st);
+        const size_t fb = field_bytes(h->p);
+        if (e == hipSuccess)
+            e = h->real_bytes == 8 ? state_upload<double>(h->pp[0][0], h->mom[0][0], fb, host_soa, h->p.N, h->P, *st, h->stream)
+                                   : state_upload<float>(h->pp[0][0], h->mom[0][0], fb, host_soa, h->p.N, h->P, *st, h->stream);
+        if (e != hipSuccess) return hip_fail(h, e, "ah_set_state copy");
         h->step = step;
         h->ready = true;
         return AH_OK;
@@ -939,23 +1110,16 @@ int ah_get_state(ah_handle* h, double* host_soa, int64_t* step)
         if (!h || !host_soa) return fail(h, AH_E_INVAL, "ah_get_state: bad argument");
         if (!h->ready) return fail(h, AH_E_STATE, "ah_get_state before ah_init/ah_set_state");
         DeviceGuard g(h->device);
-        const size_t V = (size_t)h->V;
-        std::vector<float> tmp;
-        if (h->real_bytes == 4) tmp.resize(V);
-        for (int c = 0; c < 10; ++c) {
-            double* dst = host_soa + (size_t)c * V;
-            hipError_t e;
-            if (h->real_bytes == 8) {
-                e = field_download(dst, comp_ptr(h, c), h->p.N, h->P, 8, h->stream);
-            } else {
-                e = field_download(tmp.data(), comp_ptr(h, c), h->p.N, h->P, 4, h->stream);
-            }
-            if (e != hipSuccess) return hip_fail(h, e, "ah_get_state copy");
-            e = hipStreamSynchronize(h->stream);
-            if (e != hipSuccess) return hip_fail(h, e, "ah_get_state sync");
-            if (h->real_bytes == 4)
-                for (size_t i = 0; i < V; ++i) dst[i] = (double)tmp[i];
-        }
+        hipError_t e = hipStreamSynchronize(h->stream);
+        if (e != hipSuccess) return hip_fail(h, e, "ah_get_state sync");
+        IoStage* st = nullptr;
+        e = io_stage(h, 10 * (size_t)h->V * h->real_bytes, &st);
+        const size_t fb = field_bytes(h->p);
+        void *pp = h->pp[h->cur][0], *mom = h->mom[h->curm][0];
+        if (e == hipSuccess)
+            e = h->real_bytes == 8 ? state_download<double>(pp, mom, fb, host_soa, h->p.N, h->P, *st, h->stream)
+                                   : state_download<float>(pp, mom, fb, host_soa, h->p.N, h->P, *st, h->stream);
+        if (e != hipSuccess) return hip_fail(h, e, "ah_get_state copy");
         if (step) *step = h->step;
         return AH_OK;
     });
@@ -970,32 +1134,35 @@ int ah_gather(ah_handle* h, const int64_t* sites, int64_t count, double* host_ou
             if (sites[k] < 0 || sites[k] >= h->V) return fail(h, AH_E_INVAL, "ah_gather: site index out of range");
         if (count == 0) return AH_OK;
         DeviceGuard g(h->device);
-        void* d_sites = nullptr;
-        void* d_out = nullptr;
-        const size_t rb = h->real_bytes;
-        std::vector<float> tmp(rb == 4 ? count * 10 : 0);  // host staging first: a throw after hipMalloc would leak
-        hipError_t e = hipMalloc(&d_sites, count * sizeof(int64_t));
-        if (e == hipSuccess) e = hipMalloc(&d_out, count * 10 * rb);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            if (d_sites) (void)hipFree(d_sites);
-            return fail(h, AH_E_NOMEM, "ah_gather: cannot allocate the temporary buffers");
-        }
-        e = hipMemcpyAsync(d_sites, sites, count * sizeof(int64_t), hipMemcpyHostToDevice, h->stream);
-        if (e == hipSuccess)
-            e = rb == 8 ? launch_gather<double>(fields_of<double>(h, h->cur), (const int64_t*)d_sites, count, h->p.N, h->P,
-                                                (double*)d_out, h->stream)
-                        : launch_gather<float>(fields_of<float>(h, h->cur), (const int64_t*)d_sites, count, h->p.N, h->P,
-                                               (float*)d_out, h->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(rb == 8 ? (void*)host_out : (void*)tmp.data(), d_out, count * 10 * rb,
-                               hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-        (void)hipFree(d_sites);
-        (void)hipFree(d_out);
+        // through the staging memory, which the kernel reads the indices from
+        // and writes the values to
+        const size_t rb = h->real_bytes, each = sizeof(int64_t) + 10 * rb;
+        IoStage* st = nullptr;
+        hipError_t e = io_stage(h, (size_t)count * each, &st);
+        void* dev = nullptr;
+        if (e == hipSuccess) e = hipHostGetDevicePointer(&dev, st->host, 0);
         if (e != hipSuccess) return hip_fail(h, e, "ah_gather");
-        if (rb == 4)
-            for (int64_t q = 0; q < count * 10; ++q) host_out[q] = (double)tmp[q];
+        const int64_t per = (int64_t)(st->bytes / each) / 32 * 32;  // values start on a cache line
+        for (int64_t k = 0; k < count; k += per) {
+            const int64_t n = std::min(per, count - k);
+            std::memcpy(st->host, sites + k, n * sizeof(int64_t));
+            const size_t off = per * sizeof(int64_t);
+            const int64_t* d_sites = (const int64_t*)dev;
+            void* d_out = (char*)dev + off;
+            e = rb == 8 ? launch_gather<double>(fields_of<double>(h, h->cur), d_sites, n, h->p.N, h->P, (double*)d_out,
+                                                h->stream)
+                        : launch_gather<float>(fields_of<float>(h, h->cur), d_sites, n, h->p.N, h->P, (float*)d_out,
+                                               h->stream);
+            if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+            if (e != hipSuccess) return hip_fail(h, e, "ah_gather");
+            double* dst = host_out + 10 * k;
+            const char* src = st->host + off;
+            if (rb == 8) {
+                std::memcpy(dst, src, 10 * n * 8);
+            } else {
+                for (int64_t q = 0; q < 10 * n; ++q) dst[q] = (double)((const float*)src)[q];
+            }
+        }
         return AH_OK;
     });
 }
@@ -1163,20 +1330,17 @@ int ah_get_winding(ah_handle* h, int8_t* host_w)
         if (!h || !host_w) return fail(h, AH_E_INVAL, "ah_get_winding: bad argument");
         if (!h->ready) return fail(h, AH_E_STATE, "ah_get_winding before ah_init/ah_set_state");
         DeviceGuard g(h->device);
-        int8_t* d = nullptr;
+        // the Pi and E buffers that no snapshot is in hold them (3 bytes a
+        // site of their 20 or 40): the next step writes those anew
+        int8_t* d = (int8_t*)h->mom[h->curm ^ 1][0];
         const size_t bytes = 3 * (size_t)h->V;
-        hipError_t e = hipMalloc(&d, bytes);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(h, AH_E_NOMEM, "ah_get_winding: cannot allocate the temporary winding buffer");
-        }
-        e = h->p.precision == AH_FP64 ? launch_winding<double>(fields_of<double>(h, h->cur), lconst(h->p), d, h->stream)
-                                      : launch_winding<float>(fields_of<float>(h, h->cur), lconst(h->p), d, h->stream);
-        if (e == hipSuccess) e = hipMemcpyAsync(host_w, d, bytes, hipMemcpyDeviceToHost, h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-        hipError_t e2 = hipFree(d);
+        hipError_t e = h->p.precision == AH_FP64
+                           ? launch_winding<double>(fields_of<double>(h, h->cur), lconst(h->p), d, h->stream)
+                           : launch_winding<float>(fields_of<float>(h, h->cur), lconst(h->p), d, h->stream);
+        IoStage* st = nullptr;
+        if (e == hipSuccess) e = io_stage(h, bytes, &st);
+        if (e == hipSuccess) e = bytes_download(d, host_w, bytes, *st, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "ah_get_winding");
-        if (e2 != hipSuccess) return hip_fail(h, e2, "ah_get_winding free");
         return AH_OK;
     });
 }
@@ -1233,6 +1397,8 @@ int ah_destroy(ah_handle* h)
     DeviceGuard g(h->device);
     (void)hipStreamSynchronize(h->stream);
     for (hipEvent_t ev : h->ev) (void)hipEventDestroy(ev);
+    io_close(&h->io);
+    if (h->io_mem) (void)hipHostFree(h->io_mem);
     if (h->host_series) (void)hipHostFree(h->host_series);
     if (h->owns_arena && h->arena) (void)hipFree(h->arena);
     delete h;
