@@ -602,11 +602,10 @@ bool default_two(int precision, int N, TileConfig* two)
 
 // Any tile shape computes the same fields bit for bit, so the measured march
 // may run another shape than the plain step: the fastest measured march
-// (measured_tile: 32 x 8), with the step's z-chunk when
-// the step runs that shape too, else the automatic z-chunk of the measured
-// march but no shorter than the step's (a pool's floor of 16 planes then
-// holds for its measured node too).  A lattice of the site kernel takes the
-// automatic one.  The diagnostics records are summed in tile order, so a
+// (measured_tile: 32 x 8), with its own automatic z-chunk, but no shorter than
+// the step's up to 16 planes (a pool's floor of 16 then holds for its
+// measured node too).  A step's longer z-chunk is not taken over: two-step
+// 32 x 8 FP64 passes of 128^3 run best on 32 planes, its measured march on 16.  The diagnostics records are summed in tile order, so a
 // lattice measured with the same tiling (alone or in a pool) gets the same
 // bits.
 TileConfig measured_tiling(const ah_params& p, const ah_step_config& cfg)
@@ -615,7 +614,7 @@ TileConfig measured_tiling(const ah_params& p, const ah_step_config& cfg)
     const bool tiled = cfg.kernel == AH_KERNEL_TILE || cfg.kernel == AH_KERNEL_TILE2;
     if (!measured_tile(&tx, &ty) && tiled) return TileConfig{tx, ty, cfg.zchunk};
     int zc = auto_zchunk(AH_KERNEL_TILE, p.precision, p.N, tx, ty, true);
-    if (tiled && cfg.zchunk > zc) zc = std::min(cfg.zchunk, p.N);
+    if (tiled) zc = std::min(std::max(zc, std::min(cfg.zchunk, 16)), p.N);
     return TileConfig{tx, ty, zc};
 }
 
