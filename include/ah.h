@@ -289,7 +289,7 @@ int ah_tune_load(const char* path);
 /* A pool keeps many independent lattices (any N, precision, expansion
  * history; compact action) resident in one device arena and advances all
  * active ones together: each ah_pool_advance step is one replay of a HIP
- * graph holding the measured step of the lattices whose snapshot is due (it
+ * graph holding, as far as there is work for them, the measured step of the lattices whose snapshot is due (it
  * forms every diagnostic, the Gauss residual included) and its fixed-order
  * fold, the plain step of every other active lattice (one kernel node per precision and
  * tile shape, one block per (lattice, tile) work item) and a counter update;
@@ -303,7 +303,7 @@ int ah_tune_load(const char* path);
  * FP64 table, so its fields and diagnostics are bitwise identical to the
  * same lattice run alone through ah_step / ah_measure with the same tiling.
  * Requests enter and leave between advances (continuous batching); the
- * graph is captured again only when a node's work list outgrows its
+ * graphs are captured again only when a node's work list outgrows its
  * capacity (or shrinks far below it) or a new node is needed.  A pool is
  * used from one host thread at a time. */
 typedef struct ah_pool ah_pool;
@@ -315,7 +315,7 @@ typedef struct ah_pool_info {
     int32_t active;         /* lattices admitted and not yet collected */
     int32_t max_slots;
     int64_t graph_launches; /* steps issued so far */
-    int64_t graph_captures; /* times the per-step graph was captured */
+    int64_t graph_captures; /* times the nodes of the per-step graphs were laid out */
 } ah_pool_info;
 
 /* Create a pool with a device arena of hbm_budget bytes (hipMalloc'd and

@@ -10,14 +10,17 @@
 //     -> single step and two-step pass (one node per precision and tile
 //     shape) -> advance counters
 // and every kernel reads the lattice's own counter, so the same graph serves
-// every step until the set of lattices changes.
+// every step until the set of lattices changes.  What a replay does to each
+// lattice follows from its step count alone, so the host keeps its own count
+// and replays a graph of only those nodes that have work: a node without any
+// takes 4.5 us all the same, and a mixed pool has nine (a stream of 64^3 ..
+// 192^3 requests spent 3.2 of 26.7 ms on them).
 //
 // The host never drains the stream in the serving path: uploads (coefficient
 // tables, descriptors, work lists) go through a pinned staging ring and are
 // ordered on the pool stream after the replays already queued; each advance
-// queues a copy of the step counters into pinned memory behind an event, and
-// ah_pool_poll_async reads the newest copy that has landed; series downloads
-// run on a side stream.  At most kMaxInflight replays are queued ahead of the
+// records an event, and ah_pool_poll_async takes the host's counts as of the
+// newest event that has passed; series downloads run on a side stream.  At most kMaxInflight replays are queued ahead of the
 // host, so a request admitted now joins within that many steps.
 #include "ah.h"
 #include "ah_internal.h"
@@ -53,13 +56,14 @@ constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 constexpr int64_t kMaxInflight = 8;  // graph replays queued ahead of the host
-constexpr int kSnapshots = 16;       // counter copies in flight (> kMaxInflight)
+constexpr int kSnapshots = 16;       // events in flight (> kMaxInflight)
+constexpr size_t kMaxGraphs = 64;
 constexpr size_t kStageBytes = 32u << 20;
 
 struct Slot {
     bool used = false;
     int64_t id = -1;
-    int64_t seq = 0;  // admission order: counter copies issued before it do not describe it
+    int64_t seq = 0;  // admission order: snapshots taken before it do not describe it
     ah_params p{};
     int64_t nsteps = 0;
     int measure_every = 0;
@@ -109,11 +113,20 @@ struct StageChunk {
     size_t off, len;
     hipEvent_t ev;
 };
+// Where a lattice is after some replay: the step of its next replay and the
+// records it has, as the words 0 and 1 of its device counter hold them then.
+struct Progress {
+    int64_t step = 0, records = 0;
+};
 struct Snapshot {
-    int64_t* h = nullptr;    // pinned copy of the counters
+    std::vector<Progress> at;  // of every slot, once ev has passed
     hipEvent_t ev = nullptr;
-    int64_t launches = 0;    // replays queued before the copy
-    int64_t seq = 0;         // admissions made before the copy
+    int64_t launches = 0;    // replays queued before the event
+    int64_t seq = 0;         // admissions made before the event
+};
+struct StepGraph {
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
 };
 struct Retired {
     hipGraphExec_t exec;
@@ -132,6 +145,11 @@ struct GroupKey {
         return std::tie(kind, precision, tx, ty) < std::tie(o.kind, o.precision, o.tx, o.ty);
     }
 };
+// A lattice in the work lists, and the nodes of its three kinds of step.
+struct ActiveLattice {
+    int slot;
+    uint64_t single, measured, two;  // bits of a graph's key
+};
 struct NodeGroup {
     size_t off, cap;  // region of the work list (items); a step group's cap is a multiple of kXcdCount
 };
@@ -148,7 +166,7 @@ struct ah_pool {
     std::vector<hipEvent_t> free_events;
     std::vector<Snapshot> snaps;
     std::deque<int> snap_order;           // issued, not yet read, oldest first
-    std::vector<int64_t> host_counters;   // newest counters read back
+    std::vector<Progress> queued, done;   // of every slot: after the replays queued; as of the newest event passed
     int64_t launches_done = 0;            // replays known to have finished
     int64_t seq = 0;                      // admissions so far
     std::vector<Retired> retired;
@@ -161,10 +179,11 @@ struct ah_pool {
     int64_t* d_counters = nullptr;
     WorkItem* d_work = nullptr;
     size_t work_cap = 0;
-    std::map<GroupKey, NodeGroup> groups;  // work-list regions of the captured graph's nodes
+    std::map<GroupKey, NodeGroup> groups;  // work-list regions of the graph's nodes
+    bool laid_out = false;                 // the regions and the lists in them are uploaded
+    std::map<uint64_t, StepGraph> graphs;  // by the nodes in them: bit n the n-th of groups
+    std::vector<ActiveLattice> active;     // as of the last rebuild
     int64_t graph_captures = 0;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
     bool dirty = true;
     int64_t graph_launches = 0;
     std::string err;
@@ -292,7 +311,7 @@ hipError_t stage_upload(ah_pool* P, void* dst, const void* src, size_t n)
     return hipSuccess;
 }
 
-// Read the counter copies that have landed (wait = block for the oldest
+// Take the snapshots whose events have passed (wait = block for the oldest
 // one); the newest becomes the host's view of every lattice admitted before it.
 hipError_t read_snapshots(ah_pool* P, bool wait)
 {
@@ -302,10 +321,7 @@ hipError_t read_snapshots(ah_pool* P, bool wait)
         if (e == hipErrorNotReady) break;
         if (e != hipSuccess) return e;
         for (size_t i = 0; i < P->slots.size(); ++i)
-            if (P->slots[i].used && P->slots[i].seq <= sn.seq) {
-                for (int w = 0; w < kCounterWords; ++w)
-                    P->host_counters[kCounterWords * i + w] = sn.h[kCounterWords * i + w];
-            }
+            if (P->slots[i].used && P->slots[i].seq <= sn.seq) P->done[i] = sn.at[i];
         P->launches_done = std::max(P->launches_done, sn.launches);
         P->snap_order.pop_front();
         wait = false;
@@ -327,7 +343,8 @@ hipError_t read_snapshots(ah_pool* P, bool wait)
     return hipSuccess;
 }
 
-// Queue a copy of the counters behind the replays queued so far.
+// Record an event behind the replays queued so far, with what the lattices
+// will have done when it passes.
 hipError_t queue_snapshot(ah_pool* P)
 {
     if ((int)P->snap_order.size() >= kSnapshots) {
@@ -341,9 +358,8 @@ hipError_t queue_snapshot(ah_pool* P)
         if (!busy) break;
     }
     Snapshot& sn = P->snaps[j];
-    hipError_t e = hipMemcpyAsync(sn.h, P->d_counters, kCounterWords * P->slots.size() * sizeof(int64_t), hipMemcpyDeviceToHost,
-                                  P->stream);
-    if (e == hipSuccess) e = hipEventRecord(sn.ev, P->stream);
+    sn.at = P->queued;
+    const hipError_t e = hipEventRecord(sn.ev, P->stream);
     if (e != hipSuccess) return e;
     sn.launches = P->graph_launches;
     sn.seq = P->seq;
@@ -362,17 +378,29 @@ hipError_t retire(ah_pool* P, hipGraphExec_t exec, hipGraph_t graph, void* buf)
     return hipSuccess;
 }
 
+// The graphs of the present layout give way to another's.
+hipError_t retire_graphs(ah_pool* P)
+{
+    while (!P->graphs.empty()) {
+        auto it = P->graphs.begin();
+        const hipError_t e = retire(P, it->second.exec, it->second.graph, nullptr);
+        if (e != hipSuccess) return e;
+        P->graphs.erase(it);
+    }
+    return hipSuccess;
+}
+
 // Rebuild descriptors and work lists, and the per-step graph when its
 // node layout no longer fits.  Nothing here waits for the stream: the
 // uploads are ordered after the replays already queued, which keep reading
 // the old descriptors and lists until then.
 //
-// The graph has one step node (plain, measured, two-step) per (precision,
-// tile shape), each over a fixed-capacity region
-// of the work list whose unused items are empty.  An admission or a release
-// that fits the captured capacities only rewrites the lists; a new group or
-// a list beyond its capacity (or far below it) captures anew, with room for
-// growth.
+// There is one step node (plain, measured, two-step) per (precision, tile
+// shape), each over a fixed-capacity region of the work list whose unused
+// items are empty; a replay's graph holds those that have work (step_graph).
+// An admission or a release that fits the capacities only rewrites the lists;
+// a new group or a list beyond its capacity (or far below it) lays the nodes
+// out anew, with room for growth.
 int rebuild(ah_pool* P)
 {
     hipError_t e;
@@ -439,7 +467,7 @@ int rebuild(ah_pool* P)
         need[kv.first] = len * kXcdCount;
     }
     size_t need_total = 0, cap_total = 0;
-    bool fits = P->exec != nullptr;
+    bool fits = P->laid_out;
     for (auto& kv : need) {
         need_total += kv.second;
         auto it = P->groups.find(kv.first);
@@ -448,6 +476,9 @@ int rebuild(ah_pool* P)
     for (auto& kv : P->groups) cap_total += kv.second.cap;
     if (cap_total > 4 * std::max<size_t>(need_total, 4096)) fits = false;  // mostly empty: shrink
     if (!fits) {
+        e = retire_graphs(P);
+        if (e != hipSuccess) return phip(P, e, "pool graph retire");
+        P->laid_out = false;
         // capacities with room for growth (groups that emptied keep a small
         // one), laid out one after another
         std::map<GroupKey, NodeGroup> groups;
@@ -489,50 +520,103 @@ int rebuild(ah_pool* P)
     e = stage_upload(P, P->d_lat, desc.data(), nslot * sizeof(PoolLattice));
     if (e == hipSuccess && total) e = stage_upload(P, P->d_work, work.data(), total * sizeof(WorkItem));
     if (e != hipSuccess) return phip(P, e, "pool descriptor upload");
+    // the nodes each lattice's steps run in (a pool has a dozen at most: the
+    // tile shapes of three kinds of step in two precisions)
+    std::map<GroupKey, uint64_t> bit;
+    for (auto& kv : P->groups) {
+        if (bit.size() >= 64) return pfail(P, AH_E_INVAL, "pool graph: too many nodes");
+        bit.emplace(kv.first, (uint64_t)1 << bit.size());
+    }
+    P->active.clear();
+    for (int i = 0; i < nslot; ++i) {
+        const Slot& s = P->slots[i];
+        if (!s.used) continue;
+        P->active.push_back({i, bit[GroupKey{1, s.p.precision, s.cfg.tile_x, s.cfg.tile_y}],
+                             bit[GroupKey{2, s.p.precision, s.meas.tx, s.meas.ty}],
+                             s.two.zchunk > 0 ? bit[GroupKey{3, s.p.precision, s.two.tx, s.two.ty}] : 0});
+    }
+    if (!fits) ++P->graph_captures;
+    P->laid_out = true;
     P->dirty = false;
-    if (fits) return AH_OK;
+    return AH_OK;
+}
 
-    if (P->exec || P->graph) {
-        e = retire(P, P->exec, P->graph, nullptr);
+// What the next replay does to the lattices: the nodes that have work, and
+// with `take` the host's count moves on as the device's will
+// (k_advance_batch, k_fold_batch).
+uint64_t next_replay(ah_pool* P, bool take)
+{
+    uint64_t nodes = 0;
+    for (const ActiveLattice& a : P->active) {
+        const PoolLattice& d = P->slots[a.slot].d;
+        Progress& q = P->queued[a.slot];
+        const int64_t k = q.step;
+        if (k > d.nsteps) continue;
+        const bool due = measure_due(d, k), two = two_step_due(d, k);
+        nodes |= due ? a.measured : (two ? a.two : a.single);
+        if (take) {
+            q.step += two ? 2 : 1;
+            if (due) q.records += 1;
+        }
+    }
+    return nodes;
+}
+
+// The graph of the nodes given: captured when it is first needed.  A pool
+// whose requests keep coming needs a few (measured, single and two-step nodes
+// of each precision, mostly together); past kMaxGraphs they start anew.
+int step_graph(ah_pool* P, uint64_t nodes, hipGraphExec_t* exec)
+{
+    auto it = P->graphs.find(nodes);
+    if (it != P->graphs.end()) {
+        *exec = it->second.exec;
+        return AH_OK;
+    }
+    hipError_t e;
+    if (P->graphs.size() >= kMaxGraphs) {
+        e = retire_graphs(P);
         if (e != hipSuccess) return phip(P, e, "pool graph retire");
     }
-    P->exec = nullptr;
-    P->graph = nullptr;
-    P->dirty = true;  // until a graph is instantiated
+    const int nslot = (int)P->slots.size();
+    std::vector<std::pair<GroupKey, NodeGroup>> parts;
+    uint64_t bit = 1;
+    for (auto& kv : P->groups) {
+        if (nodes & bit) parts.push_back(kv);
+        bit <<= 1;
+    }
+    StepGraph g;
     e = hipStreamBeginCapture(P->stream, hipStreamCaptureModeRelaxed);
     if (e != hipSuccess) return phip(P, e, "pool graph capture begin");
     hipError_t le = hipSuccess;
     // measured steps of the due lattices, their fold, the plain steps of all
-    // others, the counter update
-    for (int measured = 1; measured >= 0; --measured) {
-        for (auto& kv : P->groups) {
-            if (kv.first.kind != (measured ? 2 : 1) || le != hipSuccess) continue;
-            const GroupKey& k = kv.first;
-            const NodeGroup& g = kv.second;
-            const int grid = (int)g.cap;  // one block per work item
-            le = k.precision == AH_FP64 ? launch_step_batch<double>(P->d_lat, P->d_work + g.off, (int)g.cap, k.tx,
-                                                                    k.ty, grid, measured != 0, P->stream)
-                                        : launch_step_batch<float>(P->d_lat, P->d_work + g.off, (int)g.cap, k.tx, k.ty,
-                                                                   grid, measured != 0, P->stream);
+    // others, the counter update; one block per work item
+    for (int kind : {2, 1, 3}) {
+        bool any = false;
+        for (auto& part : parts) {
+            const GroupKey& k = part.first;
+            if (k.kind != kind || le != hipSuccess) continue;
+            any = true;
+            const WorkItem* work = P->d_work + part.second.off;
+            const int cap = (int)part.second.cap;
+            const bool fp64 = k.precision == AH_FP64;
+            if (kind == 3)
+                le = fp64 ? launch_step2_batch<double>(P->d_lat, work, cap, k.tx, k.ty, cap, P->stream)
+                          : launch_step2_batch<float>(P->d_lat, work, cap, k.tx, k.ty, cap, P->stream);
+            else
+                le = fp64 ? launch_step_batch<double>(P->d_lat, work, cap, k.tx, k.ty, cap, kind == 2, P->stream)
+                          : launch_step_batch<float>(P->d_lat, work, cap, k.tx, k.ty, cap, kind == 2, P->stream);
         }
-        if (measured && le == hipSuccess) le = launch_fold_batch(P->d_lat, nslot, P->stream);
-    }
-    for (auto& kv : P->groups) {
-        if (kv.first.kind != 3 || le != hipSuccess) continue;
-        const GroupKey& k = kv.first;
-        const NodeGroup& g = kv.second;
-        le = k.precision == AH_FP64
-                 ? launch_step2_batch<double>(P->d_lat, P->d_work + g.off, (int)g.cap, k.tx, k.ty, (int)g.cap, P->stream)
-                 : launch_step2_batch<float>(P->d_lat, P->d_work + g.off, (int)g.cap, k.tx, k.ty, (int)g.cap, P->stream);
+        if (kind == 2 && any && le == hipSuccess) le = launch_fold_batch(P->d_lat, nslot, P->stream);
     }
     if (le == hipSuccess) le = launch_advance_batch(P->d_lat, nslot, P->stream);
-    e = hipStreamEndCapture(P->stream, &P->graph);
-    if (le != hipSuccess) return phip(P, le, "pool graph capture launch");
-    if (e != hipSuccess) return phip(P, e, "pool graph capture end");
-    e = hipGraphInstantiate(&P->exec, P->graph, nullptr, nullptr, 0);
-    if (e != hipSuccess) return phip(P, e, "pool graph instantiate");
-    ++P->graph_captures;
-    P->dirty = false;
+    e = hipStreamEndCapture(P->stream, &g.graph);
+    if (le == hipSuccess && e == hipSuccess) e = hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0);
+    if (le != hipSuccess || e != hipSuccess) {
+        if (g.graph) (void)hipGraphDestroy(g.graph);
+        return phip(P, le != hipSuccess ? le : e, "pool graph capture");
+    }
+    P->graphs.emplace(nodes, g);
+    *exec = g.exec;
     return AH_OK;
 }
 
@@ -579,15 +663,15 @@ int ah_pool_create(size_t hbm_budget, int32_t max_slots, void* hip_stream, ah_po
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&P->side, hipStreamNonBlocking);
         P->snaps.resize(kSnapshots);
         for (int j = 0; j < kSnapshots && e == hipSuccess; ++j) {
-            e = hipHostMalloc((void**)&P->snaps[j].h, kCounterWords * max_slots * sizeof(int64_t), hipHostMallocDefault);
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&P->snaps[j].ev, hipEventDisableTiming);
+            e = hipEventCreateWithFlags(&P->snaps[j].ev, hipEventDisableTiming);
         }
         if (e != hipSuccess) {
             (void)hipGetLastError();
             (void)ah_pool_destroy(P);
             return AH_E_NOMEM;
         }
-        P->host_counters.assign(kCounterWords * (size_t)max_slots, 0);
+        P->queued.assign(max_slots, Progress{});
+        P->done.assign(max_slots, Progress{});
         *out = P;
         return AH_OK;
     });
@@ -685,7 +769,7 @@ int ah_pool_submit(ah_pool* P, const ah_params* p, uint64_t seed, int64_t nsteps
         s.used = true;
         s.id = P->next_id++;
         s.seq = ++P->seq;
-        for (int w = 0; w < kCounterWords; ++w) P->host_counters[kCounterWords * slot + w] = 0;
+        P->queued[slot] = P->done[slot] = Progress{};
         s.p = *p;
         s.nsteps = nsteps;
         s.measure_every = measure_every;
@@ -766,25 +850,33 @@ int ah_pool_advance(ah_pool* P, int32_t nsteps)
         hipError_t e = hipSuccess;
         for (int32_t k = 0; k < nsteps; ++k) {
             // keep at most kMaxInflight replays queued ahead of the host: wait
-            // for the counter copy queued after an earlier replay (one is
-            // queued every kMaxInflight / 2 replays, so the wait leaves at
-            // least that many queued)
+            // for the event recorded after an earlier replay (one is recorded
+            // every kMaxInflight / 2 replays, so the wait leaves at least that
+            // many queued)
             while (e == hipSuccess && P->graph_launches - P->launches_done >= kMaxInflight) {
                 if (P->snap_order.empty()) e = queue_snapshot(P);
                 if (e == hipSuccess) e = read_snapshots(P, true);
             }
-            if (e == hipSuccess) e = hipGraphLaunch(P->exec, P->stream);
-            if (e != hipSuccess) return phip(P, e, "ah_pool_advance graph launch");
+            if (e != hipSuccess) return phip(P, e, "ah_pool_advance wait");
+            const uint64_t nodes = next_replay(P, false);
+            if (nodes) {  // else every lattice has finished
+                hipGraphExec_t exec = nullptr;
+                const int rc = step_graph(P, nodes, &exec);
+                if (rc != AH_OK) return rc;
+                e = hipGraphLaunch(exec, P->stream);
+                if (e != hipSuccess) return phip(P, e, "ah_pool_advance graph launch");
+                (void)next_replay(P, true);
+            }
             ++P->graph_launches;
             if (k + 1 < nsteps && P->graph_launches % (kMaxInflight / 2) == 0) {
                 e = queue_snapshot(P);
-                if (e != hipSuccess) return phip(P, e, "ah_pool_advance counter copy");
+                if (e != hipSuccess) return phip(P, e, "ah_pool_advance event");
             }
         }
         if (nsteps > 0) {
             e = queue_snapshot(P);
             if (e == hipSuccess) e = stage_reclaim(P, false);
-            if (e != hipSuccess) return phip(P, e, "ah_pool_advance counter copy");
+            if (e != hipSuccess) return phip(P, e, "ah_pool_advance event");
         }
         return AH_OK;
     });
@@ -797,7 +889,7 @@ static int report_done(ah_pool* P, int64_t* done_ids, int32_t cap, int32_t* n)
     for (size_t i = 0; i < P->slots.size(); ++i) {
         Slot& s = P->slots[i];
         if (!s.used || s.reported) continue;
-        if (P->host_counters[kCounterWords * i] == s.nsteps + 1) {
+        if (P->done[i].step == s.nsteps + 1) {
             if (k < cap) {
                 done_ids[k] = s.id;
                 s.reported = true;
@@ -911,8 +1003,7 @@ int ah_pool_results(ah_pool* P, int64_t id, ah_measurement* series, int32_t cap,
         if (!s) return pfail(P, AH_E_INVAL, "ah_pool_results: unknown id");
         Guard g(P->device);
         hipError_t e;
-        int64_t c[kCounterWords];
-        for (int w = 0; w < kCounterWords; ++w) c[w] = P->host_counters[kCounterWords * i + w];
+        int64_t c[kCounterWords] = {P->done[i].step, P->done[i].records};
         if (c[0] != s->nsteps + 1) {
             // not seen finished yet: read the counters after the queued work
             e = hipMemcpyAsync(c, P->d_counters + kCounterWords * i, sizeof(c), hipMemcpyDeviceToHost, P->stream);
@@ -990,14 +1081,15 @@ int ah_pool_destroy(ah_pool* P)
     for (StageChunk& c : P->stage_busy) (void)hipEventDestroy(c.ev);
     for (hipEvent_t ev : P->free_events) (void)hipEventDestroy(ev);
     for (Snapshot& sn : P->snaps) {
-        if (sn.h) (void)hipHostFree(sn.h);
         if (sn.ev) (void)hipEventDestroy(sn.ev);
     }
     io_close(&P->io);
     if (P->stage) (void)hipHostFree(P->stage);
     if (P->side) (void)hipStreamDestroy(P->side);
-    if (P->exec) (void)hipGraphExecDestroy(P->exec);
-    if (P->graph) (void)hipGraphDestroy(P->graph);
+    for (auto& kv : P->graphs) {
+        (void)hipGraphExecDestroy(kv.second.exec);
+        (void)hipGraphDestroy(kv.second.graph);
+    }
     if (P->d_work) (void)hipFree(P->d_work);
     if (P->d_lat) (void)hipFree(P->d_lat);
     if (P->d_counters) (void)hipFree(P->d_counters);

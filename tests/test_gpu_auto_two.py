@@ -118,3 +118,38 @@ def test_captured_steps_replay(ah, precision):
     for a, b in zip(*out):
         assert np.array_equal(a, b)
     assert not np.array_equal(out[0][0], out[0][2])
+
+
+@pytest.mark.parametrize("chunk", [1, 3, 20])
+def test_pool_replays_hold_every_node_with_work(ah, chunk):
+    """A replay leaves out nodes without work, by the host's own count of the
+    steps: requests of every short length and cadence, in both precisions,
+    joining while others run, give the series and fields of a lattice alone,
+    and are done on the host's count when they are on the device's."""
+    P = ah.Params
+    reqs = [(P(N=8 + 2 * (k % 3), precision="fp64" if k % 4 == 1 else "fp32", m=1.0), 40 + k, n, every)
+            for k, (n, every) in enumerate((n, e) for n in (0, 1, 2, 3, 7) for e in (0, 1, 2, 5))]
+    got = {}
+    with ah.Pool(hbm_budget=256 << 20, max_slots=len(reqs)) as pool:
+        waiting, ids = list(enumerate(reqs)), {}
+        for _ in range(200):
+            if waiting:
+                k, r = waiting.pop(0)
+                ids[pool.submit(*r)] = k
+            pool.advance(chunk)
+            pool.synchronize()
+            for rid in pool.poll_async():
+                k = ids[rid]
+                p, _, n, _ = reqs[k]
+                assert pool.progress(rid) == (n, n)
+                cfg = pool.step_config(rid)
+                state = pool.get_state(rid, p.N)
+                got[k] = (cfg, state, pool.results(rid))
+            if len(got) == len(reqs):
+                break
+        assert len(got) == len(reqs)
+    for k, (p, seed, n, every) in enumerate(reqs):
+        cfg, state, series = got[k]
+        st, ser = run_alone(p, seed, n, every, cfg["tile"], cfg["zchunk"])
+        assert np.array_equal(state, st), (p, n, every)
+        assert len(series) == len(ser) and all(same_record(a, b) for a, b in zip(series, ser)), (p, n, every)
