@@ -175,6 +175,7 @@ bool default_tile(int precision, int N, int* tx, int* ty);
 int resident_per_cu(int kernel, int precision, int tx, int ty, bool measured);
 // Automatic z-chunk of a tiled launch.
 int auto_zchunk(int kernel, int precision, int N, int tx, int ty, bool measured);
+int start_planes(int kernel, int tx, int ty);
 // Tiling of the two-step passes of an automatic configuration; false if it
 // takes none.
 bool default_two(int precision, int N, TileConfig* two);

@@ -33,6 +33,7 @@
 #include <cstdint>
 #include <cstring>
 #include <deque>
+#include <functional>
 #include <map>
 #include <new>
 #include <string>
@@ -390,6 +391,53 @@ hipError_t retire_graphs(ah_pool* P)
     return hipSuccess;
 }
 
+// z-chunk of every lattice of one two-step node, by side N: the cap on the
+// planes of a chunk (or none: each lattice's z-chunk of its own, which alone
+// fills the chip best) for which the node's items, longest first, fill the
+// chip's workgroup places in the least time.  Forty-eight lattices of 32^3 ..
+// 64^3 FP32 fill it best on chunks of 16 planes (MI355X, an ensemble: 10.4 ms,
+// 11.3 on 8 planes, 12.2 on 32), five of 52^3 .. 131^3 on shorter ones (a
+// stream of 11 requests: 13.2 ms on 16 planes, 12.1 by this rule).  The fields
+// do not depend on it.
+std::map<int, int> two_step_chunks(int precision, int tx, int ty, const std::map<int, int>& count)
+{
+    const int places = 256 * resident_per_cu(AH_KERNEL_TILE2, precision, tx, ty, false);
+    const int start = start_planes(AH_KERNEL_TILE2, tx, ty);
+    std::map<int, int> best, own;
+    for (auto& kv : count) own[kv.first] = auto_zchunk(AH_KERNEL_TILE2, precision, kv.first, tx, ty, false);
+    int64_t best_t = -1;
+    for (int cap : {0, 4, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64, 96, 128, 256, 4096}) {
+        std::map<int, int> zc;
+        std::map<int, int64_t, std::greater<int>> items;  // by length in planes
+        for (auto& kv : count) {
+            const int N = kv.first;
+            int c = own[N];
+            if (cap > 0) {
+                const int most = std::min(std::max(cap, min_zchunk(N)), N), nz = (N + most - 1) / most;
+                c = std::max((N + nz - 1) / nz, std::min(min_zchunk(N), N));
+            }
+            zc[N] = c;
+            items[c + start] += (int64_t)kv.second * ((N + tx - 1) / tx) * ((N + ty - 1) / ty) * ((N + c - 1) / c);
+        }
+        // list scheduling: each item to the place that is free first
+        std::map<int64_t, int64_t> free_at{{0, places}};
+        for (auto& it : items)
+            for (int64_t left = it.second; left > 0;) {
+                const auto first = free_at.begin();
+                const int64_t t = first->first, n = std::min(left, first->second);
+                if ((first->second -= n) == 0) free_at.erase(first);
+                free_at[t + it.first] += n;
+                left -= n;
+            }
+        const int64_t t = free_at.rbegin()->first;
+        if (best_t < 0 || t < best_t) {
+            best_t = t;
+            best = zc;
+        }
+    }
+    return best;
+}
+
 // Rebuild descriptors and work lists, and the per-step graph when its
 // node layout no longer fits.  Nothing here waits for the stream: the
 // uploads are ordered after the replays already queued, which keep reading
@@ -429,12 +477,22 @@ int rebuild(ah_pool* P)
         by_shape[GroupKey{2, s.p.precision, s.meas.tx, s.meas.ty}].push_back(i);
         if (s.two.zchunk > 0) by_shape[GroupKey{3, s.p.precision, s.two.tx, s.two.ty}].push_back(i);
     }
+    for (auto& kv : by_shape) {
+        if (kv.first.kind != 3) continue;
+        std::map<int, int> count;
+        for (int i : kv.second) ++count[P->slots[i].p.N];
+        const std::map<int, int> zc = two_step_chunks(kv.first.precision, kv.first.tx, kv.first.ty, count);
+        for (int i : kv.second) desc[i].two_zchunk = P->slots[i].d.two_zchunk = zc.at(P->slots[i].p.N);
+    }
     // The step kernels run one block per item and give XCD x (which runs
     // blocks x, x+8, ...) the x-th eighth of the list.  So that every XCD
     // gets an equal share of every lattice, with neighbouring tiles (which
     // read each other's halo) in the same L2, each lattice's tiles, in index
-    // order, are cut into eight contiguous runs, run x goes to band x, bands
-    // list the lattices with the longest z-marches first.
+    // order, are cut into eight contiguous runs, and the runs go to the bands
+    // in turn, from the band on where they even out the bands' planes best:
+    // runs differ by a tile, always in the same places (a 48^3 lattice of 18
+    // items has its three-item runs fourth and last).  Bands list the lattices
+    // with the longest z-marches first.
     for (auto& kv : by_shape) {
         const int kind = kv.first.kind;
         auto zc_of = [&](const PoolLattice& d) {
@@ -449,13 +507,28 @@ int rebuild(ah_pool* P)
             return std::min(zc_of(da), da.N) > std::min(zc_of(db), db.N);  // planes per item
         });
         auto& band = step_need[kv.first];
+        std::array<int64_t, kXcdCount> load{};  // planes in each band
         for (int i : order) {
             const PoolLattice& d = P->slots[i].d;
             const int tiles_z = (d.N + zc_of(d) - 1) / zc_of(d);
             const int nt = tiles_of(d) * tiles_z;
+            const int planes = std::min(zc_of(d), d.N);
+            auto run = [&](int x) { return (int)((int64_t)nt * x / kXcdCount); };  // first tile of run x
+            int shift = 0;
+            int64_t least = -1;
+            for (int c = 0; c < kXcdCount && nt % kXcdCount != 0; ++c) {
+                int64_t most = 0;
+                for (int x = 0; x < kXcdCount; ++x)
+                    most = std::max(most, load[(x + c) % kXcdCount] + (int64_t)(run(x + 1) - run(x)) * planes);
+                if (least < 0 || most < least) {
+                    least = most;
+                    shift = c;
+                }
+            }
             for (int x = 0; x < kXcdCount; ++x) {
-                const int t0 = (int)((int64_t)nt * x / kXcdCount), t1 = (int)((int64_t)nt * (x + 1) / kXcdCount);
-                for (int t = t0; t < t1; ++t) band[x].push_back({i, t});
+                const int to = (x + shift) % kXcdCount;
+                load[to] += (int64_t)(run(x + 1) - run(x)) * planes;
+                for (int t = run(x); t < run(x + 1); ++t) band[to].push_back({i, t});
             }
         }
     }
@@ -683,7 +756,7 @@ int ah_pool_create(size_t hbm_budget, int32_t max_slots, void* hip_stream, ah_po
 // alone; z-chunks of at least 16 planes.  The measured node runs the
 // measured march's tiling (measured_tiling), as a lattice alone does.
 // Lattices also take two-step passes wherever neither of two snapshots is
-// due (two), with the automatic z-chunk of at least 16 planes, on the tuned
+// due (two), with z-chunks by what is in the pool (two_step_chunks), on the tuned
 // two-step tile shape, else 64 x 8 for FP32 and 32 x 8 for FP64; FP64 ones
 // from N = 65 on (default_two; in a pool the pass does not lose below that
 // for FP32, as other lattices fill the chip).
@@ -713,7 +786,7 @@ static int pool_config(const ah_params& p, ah_step_config* cfg, TileConfig* two,
     cfg->zchunk = floor16(cfg->zchunk);
     *two = TileConfig{0, 0, 0};
     if (take_two && tile2_supported(p.precision, two_tx, two_ty))
-        *two = TileConfig{two_tx, two_ty, floor16(auto_zchunk(AH_KERNEL_TILE2, p.precision, p.N, two_tx, two_ty, false))};
+        *two = TileConfig{two_tx, two_ty, auto_zchunk(AH_KERNEL_TILE2, p.precision, p.N, two_tx, two_ty, false)};
     return AH_OK;
 }
 

@@ -517,13 +517,19 @@ int resident_per_cu(int kernel, int precision, int tx, int ty, bool measured)
     return std::max(1, (precision == AH_FP64 || measured ? 8 : 16) / waves);
 }
 
+// Planes' worth of time that a chunk's start takes.
+int start_planes(int kernel, int tx, int ty)
+{
+    return kernel != AH_KERNEL_TILE2 ? 1 : (tx * ty > 256 ? 4 : 3);
+}
+
 namespace {
 
 // Estimated time of a tiled launch with z-chunks of zc planes, in units of
 // the time a workgroup that has its CU to itself takes for a plane.
 //
 // Workgroups run in rounds of (CUs x resident workgroups), each as long as
-// a chunk's planes and its start, `ramp` planes more.  A round in which all
+// a chunk's planes and its start (start_planes).  A round in which all
 // of a CU's places are taken lasts `full` times as long as one in which a
 // workgroup has its CU to itself.  Both fitted to a sweep on MI355X (27 sizes
 // of 24 .. 640, seven kernel and tile shapes in both precisions, up to 16
@@ -538,7 +544,7 @@ double launch_estimate(int kernel, int precision, int N, int tx, int ty, bool me
     const int res = resident_per_cu(kernel, precision, tx, ty, measured);
     const bool two = kernel == AH_KERNEL_TILE2;
     const double full = res == 1 ? 1.0 : two ? 2.0 : (precision == AH_FP64 || measured ? 1.6 : (res == 2 ? 1.4 : 1.8));
-    const int ramp = !two ? 1 : (tx * ty > 256 ? 4 : 3);
+    const int ramp = start_planes(kernel, tx, ty);
     const int nb = ((N + tx - 1) / tx) * ((N + ty - 1) / ty) * ((N + zc - 1) / zc);  // < 2^28 for N <= 4096
     const int slots = kCUs * res;
     const int left = (nb % slots + kCUs - 1) / kCUs;  // workgroups per CU of the last round

@@ -881,8 +881,9 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
 // Waves per SIMD the compiler must leave room for.  The plain FP32 march
 // fits in 128 registers, i.e. four waves per SIMD: two 512-thread workgroups
 // per CU, so one can load while the other waits at a barrier.  FP64 fits two
-// (its measured march takes 255 registers).  The FP32 measured march takes 176
-// and runs two; held to 168 for three it spills, and runs 30% slower.
+// (its measured march takes 255 registers).  The FP32 measured march takes 174
+// and runs two; held to 168 for three it spills 8, and runs slower (512^3 3583
+// us against 3400, 128^3 73 against 65).
 template <typename R, bool MEAS>
 constexpr int kMinWaves = sizeof(R) == 8 ? 2 : (MEAS ? 1 : 4);
 

@@ -153,3 +153,27 @@ def test_pool_replays_hold_every_node_with_work(ah, chunk):
         st, ser = run_alone(p, seed, n, every, cfg["tile"], cfg["zchunk"])
         assert np.array_equal(state, st), (p, n, every)
         assert len(series) == len(ser) and all(same_record(a, b) for a, b in zip(series, ser)), (p, n, every)
+
+
+@pytest.mark.parametrize("precision,sizes", [
+    ("fp32", (66,)), ("fp32", (8, 9, 66)), ("fp32", (24,) * 20 + (40,) * 9 + (51, 90)), ("fp64", (65, 66, 90, 130)),
+])
+def test_pool_work_lists_hold_every_tile(ah, precision, sizes):
+    """Two-step z-chunks follow from what is in the pool, and the tiles' runs
+    are dealt to the XCDs by load: whatever the mix, every site is stepped
+    once (the fields of a lattice alone)."""
+    reqs = [(ah.Params(N=N, precision=precision, m=1.0), 70 + k, 5, 0) for k, N in enumerate(sizes)]
+    with ah.Pool(hbm_budget=2 << 30, max_slots=40) as pool:
+        ids = [pool.submit(*r) for r in reqs[:-1]]
+        pool.advance(1)
+        ids.append(pool.submit(*reqs[-1]))
+        pool.advance(7)
+        assert sorted(pool.poll()) == sorted(ids)
+        for k, (p, seed, n, _) in enumerate(reqs):
+            if k % 5 and k < len(reqs) - 3:
+                continue
+            with ah.Lattice(p) as lat:
+                lat.set_step_config("tile")
+                lat.init(seed)
+                lat.step(n)
+                assert np.array_equal(pool.get_state(ids[k], p.N), lat.get_state()), (k, p.N)
