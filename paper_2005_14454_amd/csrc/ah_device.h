@@ -14,9 +14,10 @@ namespace ah {
 // records t / 16, t / 16 + 64, ..., so that all slots go through one chain of
 // whole-line loads (eight in flight), shuffles and one pass through LDS,
 // rather than through a chain and a barrier tree per slot, one slot after
-// another.  With the record written straight to the host, ah_measure on a
-// 32^3 FP32 lattice takes 35.6 us on MI355X (48.8 us with a slot at a time and
-// a copy behind it), on a 256^3 FP64 lattice 843 us (859 us).
+// another.  With the record written straight to the host this took
+// ah_measure of a 32^3 FP32 lattice on MI355X from 48.8 us (a slot at a time
+// and a copy behind it) to 35.6, of a 256^3 FP64 lattice from 859 us to 843
+// (26.5 and 650 us with the present march).
 constexpr int kFoldThreads = 1024;
 constexpr int kFoldRed = kFoldThreads / 64 * kMeasStride;
 __device__ inline void fold_records(const double* __restrict__ partials, int nblocks, double* __restrict__ out,

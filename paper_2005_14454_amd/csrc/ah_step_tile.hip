@@ -23,7 +23,7 @@
 // MI355X: FP32 128 x 4 2.00 ms a step, 5.4 TB/s of algorithmic bytes; FP64
 // 64 x 8 4.49 ms, 4.8 TB/s; a copy reaches 5.5 TB/s); the latency of a chunk's
 // first loads and barriers for a small one (64^3 FP64, 2-plane chunks: 13.0
-// us); instruction issue and latency for the measured march (512^3: FP32 3.65
+// us); instruction issue and latency for the measured march (512^3: FP32 3.4
 // ms, FP64 6.2 ms).  Links in three slots, so that one barrier a plane is
 // enough, and every load of a chunk's start issued before its first barrier
 // took the measured march from 3.74 and 7.3 ms and the 64^3 step from 16.4 us
@@ -286,8 +286,8 @@ __device__ inline double swap_add(double a, double b)
 // every lane: 8 + 4 + 2 + 1 additions and two more, where 16 butterflies take
 // 96 and, through LDS, 192 permutes, which on a short march are a tenth of
 // its time (MI355X, 32^3 FP32: 15.0 us with the butterflies, 12.9 now; 64^3 FP64
-// 25.3, 23.1).  Every sum
-// goes through the lanes in the butterfly's order: 32, 16, 8, 4, 2, 1.
+// 25.3, 23.1).  Every sum goes through the lanes in the butterfly's order: 32,
+// 16, 8, 4, 2, 1.
 __device__ inline double wave_sums(const double (&v)[16])
 {
     const int lane = threadIdx.x & 63;
