@@ -288,24 +288,25 @@ int ah_tune_load(const char* path);
 /* --------------------------------------------------------- lattice pool */
 /* A pool keeps many independent lattices (any N, precision, expansion
  * history; compact action) resident in one device arena and advances all
- * active ones together: each ah_pool_advance step is one replay of a HIP
- * graph holding, as far as there is work for them, the measured step of the lattices whose snapshot is due (it
- * forms every diagnostic, the Gauss residual included) and its fixed-order
- * fold, the plain step of every other active lattice (one kernel node per precision and
- * tile shape, one block per (lattice, tile) work item) and a counter update;
- * a lattice (FP64: with N > 64 or a two-step tuning entry) whose next two
- * snapshots are both not due takes a two-step pass instead (AH_KERNEL_TILE2;
- * FP32 64 x 8, FP64 32 x 8, unless its tuning entry names another two-step
- * shape), which advances it by two steps in that replay.  Pool lattices run the tuned one-step (else the default) tile
- * shape with z-chunks of at least 16 planes (ah_pool_step_config reports
- * them), and their measured steps the measured march's tiling, as a lattice
- * alone does.  Every lattice takes the coefficients of its own step from its own
- * FP64 table, so its fields and diagnostics are bitwise identical to the
- * same lattice run alone through ah_step / ah_measure with the same tiling.
- * Requests enter and leave between advances (continuous batching); the
- * graphs are captured again only when a node's work list outgrows its
- * capacity (or shrinks far below it) or a new node is needed.  A pool is
- * used from one host thread at a time. */
+ * active ones together.  Each ah_pool_advance step is one replay of a HIP
+ * graph that holds, as far as there is work for them, the measured step of the
+ * lattices whose snapshot is due (it forms every diagnostic, the Gauss residual
+ * included) and its fixed-order fold, the plain step of every other active
+ * lattice (one kernel node per precision and tile shape, one block per
+ * (lattice, tile) work item) and a counter update.  A lattice (FP64: with
+ * N > 64 or a two-step tuning entry) whose next two snapshots are both not due
+ * takes a two-step pass instead (AH_KERNEL_TILE2; FP32 64 x 8, FP64 32 x 8,
+ * unless its tuning entry names another two-step shape), which advances it by
+ * two steps in that replay.  Pool lattices run the tuned one-step (else the
+ * default) tile shape with z-chunks of at least 16 planes (two-step passes: by
+ * what the pool holds; ah_pool_step_config reports the one-step tiling), and
+ * their measured steps the measured march's tiling, as a lattice alone does.
+ * Every lattice takes the coefficients of its own step from its own FP64 table,
+ * so its fields and diagnostics are bitwise identical to the same lattice run
+ * alone through ah_step / ah_measure with the same tiling.  Requests enter and
+ * leave between advances (continuous batching); the graphs are captured again
+ * only when a node's work list outgrows its capacity (or shrinks far below it)
+ * or a new node is needed.  A pool is used from one host thread at a time. */
 typedef struct ah_pool ah_pool;
 
 typedef struct ah_pool_info {
@@ -351,10 +352,10 @@ int ah_pool_advance(ah_pool* pool, int32_t nsteps);
  * number written).  Synchronises with the pool stream. */
 int ah_pool_poll(ah_pool* pool, int64_t* done_ids, int32_t cap, int32_t* n);
 
-/* As ah_pool_poll without waiting: reports the lattices that the newest
- * counter copy already on the host shows finished (the copies queued by
- * ah_pool_advance land as the GPU reaches them).  For serving loops that keep
- * the GPU busy while they admit and collect requests. */
+/* As ah_pool_poll without waiting: reports the lattices finished as of the
+ * newest event that the GPU has passed (ah_pool_advance records them behind
+ * its steps).  For serving loops that keep the GPU busy while they admit and
+ * collect requests. */
 int ah_pool_poll_async(ah_pool* pool, int64_t* done_ids, int32_t cap, int32_t* n);
 
 /* Tile shape and z-chunk a request is stepped with (kernel AH_KERNEL_TILE).

@@ -902,8 +902,8 @@ hipError_t plain_steps(ah_handle* h, int64_t nsteps)
     } else if (tc.zchunk > 0 && nsteps >= 2) {
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
         const hipError_t e = hipStreamIsCapturing(h->stream, &st);
-        if (e != hipSuccess) return e;
-        if (st != hipStreamCaptureStatusNone) tc.zchunk = 0;
+        if (e != hipSuccess) (void)hipGetLastError();  // the launch will say what is wrong
+        if (e != hipSuccess || st != hipStreamCaptureStatusNone) tc.zchunk = 0;
     }
     while (nsteps > 0) {
         hipError_t e;
@@ -1339,9 +1339,10 @@ int ah_get_winding(ah_handle* h, int8_t* host_w)
         // site of their 20 or 40): the next step writes those anew
         int8_t* d = (int8_t*)h->mom[h->curm ^ 1][0];
         const size_t bytes = 3 * (size_t)h->V;
-        hipError_t e = h->p.precision == AH_FP64
-                           ? launch_winding<double>(fields_of<double>(h, h->cur), lconst(h->p), d, h->stream)
-                           : launch_winding<float>(fields_of<float>(h, h->cur), lconst(h->p), d, h->stream);
+        hipError_t e = hipStreamSynchronize(h->stream);
+        if (e == hipSuccess)
+            e = h->p.precision == AH_FP64 ? launch_winding<double>(fields_of<double>(h, h->cur), lconst(h->p), d, h->stream)
+                                          : launch_winding<float>(fields_of<float>(h, h->cur), lconst(h->p), d, h->stream);
         IoStage* st = nullptr;
         if (e == hipSuccess) e = io_stage(h, bytes, &st);
         if (e == hipSuccess) e = bytes_download(d, host_w, bytes, *st, h->stream);

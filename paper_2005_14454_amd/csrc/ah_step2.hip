@@ -19,12 +19,12 @@
 // one wave.
 //
 // What bounds it: instruction issue and latency (512^3 FP32 on 64 x 8 tiles,
-// one 11-wave workgroup per CU: vector ALU busy 67%; HBM 3.7 TB/s).  MI355X,
-// us per step, against stage 2 one plane behind stage 1 with a barrier behind
-// each of them (half the LDS, two barriers a plane): 512^3 FP32 64 x 8 1468
-// against 1677, FP64 32 x 8 3774 against 4420; 64^3 FP32 7.7 against 8.4, FP64
-// 14.9 against 16.1.  Running stage 2 before stage 1 within a phase: 1513 and
-// 4103 at 512^3.
+// one 11-wave workgroup per CU: vector ALU busy 77%; HBM 4.8 TB/s).  MI355X,
+// us per step: 512^3 FP32 64 x 8 1283, FP64 32 x 8 3610.  Stage 2 one plane
+// behind stage 1 with a barrier behind each of them (half the LDS, two
+// barriers a plane) took 1677 and 4420 where this form took 1468 and 3774,
+// before the values in LDS were paired (Pair); stage 2 before stage 1 within a
+// phase 1513 and 4103.
 //
 // Stage 1 reads Pi and E of snapshot n on the ring too, which the
 // neighbouring workgroups' stage 2 would overwrite in place, so Pi and E are
@@ -59,11 +59,49 @@ struct Geom2 {
 // R1.  x and y links are kept for three planes (a phase reads two, as the
 // plaquettes at x-kx and x-ky reach one plane up, and writes the third), z
 // links and phi for two.
+//
+// Two values a site (the x and y links, or the z link and phi) share an array:
+// FP32 ones side by side, so that one 16-byte access has both: LDS reads bound
+// the pass where each value had an array and 8-byte reads of its own (MI355X,
+// us per step: 512^3 FP32 1495, 1283 now; 96^3 17.2, 14.8; 64^3 7.7, 6.3).  FP64
+// ones lie in two rows (at 32 bytes from site to site the lanes of a row would
+// meet in the same banks; 512^3 3828, 3610 now).  A single value of a pair is
+// read as 8 bytes (16 and half of it unused: 1328).
+template <typename R, int S>
+struct alignas(16) Pair {
+    Cx<R> v[2 * S];
+    static constexpr bool kBeside = sizeof(R) == 4;
+    __device__ __forceinline__ Cx<R>& at(int c, int k) { return v[kBeside ? 2 * c + k : c + k * S]; }
+    __device__ __forceinline__ Cx<R> get(int c, int k) const
+    {
+        return v[kBeside ? 2 * c + k : c + k * S];
+    }
+    __device__ __forceinline__ void get(int c, Cx<R>* a, Cx<R>* b) const
+    {
+        if constexpr (kBeside) {
+            const float4 q = *(const float4*)&v[2 * c];
+            *a = {q.x, q.y};
+            *b = {q.z, q.w};
+        } else {
+            *a = v[c];
+            *b = v[c + S];
+        }
+    }
+    __device__ __forceinline__ void set(int c, Cx<R> a, Cx<R> b)
+    {
+        if constexpr (kBeside) {
+            *(float4*)&v[2 * c] = float4{a.r, a.i, b.r, b.i};
+        } else {
+            v[c] = a;
+            v[c + S] = b;
+        }
+    }
+};
 template <typename R, int TX, int TY>
 struct Shared2 {
     using G = Geom2<TX, TY>;
-    Cx<R> u0x[3][G::S2], u0y[3][G::S2], u0z[2][G::S2], p0[2][G::S2];
-    Cx<R> u1x[3][G::S1], u1y[3][G::S1], u1z[2][G::S1], p1[2][G::S1];
+    Pair<R, G::S2> u0[3], w0[2];  // links x, y; link z and phi
+    Pair<R, G::S1> u1[3], w1[2];
     // FP64, where they fit: stage 1's Pi, E and A of a tile site for stage 2
     // two planes later (registers otherwise)
     static constexpr bool HELD =
@@ -81,29 +119,22 @@ struct Step2Args {
 
 // Neighbourhood of the site at index c of a region of width W whose links
 // (x, y, z of plane z; x, y of plane z+1) and phi (plane z) are in LDS.
-template <typename R, int W>
-__device__ __forceinline__ SiteNbr<R> gather_nbr(int c, const Cx<R>* ux, const Cx<R>* uy, const Cx<R>* uz,
-                                                 const Cx<R>* ph, const Cx<R>* uxp, const Cx<R>* uyp)
+template <int W, typename R, int S>
+__device__ __forceinline__ SiteNbr<R> gather_nbr(int c, const Pair<R, S>& u, const Pair<R, S>& w, const Pair<R, S>& up)
 {
     SiteNbr<R> n;
-    n.ph_xm = ph[c - 1];
-    n.ph_xp = ph[c + 1];
-    n.ph_ym = ph[c - W];
-    n.ph_yp = ph[c + W];
-    n.ux_xm = ux[c - 1];
-    n.uy_ym = uy[c - W];
-    n.uy_xp = uy[c + 1];
-    n.ux_yp = ux[c + W];
-    n.uz_xp = uz[c + 1];
-    n.uz_yp = uz[c + W];
-    n.ux_xm_yp = ux[c - 1 + W];
-    n.uy_xm = uy[c - 1];
-    n.uz_xm = uz[c - 1];
-    n.ux_ym = ux[c - W];
-    n.uy_xp_ym = uy[c + 1 - W];
-    n.uz_ym = uz[c - W];
-    n.ux_xm_zp = uxp[c - 1];
-    n.uy_ym_zp = uyp[c - W];
+    w.get(c - 1, &n.uz_xm, &n.ph_xm);
+    w.get(c + 1, &n.uz_xp, &n.ph_xp);
+    w.get(c - W, &n.uz_ym, &n.ph_ym);
+    w.get(c + W, &n.uz_yp, &n.ph_yp);
+    u.get(c - 1, &n.ux_xm, &n.uy_xm);
+    u.get(c - W, &n.ux_ym, &n.uy_ym);
+    n.uy_xp = u.get(c + 1, 1);
+    n.ux_yp = u.get(c + W, 0);
+    n.ux_xm_yp = u.get(c - 1 + W, 0);
+    n.uy_xp_ym = u.get(c + 1 - W, 1);
+    n.ux_xm_zp = up.get(c - 1, 0);
+    n.uy_ym_zp = up.get(c - W, 1);
     return n;
 }
 
@@ -264,33 +295,27 @@ __device__ __forceinline__ void march2_role(Shared2<R, TX, TY>& sh, const Step2A
         // z0-1 into slot 0, U_z of z0-2 (for F^n there) into slot 1
         Cx<R> um2[3], uc[3], up[3];
         links(dx, am2, um2);
-        sh.u0z[1][c2] = um2[2];
+        sh.w0[1].at(c2, 0) = um2[2];
         uz_m = um2[2];
         links(dx, ac, uc);
-        sh.u0x[0][c2] = uc[0];
-        sh.u0y[0][c2] = uc[1];
-        sh.u0z[0][c2] = uc[2];
-        sh.p0[0][c2] = phc;
+        sh.u0[0].set(c2, uc[0], uc[1]);
+        sh.w0[0].set(c2, uc[2], phc);
         links(dx, ap, up);
-        sh.u0x[1][c2] = up[0];
-        sh.u0y[1][c2] = up[1];
+        sh.u0[1].set(c2, up[0], up[1]);
         upz = up[2];
         if constexpr (!TILE) {
             Cx<R> uo[7];
             links(dx, om, uo);
-            sh.u0z[1][co] = uo[0];
-            sh.u0x[0][co] = uo[1];
-            sh.u0y[0][co] = uo[2];
-            sh.u0z[0][co] = uo[3];
-            sh.p0[0][co] = oph;
-            sh.u0x[1][co] = uo[4];
-            sh.u0y[1][co] = uo[5];
+            sh.w0[1].at(co, 0) = uo[0];
+            sh.u0[0].set(co, uo[1], uo[2]);
+            sh.w0[0].set(co, uo[3], oph);
+            sh.u0[1].set(co, uo[4], uo[5]);
             uo_z = uo[6];
         }
         __syncthreads();
         // F^n_xz, F^n_yz at z0-2 of the stage-1 site
-        fxz_m = plaq_sin(um2[0], sh.u0z[1][c2 + 1], uc[0], um2[2]) * k0.inv_dx2;
-        fyz_m = plaq_sin(um2[1], sh.u0z[1][c2 + W2], uc[1], um2[2]) * k0.inv_dx2;
+        fxz_m = plaq_sin(um2[0], sh.w0[1].get(c2 + 1, 0), uc[0], um2[2]) * k0.inv_dx2;
+        fyz_m = plaq_sin(um2[1], sh.w0[1].get(c2 + W2, 0), uc[1], um2[2]) * k0.inv_dx2;
         __syncthreads();
     }
 
@@ -312,30 +337,32 @@ __device__ __forceinline__ void march2_role(Shared2<R, TX, TY>& sh, const Step2A
         if (S1 && more && p > z0 - 1) prefetch(p);
 
         const Cx<R> phq = s1phi;  // phi^{n+1} of plane p-1 = q+1
-        sh.p1[b ^ 1][c1] = s1phi;
-        sh.u1z[b ^ 1][c1] = s1z;
+        sh.w1[b ^ 1].set(c1, s1z, s1phi);
         SiteOut<R> o1 = {}, o2 = {};
         Cx<R> u1[3];
         if constexpr (S1) {
-            const Cx<R> *ux = sh.u0x[sa], *uy = sh.u0y[sa], *uz = sh.u0z[b], *uxp = sh.u0x[sb], *uyp = sh.u0y[sb];
-            const Cx<R> uc[3] = {ux[c2], uy[c2], uz[c2]};
-            const SiteNbr<R> nb = gather_nbr<R, W2>(c2, ux, uy, uz, sh.p0[b], uxp, uyp);
-            o1 = site_update(k0, nb, phm, phc, php, uc, uxp[c2], uyp[c2], uz_m, fxz_m, fyz_m, pr, pi, e, ac);
+            Cx<R> uc[3], upx, upy;
+            sh.u0[sa].get(c2, &uc[0], &uc[1]);
+            uc[2] = sh.w0[b].get(c2, 0);
+            sh.u0[sb].get(c2, &upx, &upy);
+            const SiteNbr<R> nb = gather_nbr<W2>(c2, sh.u0[sa], sh.w0[b], sh.u0[sb]);
+            o1 = site_update(k0, nb, phm, phc, php, uc, upx, upy, uz_m, fxz_m, fyz_m, pr, pi, e, ac);
             fxz_m = o1.fxz;
             fyz_m = o1.fyz;
             uz_m = uc[2];
             links(dx, o1.a, u1);
-            sh.u1x[sa][c1] = u1[0];
-            sh.u1y[sa][c1] = u1[1];
+            sh.u1[sa].set(c1, u1[0], u1[1]);
             s1phi = o1.phi;
             s1z = u1[2];
         }
         if constexpr (S2) {
-            const Cx<R> *ux = sh.u1x[sb], *uy = sh.u1y[sb], *uz = sh.u1z[b], *uxp = sh.u1x[sc], *uyp = sh.u1y[sc];
-            const Cx<R> vc[3] = {ux[c1], uy[c1], uz[c1]}, chc = sh.p1[b][c1];
+            Cx<R> vc[3], chc, vpx, vpy;
+            sh.u1[sb].get(c1, &vc[0], &vc[1]);
+            sh.w1[b].get(c1, &vc[2], &chc);
+            sh.u1[sc].get(c1, &vpx, &vpy);
             const R qe[3] = {h(b, 2), h(b, 3), h(b, 4)}, qa[3] = {h(b, 5), h(b, 6), h(b, 7)};
-            const SiteNbr<R> nb = gather_nbr<R, W1>(c1, ux, uy, uz, sh.p1[b], uxp, uyp);
-            o2 = site_update(k1, nb, chm, chc, phq, vc, uxp[c1], uyp[c1], vz_m, gxz_m, gyz_m, h(b, 0), h(b, 1), qe, qa);
+            const SiteNbr<R> nb = gather_nbr<W1>(c1, sh.u1[sb], sh.w1[b], sh.u1[sc]);
+            o2 = site_update(k1, nb, chm, chc, phq, vc, vpx, vpy, vz_m, gxz_m, gyz_m, h(b, 0), h(b, 1), qe, qa);
             gxz_m = o2.fxz;
             gyz_m = o2.fyz;
             vz_m = vc[2];
@@ -365,19 +392,15 @@ __device__ __forceinline__ void march2_role(Shared2<R, TX, TY>& sh, const Step2A
             if (more) {
                 // stage-1 operands of the next phase: U_z and phi of plane
                 // p+1, links of plane p+2 (U_z held)
-                sh.u0z[b ^ 1][c2] = upz;
-                sh.p0[b ^ 1][c2] = php;
+                sh.w0[b ^ 1].set(c2, upz, php);
                 Cx<R> un[3];
                 links(dx, na, un);
-                sh.u0x[sc][c2] = un[0];
-                sh.u0y[sc][c2] = un[1];
+                sh.u0[sc].set(c2, un[0], un[1]);
                 upz = un[2];
                 if constexpr (!TILE) {
-                    sh.u0z[b ^ 1][co] = uo_z;
-                    sh.p0[b ^ 1][co] = noph;
+                    sh.w0[b ^ 1].set(co, uo_z, noph);
                     links(dx, noa, un);
-                    sh.u0x[sc][co] = un[0];
-                    sh.u0y[sc][co] = un[1];
+                    sh.u0[sc].set(co, un[0], un[1]);
                     uo_z = un[2];
                 }
                 for (int d = 0; d < 3; ++d) {
