@@ -112,6 +112,45 @@ __device__ inline Cx<R> cmulc(Cx<R> a, Cx<R> b)  // conj(a) * b
     return {fm(a.r, b.r, a.i * b.i), fm(a.r, b.i, -(a.i * b.r))};
 }
 
+// Two values of each of S sites in LDS (the x and y links, or the z link and
+// phi) in one array: FP32 ones side by side, so that one 16-byte access has
+// both, FP64 ones in two rows (at 32 bytes from site to site the lanes of a row
+// would meet in the same banks).  With an array and 8-byte reads for each value
+// LDS reads bound the two-step pass (MI355X, us per step: 512^3 FP32 1495, 1283
+// now, FP64 3828, 3610 now; 96^3 FP32 17.2, 14.8); the marches gain little at
+// 512^3, 7% on 64^3 FP64 (12.9 to 12.0).  A single value of a pair is read as 8
+// bytes (as 16, half of it unused: 1328).
+template <typename R, int S>
+struct alignas(16) Pair {
+    Cx<R> v[2 * S];
+    static constexpr bool kBeside = sizeof(R) == 4;
+    __device__ __forceinline__ Cx<R>& at(int c, int k) { return v[kBeside ? 2 * c + k : c + k * S]; }
+    __device__ __forceinline__ Cx<R> get(int c, int k) const
+    {
+        return v[kBeside ? 2 * c + k : c + k * S];
+    }
+    __device__ __forceinline__ void get(int c, Cx<R>* a, Cx<R>* b) const
+    {
+        if constexpr (kBeside) {
+            const float4 q = *(const float4*)&v[2 * c];
+            *a = {q.x, q.y};
+            *b = {q.z, q.w};
+        } else {
+            *a = v[c];
+            *b = v[c + S];
+        }
+    }
+    __device__ __forceinline__ void set(int c, Cx<R> a, Cx<R> b)
+    {
+        if constexpr (kBeside) {
+            *(float4*)&v[2 * c] = float4{a.r, a.i, b.r, b.i};
+        } else {
+            v[c] = a;
+            v[c + S] = b;
+        }
+    }
+};
+
 // Links U_j = exp(-i dx A_j) = (cos(dx A_j), -sin(dx A_j)) of K values of A.
 //
 // FP64: the reduced-range sincos (accurate to ~2 ulp for |x| <= 1e9), the

@@ -59,44 +59,6 @@ struct Geom2 {
 // R1.  x and y links are kept for three planes (a phase reads two, as the
 // plaquettes at x-kx and x-ky reach one plane up, and writes the third), z
 // links and phi for two.
-//
-// Two values a site (the x and y links, or the z link and phi) share an array:
-// FP32 ones side by side, so that one 16-byte access has both: LDS reads bound
-// the pass where each value had an array and 8-byte reads of its own (MI355X,
-// us per step: 512^3 FP32 1495, 1283 now; 96^3 17.2, 14.8; 64^3 7.7, 6.3).  FP64
-// ones lie in two rows (at 32 bytes from site to site the lanes of a row would
-// meet in the same banks; 512^3 3828, 3610 now).  A single value of a pair is
-// read as 8 bytes (16 and half of it unused: 1328).
-template <typename R, int S>
-struct alignas(16) Pair {
-    Cx<R> v[2 * S];
-    static constexpr bool kBeside = sizeof(R) == 4;
-    __device__ __forceinline__ Cx<R>& at(int c, int k) { return v[kBeside ? 2 * c + k : c + k * S]; }
-    __device__ __forceinline__ Cx<R> get(int c, int k) const
-    {
-        return v[kBeside ? 2 * c + k : c + k * S];
-    }
-    __device__ __forceinline__ void get(int c, Cx<R>* a, Cx<R>* b) const
-    {
-        if constexpr (kBeside) {
-            const float4 q = *(const float4*)&v[2 * c];
-            *a = {q.x, q.y};
-            *b = {q.z, q.w};
-        } else {
-            *a = v[c];
-            *b = v[c + S];
-        }
-    }
-    __device__ __forceinline__ void set(int c, Cx<R> a, Cx<R> b)
-    {
-        if constexpr (kBeside) {
-            *(float4*)&v[2 * c] = float4{a.r, a.i, b.r, b.i};
-        } else {
-            v[c] = a;
-            v[c + S] = b;
-        }
-    }
-};
 template <typename R, int TX, int TY>
 struct Shared2 {
     using G = Geom2<TX, TY>;

@@ -77,9 +77,7 @@ struct TileShared {
     // x and y links of planes z and z+1, which the update of plane z reads,
     // and of plane z+2, which the same phase writes; z links and phi of planes
     // z (read) and z+1 (written)
-    Cx<R> Uxy[3][2][RS];
-    Cx<R> Uz[2][RS];
-    Cx<R> Phi[2][RS];
+    Pair<R, RS> U[3], W[2];
 };
 
 template <typename R, int TX, int TY>
@@ -526,25 +524,21 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
         links(dx, am, um);
         links(dx, Ac, Uc);
         links(dx, Ap, Up);
-        sh.Uz[1][ro] = um[2];
-        sh.Uz[0][ro] = Uc[2];
-        for (int d = 0; d < 2; ++d) {
-            sh.Uxy[0][d][ro] = Uc[d];
-            sh.Uxy[1][d][ro] = Up[d];
-        }
-        sh.Phi[0][ro] = phi_c;
+        sh.W[1].at(ro, 0) = um[2];
+        sh.W[0].set(ro, Uc[2], phi_c);
+        sh.U[0].set(ro, Uc[0], Uc[1]);
+        sh.U[1].set(ro, Up[0], Up[1]);
         if constexpr (MEAS)
             for (int d = 0; d < 3; ++d) mx->A[0][d][ro] = Ac[d];
         if (has_halo) {
             links(dx, hm, uhm);
-            sh.Uz[1][rh] = uhm[0];
+            sh.W[1].at(rh, 0) = uhm[0];
             links(dx, h0, uh);
-            sh.Uz[0][rh] = uh[2];
-            for (int d = 0; d < 2; ++d) sh.Uxy[0][d][rh] = uh[d];
+            sh.W[0].set(rh, uh[2], hph0);
+            sh.U[0].set(rh, uh[0], uh[1]);
             links(dx, ha1, uh);
-            for (int d = 0; d < 2; ++d) sh.Uxy[1][d][rh] = uh[d];
+            sh.U[1].set(rh, uh[0], uh[1]);
             huz = uh[2];
-            sh.Phi[0][rh] = hph0;
             if constexpr (MEAS)
                 for (int d = 0; d < 3; ++d) mx->A[0][d][rh] = h0[d];
         }
@@ -556,8 +550,8 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
         bz_m = cmulc(um[2], phi_m);
         __syncthreads();
         // F_xz, F_yz of the own column at plane z0-1
-        fxz_m = plaq_sin(um[0], sh.Uz[1][ro + 1], Uc[0], um[2]) * inv_dx2;
-        fyz_m = plaq_sin(um[1], sh.Uz[1][ro + RW], Uc[1], um[2]) * inv_dx2;
+        fxz_m = plaq_sin(um[0], sh.W[1].get(ro + 1, 0), Uc[0], um[2]) * inv_dx2;
+        fyz_m = plaq_sin(um[1], sh.W[1].get(ro + RW, 0), Uc[1], um[2]) * inv_dx2;
         __syncthreads();
         // wait here for the loads that the first plane takes from registers,
         // rather than on every pass through the loop that it enters
@@ -575,22 +569,20 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
         // neighbour slots in the region
         const int rxm = ro - 1, rxp = ro + 1, rym = ro - RW, ryp = ro + RW;
         const int rxm_yp = ro - 1 + RW, rxp_ym = ro + 1 - RW;
-        const Cx<R> *ux = sh.Uxy[s0][0], *uy = sh.Uxy[s0][1], *uz = sh.Uz[b], *uxp = sh.Uxy[s1][0], *uyp = sh.Uxy[s1][1];
-        const Cx<R>* sPhi = sh.Phi[b];
+        const auto &su = sh.U[s0], &sup = sh.U[s1];  // x, y links of planes z and z+1
+        const auto& sw = sh.W[b];                     // U_z and phi of plane z
         if constexpr (MEAS)
             if (has_ph) {
-                const Cx<R> u = (ph_z ? uz : (ph_row ? ux : uy))[ph_r], nb = sPhi[ph_n], up = q.pphi;
-                mx->Y[b][ph_d][ph_r] = phase(sPhi[ph_r], u, ph_z ? up : nb, mx->A[b][ph_d][ph_r]);
+                const Cx<R> u = ph_z ? sw.get(ph_r, 0) : su.get(ph_r, ph_row ? 0 : 1), nb = sw.get(ph_n, 1), up = q.pphi;
+                mx->Y[b][ph_d][ph_r] = phase(sw.get(ph_r, 1), u, ph_z ? up : nb, mx->A[b][ph_d][ph_r]);
             }
 
         // ---- 1. update of the own site at plane z
         {
             if constexpr (ULDS) {
-                Uc[0] = ux[ro];
-                Uc[1] = uy[ro];
-                Uc[2] = uz[ro];
-                Up[0] = uxp[ro];
-                Up[1] = uyp[ro];
+                su.get(ro, &Uc[0], &Uc[1]);
+                Uc[2] = sw.get(ro, 0);
+                sup.get(ro, &Up[0], &Up[1]);
             }
             if constexpr (GAUSS && !GLDS) {
                 // FP64: the Gauss residual of the site first, while few values
@@ -608,9 +600,23 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
                     gmax = fmax(gmax, fabs(G));
                 }
             }
-            const Cx<R> ph_xm = sPhi[rxm], ph_xp = sPhi[rxp], ph_ym = sPhi[rym], ph_yp = sPhi[ryp];
-            const Cx<R> ux_xm = ux[rxm];  // U_x^{x-kx}
-            const Cx<R> uy_ym = uy[rym];  // U_y^{x-ky}
+            Cx<R> ph_xm, ph_xp, ph_ym, ph_yp, uz_xm, uz_xp, uz_ym, uz_yp;
+            Cx<R> ux_xm, uy_xm, ux_ym, uy_ym;  // U_x, U_y at x-kx and x-ky
+            if constexpr (Pair<R, 1>::kBeside) {
+                sw.get(rxm, &uz_xm, &ph_xm);
+                sw.get(rxp, &uz_xp, &ph_xp);
+                sw.get(rym, &uz_ym, &ph_ym);
+                sw.get(ryp, &uz_yp, &ph_yp);
+                su.get(rxm, &ux_xm, &uy_xm);
+                su.get(rym, &ux_ym, &uy_ym);
+            } else {  // the others where they are used
+                ph_xm = sw.get(rxm, 1);
+                ph_xp = sw.get(rxp, 1);
+                ph_ym = sw.get(rym, 1);
+                ph_yp = sw.get(ryp, 1);
+                ux_xm = su.get(rxm, 0);
+                uy_ym = su.get(rym, 1);
+            }
             // covariant Laplacian: sum_j U_j^x phi^{x+j} + conj(U_j^{x-j}) phi^{x-j} - 2 phi^x
             const Cx<R> fx = cmul(Uc[0], ph_xp), fy = cmul(Uc[1], ph_yp), fz = cmul(Uc[2], phi_p);
             const Cx<R> bx = cmulc(ux_xm, ph_xm), by = cmulc(uy_ym, ph_ym), bz = bz_m;
@@ -660,8 +666,11 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
                 plaq_angles(ma.dx, dx, q4, th_b);
             }
             // plaquettes at x (F_ij^x, i<j)
-            const Cx<R> uy_xp = uy[rxp], ux_yp = ux[ryp];
-            const Cx<R> uz_xp = uz[rxp], uz_yp = uz[ryp];
+            const Cx<R> uy_xp = su.get(rxp, 1), ux_yp = su.get(ryp, 0);
+            if constexpr (!Pair<R, 1>::kBeside) {
+                uz_xp = sw.get(rxp, 0);
+                uz_yp = sw.get(ryp, 0);
+            }
             R sxy, sxz, syz, oxy = 0, oxz = 0, oyz = 0;
             if constexpr (MEAS) {
                 oxy = plaq_omc(Uc[0], uy_xp, ux_yp, Uc[1], &sxy);
@@ -676,9 +685,14 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
             const R fxz = sxz * inv_dx2;
             const R fyz = syz * inv_dx2;
             // plaquettes at x - kx and x - ky
-            const Cx<R> ux_xm_yp = ux[rxm_yp], uy_xm = uy[rxm], uz_xm = uz[rxm];
-            const Cx<R> ux_ym = ux[rym], uy_xp_ym = uy[rxp_ym], uz_ym = uz[rym];
-            const Cx<R> ux_xm_zp = uxp[rxm], uy_ym_zp = uyp[rym];
+            if constexpr (!Pair<R, 1>::kBeside) {
+                uy_xm = su.get(rxm, 1);
+                uz_xm = sw.get(rxm, 0);
+                ux_ym = su.get(rym, 0);
+                uz_ym = sw.get(rym, 0);
+            }
+            const Cx<R> ux_xm_yp = su.get(rxm_yp, 0), uy_xp_ym = su.get(rxp_ym, 1);
+            const Cx<R> ux_xm_zp = sup.get(rxm, 0), uy_ym_zp = sup.get(rym, 1);
             const R fxy_xm = plaq_sin(ux_xm, Uc[1], ux_xm_yp, uy_xm) * inv_dx2;
             const R fxy_ym = plaq_sin(ux_ym, uy_xp_ym, Uc[0], uy_ym) * inv_dx2;
             const R fxz_xm = plaq_sin(ux_xm, Uc[2], ux_xm_zp, uz_xm) * inv_dx2;
@@ -770,14 +784,13 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
 
         // ---- 2. planes z+1 and z+2 into LDS: phi and U_z of plane z+1 (U_z held
         //         since the phase before), x and y links of plane z+2
-        sh.Phi[b ^ 1][ro] = phi_p;
-        if (has_halo) sh.Phi[b ^ 1][rh] = q.hphi;
+        sh.W[b ^ 1].set(ro, Up[2], phi_p);
+        if (has_halo) sh.W[b ^ 1].set(rh, huz, q.hphi);
         if (!more) break;
         Cx<R> u2[3];
         if (has_halo) {
-            sh.Uz[b ^ 1][rh] = huz;
             links(dx, q.ha, u2);
-            for (int d = 0; d < 2; ++d) sh.Uxy[s2][d][rh] = u2[d];
+            sh.U[s2].set(rh, u2[0], u2[1]);
             huz = u2[2];
             if constexpr (MEAS)
                 for (int d = 0; d < 3; ++d) {
@@ -787,9 +800,8 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
             if constexpr (GLDS)
                 if (halo_e) mx->E[b ^ 1][hEc][rh] = halo_ex ? q.he.r : q.he.i;
         }
-        sh.Uz[b ^ 1][ro] = Up[2];
         links(dx, q.a, u2);
-        for (int d = 0; d < 2; ++d) sh.Uxy[s2][d][ro] = u2[d];
+        sh.U[s2].set(ro, u2[0], u2[1]);
         if constexpr (MEAS)
             for (int d = 0; d < 3; ++d) mx->A[b ^ 1][d][ro] = Ap[d];
         if constexpr (GLDS) {
@@ -833,9 +845,9 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
         // own Y_x, Y_y of plane z1 complete the windings of the chunk's last plane
         __syncthreads();
         const int b = (z1 - 1 - z0) & 1, rxp = ro + 1, ryp = ro + RW;
-        const Cx<R>* sPhi = sh.Phi[b ^ 1];
-        const float yx_n = phase(phi_p, Up[0], sPhi[rxp], Ap[0]);
-        const float yy_n = phase(phi_p, Up[1], sPhi[ryp], Ap[1]);
+        const auto& sw = sh.W[b ^ 1];
+        const float yx_n = phase(phi_p, Up[0], sw.get(rxp, 1), Ap[0]);
+        const float yy_n = phase(phi_p, Up[1], sw.get(ryp, 1), Ap[1]);
         if (active) {
             const auto& sYb = mx->Y[b];
             wabs += abs(winding_of(yx_b, sYb[1][rxp], sYb[0][ryp], yy_b, th_b[0])) +
