@@ -206,7 +206,7 @@ int ah_get_winding(ah_handle* h, int8_t* host_w);
 /* ------------------------------------------------------ step kernel choice */
 #define AH_KERNEL_AUTO 0 /* tiled kernel for the compact action, site kernel otherwise; with the tiling left
                           * automatic too, two plain steps that follow each other run as one pass
-                          * (AH_KERNEL_TILE2) where that is faster (N > 64), except while the stream is
+                          * (AH_KERNEL_TILE2) where that is faster (FP32; FP64 with N > 64), except while the stream is
                           * being captured; ah_get_step_config reports the one-step tiling */
 #define AH_KERNEL_SITE 1 /* one thread per site, every neighbour read from global memory */
 #define AH_KERNEL_TILE 2 /* z-marching tiles with links shared through LDS (compact action only) */

@@ -581,23 +581,23 @@ int auto_zchunk(int kernel, int precision, int N, int tx, int ty, bool measured)
     return best_zc;
 }
 
-// Two-step passes of an automatic configuration: from N = 65 on, where they
-// are the faster way to take two plain steps in both precisions (MI355X, us
-// per step, two-step / single: FP32 75^3 13.5 / 13.6, 96^3 17.3 / 20.7, 200^3
-// 122 / 159, 512^3 1468 / 2002; FP64 75^3 25.8 / 27.2, 200^3 300 / 329, 512^3
-// 3783 / 4450; but 64^3 FP32 8.1 / 7.6, FP64 15.0 / 13.9: the pass's longer
-// start is not paid for by two planes a chunk).  FP64 on 32 x 8 (64 x 4
-// spills); FP32 on 64 x 8 or 32 x 8, whichever the estimate says is faster (a
-// plane takes a workgroup alone on its CU 2.85 and 1.9 us).
+// Two-step passes of an automatic configuration: where they are the faster way
+// to take two plain steps, FP32 at every size, FP64 from N = 65 on (MI355X, us
+// per step, two-step / single: FP32 24^3 4.9 / 5.6, 48^3 5.8 / 6.2, 64^3 6.7 /
+// 7.0, 192^3 78 / 116, 512^3 1283 / 1998; FP64 32^3 9.5 / 8.7, 64^3 13.2 / 12.0:
+// its pass's longer start is not paid for by two planes a chunk; 75^3 25.8 /
+// 27.2, 512^3 3610 / 4490).  FP64 on 32 x 8 (64 x 4 spills); FP32 on 64 x 8 or
+// 32 x 8, whichever the estimate says is faster (a plane takes a workgroup
+// alone on its CU 1.5 times as long on 64 x 8).
 bool default_two(int precision, int N, TileConfig* two)
 {
     *two = TileConfig{0, 0, 0};
-    if (N <= 64) return false;
+    if (precision == AH_FP64 && N <= 64) return false;
     double best = 0.0;
     for (const int tx : {64, 32}) {
         if (!tile2_supported(precision, tx, 8)) continue;
         const int zc = auto_zchunk(AH_KERNEL_TILE2, precision, N, tx, 8, false);
-        const double t = launch_estimate(AH_KERNEL_TILE2, precision, N, tx, 8, false, zc, nullptr) * (tx == 64 ? 2.85 : 1.9);
+        const double t = launch_estimate(AH_KERNEL_TILE2, precision, N, tx, 8, false, zc, nullptr) * (tx == 64 ? 1.5 : 1.0);
         if (two->zchunk == 0 || t < best) {
             best = t;
             *two = TileConfig{tx, 8, zc};
