@@ -23,7 +23,7 @@
 // us per step: 512^3 FP32 64 x 8 1283, FP64 32 x 8 3610.  Stage 2 one plane
 // behind stage 1 with a barrier behind each of them (half the LDS, two
 // barriers a plane) took 1677 and 4420 where this form took 1468 and 3774,
-// before the values in LDS were paired (Pair); stage 2 before stage 1 within a
+// before the values in LDS were paired (Pair, ah_stencil.h); stage 2 before stage 1 within a
 // phase 1513 and 4103.
 //
 // Stage 1 reads Pi and E of snapshot n on the ring too, which the
@@ -103,7 +103,7 @@ __device__ __forceinline__ SiteNbr<R> gather_nbr(int c, const Pair<R, S>& u, con
 template <int TX, int TY>
 constexpr int kStep2Threads = Geom2<TX, TY>::NTH;
 // Waves per SIMD the register allocation leaves room for: FP64 two (it takes
-// 253 registers on 32 x 8); FP32 three (143 registers: one 11-wave 64 x 8 or
+// 255 registers on 32 x 8); FP32 three (149 registers: one 11-wave 64 x 8 or
 // 7-wave 64 x 4, or two 6-wave 32 x 8 workgroups per CU).
 template <typename R, int TX, int TY>
 constexpr int kStep2MinWaves = sizeof(R) == 8 ? 2 : 3;
@@ -294,7 +294,7 @@ __device__ __forceinline__ void march2_role(Shared2<R, TX, TY>& sh, const Step2A
         constexpr bool S1 = decltype(s1)::value, S2 = decltype(s2)::value && TILE;
         const bool more = p < z1;  // there is a stage 1 in the next phase
         // the LDS addresses anew in each phase, rather than some thirty of
-        // them held in registers through the march (143 registers, not spills)
+        // them held in registers through the march (149 registers, not spills)
         asm volatile("" : "+v"(c1), "+v"(c2));
         if (S1 && more && p > z0 - 1) prefetch(p);
 

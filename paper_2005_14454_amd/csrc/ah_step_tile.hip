@@ -22,9 +22,9 @@
 // What bounds it: memory for the plain march of a large lattice (512^3 on
 // MI355X: FP32 128 x 4 2.00 ms a step, 5.4 TB/s of algorithmic bytes; FP64
 // 64 x 8 4.49 ms, 4.8 TB/s; a copy reaches 5.5 TB/s); the latency of a chunk's
-// first loads and barriers for a small one (64^3 FP64, 2-plane chunks: 13.0
+// first loads and barriers for a small one (64^3 FP64, 2-plane chunks: 12.0
 // us); instruction issue and latency for the measured march (512^3: FP32 3.4
-// ms, FP64 6.2 ms).  Links in three slots, so that one barrier a plane is
+// ms, FP64 6.0 ms).  Links in three slots, so that one barrier a plane is
 // enough, and every load of a chunk's start issued before its first barrier
 // took the measured march from 3.74 and 7.3 ms and the 64^3 step from 16.4 us
 // (two barriers a plane, three rounds of loads at the start of a chunk).
@@ -893,7 +893,7 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
 // Waves per SIMD the compiler must leave room for.  The plain FP32 march
 // fits in 128 registers, i.e. four waves per SIMD: two 512-thread workgroups
 // per CU, so one can load while the other waits at a barrier.  FP64 fits two
-// (its measured march takes 255 registers).  The FP32 measured march takes 174
+// (its measured march takes 255 registers).  The FP32 measured march takes 195
 // and runs two; held to 168 for three it spills 8, and runs slower (512^3 3583
 // us against 3400, 128^3 73 against 65).
 template <typename R, bool MEAS>
