@@ -758,8 +758,7 @@ int ah_pool_create(size_t hbm_budget, int32_t max_slots, void* hip_stream, ah_po
 // Lattices also take two-step passes wherever neither of two snapshots is
 // due (two), with z-chunks by what is in the pool (two_step_chunks), on the tuned
 // two-step tile shape, else 64 x 8 for FP32 and 32 x 8 for FP64; FP64 ones
-// from N = 65 on (default_two; in a pool the pass does not lose below that
-// for FP32, as other lattices fill the chip).
+// from N = 65 on, as a lattice alone (default_two).
 // The pool supplies much of the parallelism that short z-chunks buy a
 // lattice run alone; 16 planes keep enough work items for ensembles of small
 // lattices (measured on MI355X: 128 lattices of N in {32, 48, 64} run 11%

@@ -1,8 +1,9 @@
-"""An automatic step configuration takes two plain steps in one pass on
-lattices of more than 64 sites a side.  The rule against the general path,
-explicit single steps: bitwise the same fields on both sides of the
-threshold and where the pass's FP32 tile changes from 32 x 8 to 64 x 8, for
-even and odd runs, with measured steps between them, alone and in a pool.
+"""An automatic step configuration takes two plain steps in one pass: FP32 at
+every size, FP64 above 64 sites a side.  The rule against the general path,
+explicit single steps: bitwise the same fields on the smallest lattices, on
+both sides of the threshold and where the pass's FP32 tile changes from 32 x 8
+to 64 x 8, for even and odd runs, with measured steps between them, alone and
+in a pool.
 """
 import numpy as np
 import pytest
@@ -43,7 +44,7 @@ def _run(ah, gp, st, single, pieces):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
-@pytest.mark.parametrize("N", [64, 65, 75, 97, 110, 131])
+@pytest.mark.parametrize("N", [4, 5, 24, 47, 64, 65, 75, 97, 110, 131])
 def test_automatic_passes_equal_single_steps(ah, precision, N):
     gp = _params(ah, N, precision)
     st = _state(N, precision)
@@ -55,7 +56,7 @@ def test_automatic_passes_equal_single_steps(ah, precision, N):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
-@pytest.mark.parametrize("N", [66, 112])
+@pytest.mark.parametrize("N", [9, 66, 112])
 def test_automatic_evolve_equals_single_steps(ah, precision, N):
     gp = _params(ah, N, precision)
     st = _state(N, precision)
