@@ -174,7 +174,16 @@ int ah_gather_noalloc(ah_handle* h, const int64_t* sites, int64_t count, double*
 int ah_get_step(const ah_handle* h, int64_t* step);
 
 /* Advance nsteps (>= 0) full leapfrog steps (kick + drift).  Asynchronous.
- * AH_E_STATE before ah_init/ah_set_state. */
+ * AH_E_STATE before ah_init/ah_set_state.
+ *
+ * May be recorded into a HIP graph (hip_stream being captured).  The graph
+ * holds the buffers that the snapshot is in and goes to, and the coefficients
+ * of the steps recorded; ah_get_step does not count its replays.  An even
+ * number of steps can be replayed, and goes on to work on the current snapshot
+ * through further ah_step calls of an even number of steps, and through ah_init
+ * and ah_set_state if the steps taken between one of them and the recording
+ * were even in number.  Measured steps (ah_step_measured), an odd number of
+ * steps and AH_KERNEL_TILE2 chosen by hand move the snapshot to other buffers. */
 int ah_step(ah_handle* h, int64_t nsteps);
 
 /* Advance nsteps steps; the snapshots n with n % measure_every == 0 among
@@ -206,8 +215,9 @@ int ah_get_winding(ah_handle* h, int8_t* host_w);
 /* ------------------------------------------------------ step kernel choice */
 #define AH_KERNEL_AUTO 0 /* tiled kernel for the compact action, site kernel otherwise; with the tiling left
                           * automatic too, two plain steps that follow each other run as one pass
-                          * (AH_KERNEL_TILE2) where that is faster (FP32; FP64 with N > 64), except while the stream is
-                          * being captured; ah_get_step_config reports the one-step tiling */
+                          * (AH_KERNEL_TILE2) where that is faster (FP32; FP64 with N > 64; or as the tuning table
+                          * says), and only four as two passes once steps have been recorded into a HIP graph (see
+                          * ah_step); ah_get_step_config reports the one-step tiling, or the tuning entry */
 #define AH_KERNEL_SITE 1 /* one thread per site, every neighbour read from global memory */
 #define AH_KERNEL_TILE 2 /* z-marching tiles with links shared through LDS (compact action only) */
 #define AH_KERNEL_TILE2 3 /* as AH_KERNEL_TILE, with two steps per pass over the fields wherever two plain

@@ -50,6 +50,12 @@ struct ah_handle {
     size_t ev_used = 0;
     ah_step_config cfg{AH_KERNEL_AUTO, 0, 0, 0};
     TileConfig two{};  // tiling of the two-step passes an automatic configuration takes (zchunk 0: none)
+    // Whether work of this handle has been recorded into a graph (note_capture),
+    // and whether the two-step passes of automatic configurations have, all in
+    // all, exchanged the buffer pairs, which single steps in their place would
+    // have left where they were.
+    bool captured = false;
+    int swapped = 0;
     int64_t measured_launches = 0;  // timed launches that also formed diagnostics
     std::vector<char> ev_measured;  // per event pair: 1 if that launch formed diagnostics
     std::vector<char> ev_steps;     // per event pair: steps the launch advanced (1 or 2)
@@ -728,7 +734,11 @@ int resolve_config(const ah_params& p, const ah_step_config& in, ah_step_config*
     if (in.kernel == AH_KERNEL_AUTO && in.tile_x == 0 && in.tile_y == 0 && in.zchunk == 0 &&
         p.gauge_action == AH_COMPACT) {
         ah_step_config tuned;
-        if (tuned_config(p, &tuned)) return resolve_step_config(p, tuned, out, why);
+        if (tuned_config(p, &tuned)) {
+            const int rc = resolve_step_config(p, tuned, out, why);
+            if (rc == AH_OK && out->kernel == AH_KERNEL_TILE2) *two = TileConfig{out->tile_x, out->tile_y, out->zchunk};
+            return rc;
+        }
         (void)default_two(p.precision, p.N, two);
     }
     return resolve_step_config(p, in, out, why);
@@ -860,6 +870,31 @@ hipError_t do_step(ah_handle* h)
     return hipSuccess;
 }
 
+// A graph holds the addresses of the buffers that its steps read and wrote
+// when they were recorded.  Whoever replays it between calls counts on an even
+// number of plain steps to leave the snapshot in those buffers, and on ah_init
+// and ah_set_state to put a new one there.  Single steps do; a two-step pass
+// exchanges both pairs.  So a handle remembers that work of it was recorded:
+// from then on the passes of an automatic configuration come in twos
+// (plain_steps), and a new snapshot goes to the pair that single steps in the
+// place of the passes before would have it in (first_pair).
+void note_capture(ah_handle* h)
+{
+    if (h->captured) return;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &st) != hipSuccess) {
+        (void)hipGetLastError();  // the launch will say what is wrong
+        return;
+    }
+    h->captured = st != hipStreamCaptureStatusNone;
+}
+// The buffers that a new snapshot goes to.
+void first_pair(ah_handle* h)
+{
+    if (!h->captured) h->swapped = 0;
+    h->cur = h->curm = h->swapped;
+}
+
 // Two steps in one pass on tiling tc: reads snapshot n from the
 // current buffers and writes snapshot n+2 into the other phi/A and Pi/E ones.
 template <typename R>
@@ -889,31 +924,25 @@ hipError_t do_step2(ah_handle* h, const TileConfig& tc)
 
 // nsteps plain steps: two-step passes while at least two remain when the
 // handle's kernel is AH_KERNEL_TILE2 or its automatic configuration takes
-// them, single steps otherwise.
-//
-// Into a stream that is being captured an automatic configuration records
-// single steps: an even number of them leaves every buffer where it was, so
-// that the graph can be replayed, where a two-step pass swaps them all.
+// them, single steps otherwise.  An automatic configuration takes an even
+// number of passes a call once work of the handle has been recorded into a
+// graph: every buffer is then where single steps would have left it.
 hipError_t plain_steps(ah_handle* h, int64_t nsteps)
 {
+    note_capture(h);
+    const bool automatic = h->two.zchunk > 0;
     TileConfig tc = h->two;
-    if (h->cfg.kernel == AH_KERNEL_TILE2) {
-        tc = TileConfig{h->cfg.tile_x, h->cfg.tile_y, h->cfg.zchunk};
-    } else if (tc.zchunk > 0 && nsteps >= 2) {
-        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        const hipError_t e = hipStreamIsCapturing(h->stream, &st);
-        if (e != hipSuccess) (void)hipGetLastError();  // the launch will say what is wrong
-        if (e != hipSuccess || st != hipStreamCaptureStatusNone) tc.zchunk = 0;
+    if (!automatic && h->cfg.kernel == AH_KERNEL_TILE2) tc = TileConfig{h->cfg.tile_x, h->cfg.tile_y, h->cfg.zchunk};
+    int64_t passes = tc.zchunk > 0 ? nsteps / 2 : 0;
+    if (automatic && h->captured) passes -= passes % 2;
+    const int64_t singles = nsteps - 2 * passes;
+    for (int64_t k = 0; k < passes; ++k) {
+        const hipError_t e = h->p.precision == AH_FP64 ? do_step2<double>(h, tc) : do_step2<float>(h, tc);
+        if (e != hipSuccess) return e;
+        if (automatic) h->swapped ^= 1;
     }
-    while (nsteps > 0) {
-        hipError_t e;
-        if (tc.zchunk > 0 && nsteps >= 2) {
-            e = h->p.precision == AH_FP64 ? do_step2<double>(h, tc) : do_step2<float>(h, tc);
-            nsteps -= 2;
-        } else {
-            e = h->p.precision == AH_FP64 ? do_step<double>(h) : do_step<float>(h);
-            nsteps -= 1;
-        }
+    for (int64_t k = 0; k < singles; ++k) {
+        const hipError_t e = h->p.precision == AH_FP64 ? do_step<double>(h) : do_step<float>(h);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -1075,12 +1104,12 @@ int ah_init(ah_handle* h, uint64_t seed)
     return no_throw([&]() -> int {
         if (!h) return AH_E_INVAL;
         DeviceGuard g(h->device);
-        h->cur = 0;
-        h->curm = 0;
+        note_capture(h);
+        first_pair(h);
         h->step = 0;
         hipError_t e = h->p.precision == AH_FP64
-                           ? launch_init<double>(fields_of<double>(h, 0), h->p.N, h->P, h->p.sigma, seed, h->stream)
-                           : launch_init<float>(fields_of<float>(h, 0), h->p.N, h->P, h->p.sigma, seed, h->stream);
+                           ? launch_init<double>(fields_of<double>(h, h->cur), h->p.N, h->P, h->p.sigma, seed, h->stream)
+                           : launch_init<float>(fields_of<float>(h, h->cur), h->p.N, h->P, h->p.sigma, seed, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "ah_init launch");
         h->ready = true;
         return AH_OK;
@@ -1094,14 +1123,14 @@ int ah_set_state(ah_handle* h, const double* host_soa, int64_t step)
         DeviceGuard g(h->device);
         hipError_t e = hipStreamSynchronize(h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "ah_set_state sync");
-        h->cur = 0;
-        h->curm = 0;
+        first_pair(h);
         IoStage* st = nullptr;
         e = io_stage(h, 10 * (size_t)h->V * h->real_bytes, &st);
         const size_t fb = field_bytes(h->p);
+        void *pp = h->pp[h->cur][0], *mom = h->mom[h->curm][0];
         if (e == hipSuccess)
-            e = h->real_bytes == 8 ? state_upload<double>(h->pp[0][0], h->mom[0][0], fb, host_soa, h->p.N, h->P, *st, h->stream)
-                                   : state_upload<float>(h->pp[0][0], h->mom[0][0], fb, host_soa, h->p.N, h->P, *st, h->stream);
+            e = h->real_bytes == 8 ? state_upload<double>(pp, mom, fb, host_soa, h->p.N, h->P, *st, h->stream)
+                                   : state_upload<float>(pp, mom, fb, host_soa, h->p.N, h->P, *st, h->stream);
         if (e != hipSuccess) return hip_fail(h, e, "ah_set_state copy");
         h->step = step;
         h->ready = true;
