@@ -331,6 +331,10 @@ template <class Work>
 hipError_t split_lanes(const IoStage& st, int64_t n, int most, size_t host_bytes, hipStream_t s, Work work)
 {
     constexpr size_t least = 64u << 10;  // a slot; at least a row of the longest side where there is one lane
+    // hipStreamPerThread is another stream in each thread: a helper's launches
+    // would be ordered neither behind the caller's work nor ahead of its
+    // synchronisation, so the caller makes them all
+    if (s == hipStreamPerThread) most = 1;
     const size_t lanes = std::min(1 + (host_bytes >> 24), std::max(st.bytes / (kIoSlots * least), (size_t)1));
     const int T = (int)std::min<int64_t>(most, std::min<int64_t>(n, (int64_t)lanes));
     void* dev = nullptr;
