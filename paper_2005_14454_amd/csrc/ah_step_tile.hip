@@ -23,7 +23,7 @@
 // MI355X: FP32 128 x 4 2.00 ms a step, 5.4 TB/s of algorithmic bytes; FP64
 // 64 x 8 4.49 ms, 4.8 TB/s; a copy reaches 5.5 TB/s); the latency of a chunk's
 // first loads and barriers for a small one (64^3 FP64, 2-plane chunks: 12.0
-// us); instruction issue and latency for the measured march (512^3: FP32 3.4
+// us); instruction issue and latency for the measured march (512^3: FP32 3.5
 // ms, FP64 6.0 ms).  Links in three slots, so that one barrier a plane is
 // enough, and every load of a chunk's start issued before its first barrier
 // took the measured march from 3.74 and 7.3 ms and the 64^3 step from 16.4 us
@@ -192,49 +192,26 @@ __device__ inline double turns_of(double th)
     return fabs(q - r) < 0.49 && fabs(q) < 1e12 ? r : rint(th / two_pi);
 }
 
-// Angles dx (((a + b) - c) - d) of a site's plaquettes as their windings take
-// them: FP64
-// lattices the angle itself, FP32 ones the wrapped angle in FP32.
-//
-// In FP32 the angle of |A| dx < 100 is within 1.2e-4 of its FP64 value (five
-// roundings of at most 400), 2e-5 turns, so unless it lies within 1e-4 turns
-// of a half turn the multiple that wraps it is the FP64 one; the winding only
-// needs the wrapped angle to well below pi.  Otherwise FP64 decides.
-__device__ inline void plaq_angles(double dx, double, const double (&q)[3][4], double (&th)[3])
+// Angles dx (((a + b) - c) - d) of a site's plaquettes, in FP64 from the stored
+// A of either precision.  FP32 lattices could take most of them in FP32 (MI355X,
+// measured step of 512^3 3.38 ms rather than 3.46), at fewer bits than the
+// diagnostics promise.
+template <typename R>
+__device__ inline void plaq_angles(double dx, const R (&q)[3][4], double (&th)[3])
 {
-    for (int k = 0; k < 3; ++k) th[k] = dx * (((q[k][0] + q[k][1]) - q[k][2]) - q[k][3]);
-}
-__device__ inline void plaq_angles(double dx, float dxf, const float (&q)[3][4], float (&th)[3])
-{
-    bool ok[3];
-    for (int k = 0; k < 3; ++k) {
-        const float big = fmaxf(fmaxf(fabsf(q[k][0]), fabsf(q[k][1])), fmaxf(fabsf(q[k][2]), fabsf(q[k][3])));
-        th[k] = dxf * (((q[k][0] + q[k][1]) - q[k][2]) - q[k][3]);
-        const float t = th[k] * 0.15915494309189535f;
-        const float r = __builtin_rintf(t);
-        th[k] = fm(-6.2831853071795865f, r, th[k]);
-        ok[k] = fabsf(t - r) < 0.4999f && dxf * big < 100.f;
-    }
-    if (!(ok[0] && ok[1] && ok[2]))
-        for (int k = 0; k < 3; ++k)
-            if (!ok[k]) {
-                const double t = dx * ((((double)q[k][0] + (double)q[k][1]) - (double)q[k][2]) - (double)q[k][3]);
-                th[k] = (float)(t - 6.283185307179586 * turns_of(t));
-            }
+    for (int k = 0; k < 3; ++k)
+        th[k] = dx * ((((double)q[k][0] + (double)q[k][1]) - (double)q[k][2]) - (double)q[k][3]);
 }
 
-// Winding of a plaquette from its four link phases and its angle (plaq_angles):
-// their sum is within ~1e-3 of a multiple of 2 pi.
+// Winding of a plaquette from its four link phases and its angle (FP64): their
+// sum, once the angle is wrapped, is within 4e-5 + 1e-6 |dx A| of a multiple of
+// 2 pi (four phases, link_phases_f; |dx A| up to 1e5 in FP32, FP64 beyond).
 __device__ inline int winding_of(float y1, float y2, float y3, float y4, double th)
 {
     const double two_pi = 6.283185307179586;
     const double thw = th - two_pi * turns_of(th);
     const double sum = ((((double)y1 + (double)y2) - (double)y3) - (double)y4) + thw;
     return (int)rint(sum * (1.0 / two_pi));
-}
-__device__ inline int winding_of(float y1, float y2, float y3, float y4, float thw)
-{
-    return (int)__builtin_rintf(((((y1 + y2) - y3) - y4) + thw) * 0.15915494309189535f);
 }
 
 // 1 - cos(Theta) of a plaquette from its four links, without cancellation
@@ -421,7 +398,7 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
     // z+1, so they are completed one plane later from the own link phases (_b)
     // and the plaquette angles of plane z
     float yx_b = 0.f, yy_b = 0.f, yz_b = 0.f;
-    R th_b[3] = {0, 0, 0};  // (x, y), (x, z), (y, z)
+    double th_b[3] = {0.0, 0.0, 0.0};  // (x, y), (x, z), (y, z)
     // link phase of a link U = exp(-i dx a) between phi values ph and pn
     auto phase = [&](Cx<R> ph, Cx<R> U, Cx<R> pn, R av) -> float {
         if constexpr (sizeof(R) == 8)
@@ -663,7 +640,7 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
                 const R q4[3][4] = {{Ac[0], sA[1][rxp], sA[0][ryp], Ac[1]},
                                     {Ac[0], sA[2][rxp], Ap[0], Ac[2]},
                                     {Ac[1], sA[2][ryp], Ap[1], Ac[2]}};
-                plaq_angles(ma.dx, dx, q4, th_b);
+                plaq_angles(ma.dx, q4, th_b);
             }
             // plaquettes at x (F_ij^x, i<j)
             const Cx<R> uy_xp = su.get(rxp, 1), ux_yp = su.get(ryp, 0);
@@ -893,7 +870,7 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
 // Waves per SIMD the compiler must leave room for.  The plain FP32 march
 // fits in 128 registers, i.e. four waves per SIMD: two 512-thread workgroups
 // per CU, so one can load while the other waits at a barrier.  FP64 fits two
-// (its measured march takes 255 registers).  The FP32 measured march takes 195
+// (its measured march takes 255 registers).  The FP32 measured march takes 198
 // and runs two; held to 168 for three it spills 8, and runs slower (512^3 3583
 // us against 3400, 128^3 73 against 65).
 template <typename R, bool MEAS>
