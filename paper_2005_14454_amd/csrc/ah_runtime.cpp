@@ -618,19 +618,30 @@ bool default_two(int precision, int N, TileConfig* two)
 
 // Any tile shape computes the same fields bit for bit, so the measured march
 // may run another shape than the plain step: the fastest measured march
-// (measured_tile: 32 x 8), with its own automatic z-chunk, but no shorter than
-// the step's up to 16 planes (a pool's floor of 16 then holds for its
-// measured node too).  A step's longer z-chunk is not taken over: two-step
-// 32 x 8 FP64 passes of 128^3 run best on 32 planes, its measured march on 16.  The diagnostics records are summed in tile order, so a
-// lattice measured with the same tiling (alone or in a pool) gets the same
-// bits.
+// (measured_tile: 32 x 8).  A one-step march on that shape lends it its z-chunk;
+// on another shape it leaves it its own automatic one, no shorter than the
+// step's up to 16 planes (a pool's floor of 16 then holds for its measured
+// node too).  A two-step pass lends it its z-chunk only where the estimate
+// finds that as good: one of its workgroups fills a CU, so its z-chunks are
+// long, and on them the measured march has one workgroup on a CU where two fit
+// (MI355X, ah_measure in us on the pass's z-chunk / on its own: FP64 96^3 71.5 /
+// 59.7, 128^3 131.6 / 102.1, 256^3 902 / 632, FP32 96^3 57.9 / 46.0; but 512^3
+// FP64, where the estimates are 0.2% apart, 4820 / 4970).  The diagnostics
+// records are summed in tile order, so a lattice measured with the same tiling
+// (alone or in a pool) gets the same bits.
 TileConfig measured_tiling(const ah_params& p, const ah_step_config& cfg)
 {
     int tx = cfg.tile_x, ty = cfg.tile_y;
-    const bool tiled = cfg.kernel == AH_KERNEL_TILE || cfg.kernel == AH_KERNEL_TILE2;
-    if (!measured_tile(&tx, &ty) && tiled) return TileConfig{tx, ty, cfg.zchunk};
+    const bool march = cfg.kernel == AH_KERNEL_TILE;
+    const bool other = measured_tile(&tx, &ty);
+    if (!other && march) return TileConfig{tx, ty, cfg.zchunk};
     int zc = auto_zchunk(AH_KERNEL_TILE, p.precision, p.N, tx, ty, true);
-    if (tiled) zc = std::min(std::max(zc, std::min(cfg.zchunk, 16)), p.N);
+    if (march) {
+        zc = std::min(std::max(zc, std::min(cfg.zchunk, 16)), p.N);
+    } else if (!other && cfg.kernel == AH_KERNEL_TILE2) {
+        auto time = [&](int c) { return launch_estimate(AH_KERNEL_TILE, p.precision, p.N, tx, ty, true, c, nullptr); };
+        if (time(cfg.zchunk) <= 1.01 * time(zc)) zc = cfg.zchunk;
+    }
     return TileConfig{tx, ty, zc};
 }
 
