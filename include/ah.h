@@ -326,7 +326,8 @@ typedef struct ah_pool_info {
     int32_t active;         /* lattices admitted and not yet collected */
     int32_t max_slots;
     int64_t graph_launches; /* steps issued so far */
-    int64_t graph_captures; /* times the nodes of the per-step graphs were laid out */
+    int64_t graph_captures; /* times the nodes of the per-step graphs were laid out (ah_pool_graph_counts
+                             * has the number of graphs captured as well) */
 } ah_pool_info;
 
 /* Create a pool with a device arena of hbm_budget bytes (hipMalloc'd and
@@ -393,6 +394,13 @@ int ah_pool_results(ah_pool* pool, int64_t id, ah_measurement* series, int32_t c
 
 /* Occupancy figures. */
 int ah_pool_stats(const ah_pool* pool, ah_pool_info* info);
+
+/* Times the nodes of the per-step graphs were laid out (as graph_captures of
+ * ah_pool_info), and graphs captured and instantiated: one for each set of
+ * nodes that had work in a replay, kept for later replays with the same set
+ * until the nodes are laid out anew or 64 are held (all are then given up).
+ * Either pointer may be NULL.  Host only. */
+int ah_pool_graph_counts(const ah_pool* pool, int64_t* layouts, int64_t* captures);
 
 /* Wait for all work enqueued on the pool stream. */
 int ah_pool_synchronize(ah_pool* pool);

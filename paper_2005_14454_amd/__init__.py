@@ -457,5 +457,12 @@ class Pool:
         _lib.check(self._lib.ah_pool_stats(self._h, ctypes.byref(info)), what="ah_pool_stats")
         return {k: getattr(info, k) for k, _ in _lib.ah_pool_info._fields_}
 
+    def graph_counts(self):
+        """(times the graphs' nodes were laid out, graphs captured) so far."""
+        a, b = ctypes.c_int64(), ctypes.c_int64()
+        _lib.check(self._lib.ah_pool_graph_counts(self._h, ctypes.byref(a), ctypes.byref(b)),
+                   what="ah_pool_graph_counts")
+        return a.value, b.value
+
     def synchronize(self):
         self._call(self._lib.ah_pool_synchronize, what="ah_pool_synchronize")

@@ -131,6 +131,7 @@ def load():
         "ah_pool_get_state": ([vp, i64, P(ctypes.c_double), P(i64)], ctypes.c_int),
         "ah_pool_results": ([vp, i64, P(ah_measurement), ctypes.c_int32, P(ctypes.c_int32)], ctypes.c_int),
         "ah_pool_stats": ([vp, P(ah_pool_info)], ctypes.c_int),
+        "ah_pool_graph_counts": ([vp, P(i64), P(i64)], ctypes.c_int),
         "ah_pool_synchronize": ([vp], ctypes.c_int),
         "ah_pool_last_error": ([vp], ctypes.c_char_p),
         "ah_pool_destroy": ([vp], ctypes.c_int),

@@ -184,7 +184,8 @@ struct ah_pool {
     bool laid_out = false;                 // the regions and the lists in them are uploaded
     std::map<uint64_t, StepGraph> graphs;  // by the nodes in them: bit n the n-th of groups
     std::vector<ActiveLattice> active;     // as of the last rebuild
-    int64_t graph_captures = 0;
+    int64_t layouts = 0;   // times the nodes were laid out
+    int64_t captures = 0;  // graphs captured and instantiated
     bool dirty = true;
     int64_t graph_launches = 0;
     std::string err;
@@ -608,7 +609,7 @@ int rebuild(ah_pool* P)
                              bit[GroupKey{2, s.p.precision, s.meas.tx, s.meas.ty}],
                              s.two.zchunk > 0 ? bit[GroupKey{3, s.p.precision, s.two.tx, s.two.ty}] : 0});
     }
-    if (!fits) ++P->graph_captures;
+    if (!fits) ++P->layouts;
     P->laid_out = true;
     P->dirty = false;
     return AH_OK;
@@ -689,6 +690,7 @@ int step_graph(ah_pool* P, uint64_t nodes, hipGraphExec_t* exec)
         return phip(P, le != hipSuccess ? le : e, "pool graph capture");
     }
     P->graphs.emplace(nodes, g);
+    ++P->captures;
     *exec = g.exec;
     return AH_OK;
 }
@@ -1120,7 +1122,15 @@ int ah_pool_stats(const ah_pool* P, ah_pool_info* info)
     info->largest_free = largest_free(P);
     info->max_slots = (int32_t)P->slots.size();
     info->graph_launches = P->graph_launches;
-    info->graph_captures = P->graph_captures;
+    info->graph_captures = P->layouts;
+    return AH_OK;
+}
+
+int ah_pool_graph_counts(const ah_pool* P, int64_t* layouts, int64_t* captures)
+{
+    if (!P) return AH_E_INVAL;
+    if (layouts) *layouts = P->layouts;
+    if (captures) *captures = P->captures;
     return AH_OK;
 }
 
