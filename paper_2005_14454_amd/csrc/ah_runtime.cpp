@@ -1184,33 +1184,42 @@ int ah_gather(ah_handle* h, const int64_t* sites, int64_t count, double* host_ou
         if (count == 0) return AH_OK;
         DeviceGuard g(h->device);
         // through the staging memory, which the kernel reads the indices from
-        // and writes the values to
+        // and writes the values to: in one piece if they fit, else in pieces,
+        // so that the host packs and unpacks some while others are gathered
+        // (MI355X, 1e5 sites of 8^3 FP64: 505 us, 595 one after the other)
         const size_t rb = h->real_bytes, each = sizeof(int64_t) + 10 * rb;
         IoStage* st = nullptr;
         hipError_t e = io_stage(h, (size_t)count * each, &st);
         void* dev = nullptr;
         if (e == hipSuccess) e = hipHostGetDevicePointer(&dev, st->host, 0);
         if (e != hipSuccess) return hip_fail(h, e, "ah_gather");
-        const int64_t per = (int64_t)(st->bytes / each) / 32 * 32;  // values start on a cache line
-        for (int64_t k = 0; k < count; k += per) {
-            const int64_t n = std::min(per, count - k);
-            std::memcpy(st->host, sites + k, n * sizeof(int64_t));
-            const size_t off = per * sizeof(int64_t);
-            const int64_t* d_sites = (const int64_t*)dev;
-            void* d_out = (char*)dev + off;
-            e = rb == 8 ? launch_gather<double>(fields_of<double>(h, h->cur), d_sites, n, h->p.N, h->P, (double*)d_out,
-                                                h->stream)
-                        : launch_gather<float>(fields_of<float>(h, h->cur), d_sites, n, h->p.N, h->P, (float*)d_out,
-                                               h->stream);
-            if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
-            if (e != hipSuccess) return hip_fail(h, e, "ah_gather");
-            double* dst = host_out + 10 * k;
-            const char* src = st->host + off;
-            if (rb == 8) {
-                std::memcpy(dst, src, 10 * n * 8);
-            } else {
-                for (int64_t q = 0; q < 10 * n; ++q) dst[q] = (double)((const float*)src)[q];
-            }
+        auto fits = [&](size_t bytes) { return (int64_t)(bytes / each) / 32 * 32; };  // values start on a cache line
+        const bool whole = count <= fits(st->bytes);
+        const IoLane l{st->host, (char*)dev, whole ? st->bytes : st->bytes / kIoSlots / 256 * 256, st->ev};
+        const int64_t per = fits(l.slot);
+        const size_t off = per * sizeof(int64_t);
+        e = pieces_out(
+            l, 0, count, per, h->stream,
+            [&](char* slot, int64_t k, int64_t n) {
+                std::memcpy(l.host + (slot - l.dev), sites + k, n * sizeof(int64_t));
+                const int64_t* in = (const int64_t*)slot;
+                return rb == 8 ? launch_gather<double>(fields_of<double>(h, h->cur), in, n, h->p.N, h->P,
+                                                       (double*)(slot + off), h->stream)
+                               : launch_gather<float>(fields_of<float>(h, h->cur), in, n, h->p.N, h->P,
+                                                      (float*)(slot + off), h->stream);
+            },
+            [&](const char* slot, int64_t k, int64_t n) {
+                double* dst = host_out + 10 * k;
+                if (rb == 8) {
+                    std::memcpy(dst, slot + off, 10 * n * 8);
+                } else {
+                    const float* src = (const float*)(slot + off);
+                    for (int64_t q = 0; q < 10 * n; ++q) dst[q] = (double)src[q];
+                }
+            });
+        if (e != hipSuccess) {
+            (void)hipStreamSynchronize(h->stream);  // nothing uses the staging memory once the call has failed
+            return hip_fail(h, e, "ah_gather");
         }
         return AH_OK;
     });
