@@ -342,7 +342,10 @@ hipError_t split_lanes(const IoStage& st, int64_t n, int most, size_t host_bytes
     hipError_t e = hipHostGetDevicePointer(&dev, st.host, 0);
     if (e == hipSuccess) e = hipGetDevice(&device);
     if (e != hipSuccess) return e;
-    const size_t slot = st.bytes / (T * kIoSlots) / 256 * 256;
+    // so little that the link takes a few us for it goes in one piece: each has
+    // a launch and an event (MI355X, windings of 33^3: 38 us in three, 28 in one)
+    const bool whole = T == 1 && host_bytes <= std::min(st.bytes, (size_t)128 << 10);
+    const size_t slot = whole ? st.bytes : st.bytes / (T * kIoSlots) / 256 * 256;
     hipError_t err[kIoThreads] = {};
     auto run = [&](int t) {
         const IoLane l{st.host + t * kIoSlots * slot, (char*)dev + t * kIoSlots * slot, slot, st.ev + t * kIoSlots};

@@ -1,9 +1,10 @@
-"""Gathers through the pinned staging memory at the counts where
+"""Gathers and windings through the pinned staging memory at the counts where
 the number of pieces changes: one piece in the record memory, one in a handle's
 own, several with a full or a ragged last one."""
 import numpy as np
 import pytest
 
+from helpers import both_params
 from inputs import random_state
 
 pytestmark = pytest.mark.gpu
@@ -38,3 +39,21 @@ def test_gather_counts(precision, each):
             with ah.Lattice(gp) as fresh:
                 fresh.set_state(st, 0)
                 assert np.array_equal(fresh.gather(sites), st[:, sites].T), n
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("N", [33, 35, 36, 39])  # 3 N^3 bytes about the record memory's and a piece's
+def test_windings(oracle_mod, precision, N):
+    import paper_2005_14454_amd as ah
+    op, gp = both_params(oracle_mod, N, precision)
+    st = random_state(N, seed=N)
+    if precision == "fp32":
+        st = st.astype(np.float32).astype(np.float64)
+    want = oracle_mod.winding(op, st).astype(np.int8)
+    with ah.Lattice(gp) as lat:
+        lat.set_state(st, 0)
+        assert np.array_equal(lat.winding(), want)
+    with ah.Lattice(gp) as lat:  # the record memory, before a state has made the handle take its own
+        lat.init(1)
+        w = lat.winding()
+        assert np.array_equal(w, oracle_mod.winding(op, lat.get_state()).astype(np.int8))
