@@ -64,11 +64,17 @@ struct Shared2 {
     using G = Geom2<TX, TY>;
     Pair<R, G::S2> u0[3], w0[2];  // links x, y; link z and phi
     Pair<R, G::S1> u1[3], w1[2];
-    // FP64, where they fit: stage 1's Pi, E and A of a tile site for stage 2
-    // two planes later (registers otherwise)
-    static constexpr bool HELD =
-        sizeof(R) == 8 && sizeof(Cx<R>) * 10 * (G::S1 + G::S2) + sizeof(R) * 16 * G::NT <= 160 * 1024;
-    R h[2][8][HELD ? G::NT : 1];
+    // FP64, as many as fit: stage 1's Pi, E and A of a tile site for stage 2 two
+    // planes later (the rest, and FP32's, in registers)
+    static constexpr int kFit = (160 * 1024 - (int)sizeof(Cx<R>) * 10 * (G::S1 + G::S2)) / (2 * (int)sizeof(R) * G::NT);
+    static constexpr int HELD = sizeof(R) == 8 ? (kFit < 8 ? kFit : 8) : 0;
+    R h[2][HELD > 0 ? HELD : 8][HELD > 0 ? G::NT : 1];
+    // FP64 where not all of them fit (64 x 4): U_z and phi of the own column are
+    // read back from the slots that the phase is about to write, where they are
+    // until then, and not carried in registers.  With Pi, E and A in registers
+    // and the column carried as well the pass spilled ten values a plane (MI355X,
+    // us per step: 512^3 6490, 5310 now; 256^3 784, 645; 128^3 105, 86).
+    static constexpr bool LEAN = sizeof(R) == 8 && HELD < 8;
 };
 
 template <typename R>
@@ -193,10 +199,12 @@ __device__ __forceinline__ void march2_role(Shared2<R, TX, TY>& sh, const Step2A
     R pr, pi, e[3];      // Pi, E at plane p
     Cx<R> uo_z = {};     // outer site: U_z of plane p+1
     // ---- stage-2 column state (snapshot n+1 at the tile site)
-    R hr[2][8];              // Pi, E, A of planes p-1, p-2, by parity
+    constexpr int HELD = Shared2<R, TX, TY>::HELD;
+    constexpr bool LEAN = Shared2<R, TX, TY>::LEAN;
+    R hr[2][8];              // Pi, E, A of planes p-1, p-2, by parity: those not held in LDS
     auto h = [&](int b, int k) -> R& {
-        if constexpr (Shared2<R, TX, TY>::HELD)
-            return sh.h[b][k][TILE ? tid : 0];
+        if (k >= 8 - HELD)
+            return sh.h[b][HELD > 0 ? k - (8 - HELD) : 0][TILE && HELD > 0 ? tid : 0];
         else
             return hr[b][k];
     };
@@ -257,7 +265,10 @@ __device__ __forceinline__ void march2_role(Shared2<R, TX, TY>& sh, const Step2A
         // z0-1 into slot 0, U_z of z0-2 (for F^n there) into slot 1
         Cx<R> um2[3], uc[3], up[3];
         links(dx, am2, um2);
-        sh.w0[1].at(c2, 0) = um2[2];
+        if constexpr (LEAN)
+            sh.w0[1].set(c2, um2[2], phm);
+        else
+            sh.w0[1].at(c2, 0) = um2[2];
         uz_m = um2[2];
         links(dx, ac, uc);
         sh.u0[0].set(c2, uc[0], uc[1]);
@@ -299,13 +310,19 @@ __device__ __forceinline__ void march2_role(Shared2<R, TX, TY>& sh, const Step2A
         if (S1 && more && p > z0 - 1) prefetch(p);
 
         const Cx<R> phq = s1phi;  // phi^{n+1} of plane p-1 = q+1
+        if constexpr (LEAN && S2) sh.w1[b ^ 1].get(c1, &vz_m, &chm);
         sh.w1[b ^ 1].set(c1, s1z, s1phi);
         SiteOut<R> o1 = {}, o2 = {};
         Cx<R> u1[3];
         if constexpr (S1) {
             Cx<R> uc[3], upx, upy;
             sh.u0[sa].get(c2, &uc[0], &uc[1]);
-            uc[2] = sh.w0[b].get(c2, 0);
+            if constexpr (LEAN) {
+                sh.w0[b ^ 1].get(c2, &uz_m, &phm);
+                sh.w0[b].get(c2, &uc[2], &phc);
+            } else {
+                uc[2] = sh.w0[b].get(c2, 0);
+            }
             sh.u0[sb].get(c2, &upx, &upy);
             const SiteNbr<R> nb = gather_nbr<W2>(c2, sh.u0[sa], sh.w0[b], sh.u0[sb]);
             o1 = site_update(k0, nb, phm, phc, php, uc, upx, upy, uz_m, fxz_m, fyz_m, pr, pi, e, ac);
