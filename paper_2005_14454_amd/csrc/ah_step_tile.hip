@@ -307,6 +307,7 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
     const R lamh = a.lamh, kappa = a.kappa, deta = a.deta;
     constexpr bool GAUSS = MEAS;                  // Gauss residual in this march
     constexpr bool GLDS = GAUSS && sizeof(R) == 4;  // its -x / -y E through LDS (FP64: loads)
+    constexpr bool EARLY = MEAS || (sizeof(R) == 8 && TX == 32);  // next phase's loads ahead of the barrier
 
     const R inv_dx = R(1) / dx;
     const R inv_dx2 = inv_dx * inv_dx;
@@ -807,11 +808,15 @@ __device__ void march_step(TileShared<R, TX, TY>& sh, MeasShared<R, TX, TY>* mx,
         // Measured march: issued before the barrier, which hides more of their
         // latency.  Plain march, which memory bounds: after it, and with the
         // plane's stores complete, so that the workgroups that share an L2 stay
-        // within a plane of each other and their halo reads hit it.
-        if constexpr (MEAS) prefetch(z + 1, q);
+        // within a plane of each other and their halo reads hit it.  (FP64 32 x
+        // 8, whose narrow tiles read the most halo, gains 1 to 3% from early
+        // loads all the same: MI355X 256^3 593 us after the barrier, 580
+        // before it, 512^3 4750 and 4670; the other shapes lose.)
+        if constexpr (EARLY)
+            if (MEAS || z + 2 < z1) prefetch(z + 1, q);
         if constexpr (!MEAS) __builtin_amdgcn_s_waitcnt(kWaitVm0);
         __syncthreads();
-        if constexpr (!MEAS)
+        if constexpr (!EARLY)
             if (z + 2 < z1) prefetch(z + 1, q);
         const int t = s0;
         s0 = s1;
