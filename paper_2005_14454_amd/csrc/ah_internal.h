@@ -176,9 +176,15 @@ int resident_per_cu(int kernel, int precision, int tx, int ty, bool measured);
 // Automatic z-chunk of a tiled launch.
 int auto_zchunk(int kernel, int precision, int N, int tx, int ty, bool measured);
 int start_planes(int kernel, int tx, int ty);
-// Tiling of the two-step passes of an automatic configuration; false if it
-// takes none.
-bool default_two(int precision, int N, TileConfig* two);
+// Whether two-step passes are the faster way to take two plain steps of a
+// lattice without a tuning entry, alone or in a pool: FP32 at every size, FP64
+// from N = 65 on (MI355X, us per step, two-step / single: FP32 24^3 4.9 / 5.6,
+// 48^3 5.8 / 6.2, 64^3 6.7 / 7.0, 192^3 78 / 116, 512^3 1283 / 1998; FP64 32^3
+// 9.5 / 8.7, 64^3 13.2 / 12.0: its pass's longer start is not paid for by two
+// planes a chunk; 75^3 25.8 / 27.2, 512^3 3610 / 4490).
+inline bool two_step_pays(int precision, int N) { return precision == AH_FP32 || N > 64; }
+// Tiling of the two-step passes of an automatic configuration (zchunk 0: none).
+TileConfig default_two(int precision, int N);
 // Tiling of the measured march of a lattice stepped with cfg (resolved).
 TileConfig measured_tiling(const ah_params& p, const ah_step_config& cfg);
 

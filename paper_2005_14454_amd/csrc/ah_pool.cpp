@@ -757,10 +757,13 @@ int ah_pool_create(size_t hbm_budget, int32_t max_slots, void* hip_stream, ah_po
 // shape, with the automatic z-chunk), else the default, as for a lattice run
 // alone; z-chunks of at least 16 planes.  The measured node runs the
 // measured march's tiling (measured_tiling), as a lattice alone does.
-// Lattices also take two-step passes wherever neither of two snapshots is
-// due (two), with z-chunks by what is in the pool (two_step_chunks), on the tuned
-// two-step tile shape, else 64 x 8 for FP32 and 32 x 8 for FP64; FP64 ones
-// from N = 65 on, as a lattice alone (default_two).
+// Where two-step passes pay (two_step_pays), or with a two-step entry, lattices
+// take them wherever neither of two snapshots is due (two), with z-chunks by
+// what is in the pool (two_step_chunks), on the tuned two-step tile shape, else
+// 64 x 8 for FP32 and 32 x 8 for FP64: a lattice alone may do better on 32 x 8
+// in FP32 too (default_two), as 64 x 8 leaves it too few workgroups, but a pool
+// then has a second node for them, and the two run one after the other (an
+// ensemble and a stream were no faster with 32 x 8 for small or all lattices).
 // The pool supplies much of the parallelism that short z-chunks buy a
 // lattice run alone; 16 planes keep enough work items for ensembles of small
 // lattices (measured on MI355X: 128 lattices of N in {32, 48, 64} run 11%
@@ -770,7 +773,7 @@ static int pool_config(const ah_params& p, ah_step_config* cfg, TileConfig* two,
 {
     ah_step_config t{AH_KERNEL_TILE, 0, 0, 0};
     int two_tx = p.precision == AH_FP64 ? 32 : 64, two_ty = 8;
-    bool take_two = p.precision == AH_FP32 || p.N > 64;
+    bool take_two = two_step_pays(p.precision, p.N);
     if (tuned_config(p, &t)) {
         if (t.kernel == AH_KERNEL_TILE2) {
             two_tx = t.tile_x;

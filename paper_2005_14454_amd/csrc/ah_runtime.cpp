@@ -594,29 +594,25 @@ int auto_zchunk(int kernel, int precision, int N, int tx, int ty, bool measured)
     return best_zc;
 }
 
-// Two-step passes of an automatic configuration: where they are the faster way
-// to take two plain steps, FP32 at every size, FP64 from N = 65 on (MI355X, us
-// per step, two-step / single: FP32 24^3 4.9 / 5.6, 48^3 5.8 / 6.2, 64^3 6.7 /
-// 7.0, 192^3 78 / 116, 512^3 1283 / 1998; FP64 32^3 9.5 / 8.7, 64^3 13.2 / 12.0:
-// its pass's longer start is not paid for by two planes a chunk; 75^3 25.8 /
-// 27.2, 512^3 3610 / 4490).  FP64 on 32 x 8 (64 x 4 spills); FP32 on 64 x 8 or
-// 32 x 8, whichever the estimate says is faster (a plane takes a workgroup
-// alone on its CU 1.5 times as long on 64 x 8).
-bool default_two(int precision, int N, TileConfig* two)
+// Two-step passes of an automatic configuration, where they pay: FP64 on 32 x 8
+// (MI355X, 512^3: 3640 us a step, 64 x 4 5310); FP32 on 64 x 8 or 32 x 8,
+// whichever the estimate says is faster (a plane takes a workgroup alone on its
+// CU 1.5 times as long on 64 x 8).
+TileConfig default_two(int precision, int N)
 {
-    *two = TileConfig{0, 0, 0};
-    if (precision == AH_FP64 && N <= 64) return false;
+    TileConfig two{0, 0, 0};
+    if (!two_step_pays(precision, N)) return two;
     double best = 0.0;
     for (const int tx : {64, 32}) {
         if (!tile2_supported(precision, tx, 8)) continue;
         const int zc = auto_zchunk(AH_KERNEL_TILE2, precision, N, tx, 8, false);
         const double t = launch_estimate(AH_KERNEL_TILE2, precision, N, tx, 8, false, zc, nullptr) * (tx == 64 ? 1.5 : 1.0);
-        if (two->zchunk == 0 || t < best) {
+        if (two.zchunk == 0 || t < best) {
             best = t;
-            *two = TileConfig{tx, 8, zc};
+            two = TileConfig{tx, 8, zc};
         }
     }
-    return true;
+    return two;
 }
 
 // Any tile shape computes the same fields bit for bit, so the measured march
@@ -757,7 +753,7 @@ int resolve_config(const ah_params& p, const ah_step_config& in, ah_step_config*
             if (rc == AH_OK && out->kernel == AH_KERNEL_TILE2) *two = TileConfig{out->tile_x, out->tile_y, out->zchunk};
             return rc;
         }
-        (void)default_two(p.precision, p.N, two);
+        *two = default_two(p.precision, p.N);
     }
     return resolve_step_config(p, in, out, why);
 }
