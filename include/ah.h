@@ -144,7 +144,15 @@ int ah_create(const ah_params* p, void* dev_arena, size_t arena_bytes, void* hip
 int ah_init(ah_handle* h, uint64_t seed);
 
 /* Upload a host FP64 SoA state (10*N^3 doubles, see conventions) as snapshot
- * `step` (>= 0).  Values are rounded to the storage type.  Synchronous. */
+ * `step` (>= 0).  Values are rounded to the storage type.  Synchronous.
+ *
+ * This call, ah_get_state, ah_gather and ah_get_winding go through pinned host
+ * memory: 128 KB that every handle has, and for more than fits there staging
+ * memory of the handle's own, an eighth of its fields but 512 KB to 4 MB,
+ * allocated by the first such call and kept until ah_destroy (if it cannot be
+ * had, the 128 KB serve, more slowly).  From 16 MB of host data on up to three
+ * helper threads (one here), which end with the call, convert beside the
+ * calling one; none on hipStreamPerThread. */
 int ah_set_state(ah_handle* h, const double* host_soa, int64_t step);
 
 /* Download the current snapshot as FP64 SoA (10*N^3 doubles) and its step
@@ -154,9 +162,8 @@ int ah_get_state(ah_handle* h, double* host_soa, int64_t* step);
 /* Values of the current snapshot at `count` listed site indices (each in
  * [0, N^3), else AH_E_INVAL before any device work): host_out[10*k + c] is
  * component c (state order) of site sites[k], widened to FP64.  For
- * spot-checking lattices too large to download.  Goes through the handle's
- * pinned staging memory (2 MB, allocated by the first call that needs it, as
- * for the state calls above).  Synchronous. */
+ * spot-checking lattices too large to download.  Goes through pinned memory as
+ * ah_set_state does, in pieces where the values do not fit.  Synchronous. */
 int ah_gather(ah_handle* h, const int64_t* sites, int64_t count, double* host_out);
 
 /* ah_gather without allocation, for callers that cannot allocate device
@@ -202,14 +209,19 @@ int ah_get_timing_split(ah_handle* h, double* measured_ms, int64_t* measured_lau
 
 /* All diagnostics of the current snapshot, summed in FP64 in a fixed order
  * (bitwise reproducible for a given handle configuration).  Site densities
- * are formed in the storage precision; link phases, plaquette angles and
- * windings in FP64 from the stored values, so windings are exact for FP32
- * lattices too.  The snapshot is not modified.  Synchronous. */
+ * are formed in the storage precision; plaquette angles, and their sum with
+ * the link phases that a winding rounds, in FP64 from the stored values.  A link
+ * phase is that of the FP64 definition to well within what the rounding can
+ * tell, its branch decided in FP64 wherever FP32 could leave it in doubt, so
+ * windings are exact for FP32 lattices too.  The snapshot is not modified.
+ * Synchronous. */
 int ah_measure(ah_handle* h, ah_measurement* out);
 
 /* Per-plaquette windings of the current snapshot: 3*N^3 int8 values,
- * orientation-major ((0,1), (0,2), (1,2)), site index inside.  Allocates a
- * temporary device buffer of 3*N^3 bytes.  Synchronous. */
+ * orientation-major ((0,1), (0,2), (1,2)), site index inside.  They are formed
+ * in the Pi and E buffers that the snapshot is not in, whose contents are lost
+ * (the next step would overwrite them), and downloaded through pinned memory as
+ * by ah_get_state; no device memory is allocated.  Synchronous. */
 int ah_get_winding(ah_handle* h, int8_t* host_w);
 
 /* ------------------------------------------------------ step kernel choice */
@@ -280,7 +292,8 @@ int ah_tune_lookup(const ah_params* p, ah_step_config* out);
 /* Record a choice by hand: kernel AH_KERNEL_TILE or AH_KERNEL_TILE2, a tile
  * shape that kernel supports for the precision, zchunk 0 (automatic) or at
  * least the minimum of ah_step_config.zchunk; AH_E_INVAL otherwise.  Pool
- * lattices take the tile shape of a two-step entry and step once per replay. */
+ * lattices take the tile shape of a two-step entry for their two-step passes,
+ * and for their single steps if those are built for it. */
 int ah_tune_set(const ah_params* p, const ah_step_config* c);
 
 /* Forget every recorded choice. */
@@ -314,9 +327,11 @@ int ah_tune_load(const char* path);
  * Every lattice takes the coefficients of its own step from its own FP64 table,
  * so its fields and diagnostics are bitwise identical to the same lattice run
  * alone through ah_step / ah_measure with the same tiling.  Requests enter and
- * leave between advances (continuous batching); the graphs are captured again
- * only when a node's work list outgrows its capacity (or shrinks far below it)
- * or a new node is needed.  A pool is used from one host thread at a time. */
+ * leave between advances (continuous batching).  A graph is captured for each
+ * set of nodes that has work in a replay, when it is first needed, and the nodes
+ * are laid out anew, and their graphs with them, only when a node's work list
+ * outgrows its capacity (or shrinks far below it) or a new node is needed.  A
+ * pool is used from one host thread at a time. */
 typedef struct ah_pool ah_pool;
 
 typedef struct ah_pool_info {
@@ -351,12 +366,14 @@ int ah_pool_footprint(const ah_params* p, int64_t nsteps, int32_t measure_every,
 int ah_pool_submit(ah_pool* pool, const ah_params* p, uint64_t seed, int64_t nsteps, int32_t measure_every,
                    int64_t* id);
 
-/* Enqueue nsteps graph replays (one step of every active lattice each) and a
- * copy of the step counters behind them.  Asynchronous, with at most eight
- * replays queued ahead of the host: past that it waits until the GPU has
- * reached a replay four or more behind the newest (never for the whole
- * queue).  A set of lattices changed by submit or results gets a new graph
- * here, built while earlier replays still run. */
+/* Enqueue nsteps graph replays (one step, or one two-step pass, of every active
+ * lattice each) and an event behind them; the steps each lattice has taken by
+ * then follow from its request, so the host counts them itself.  Asynchronous,
+ * with at most eight replays queued ahead of the host: past that it waits until
+ * the GPU has reached a replay four or more behind the newest (never for the
+ * whole queue).  Work lists changed by submit or results are queued here, and a
+ * set of nodes not replayed before gets its graph, while earlier replays still
+ * run. */
 int ah_pool_advance(ah_pool* pool, int32_t nsteps);
 
 /* Ids of lattices that finished since the last poll (at most cap; *n is the
@@ -371,8 +388,9 @@ int ah_pool_poll_async(ah_pool* pool, int64_t* done_ids, int32_t cap, int32_t* n
 
 /* Tile shape and z-chunk a request is stepped with (kernel AH_KERNEL_TILE).
  * The pool takes the tuned configuration of the request's (precision, N), or
- * the default one, with z-chunks of at least 16 planes and one tile shape
- * for its plain and measured steps.  Host only.  AH_E_INVAL for an unknown id. */
+ * the default one, with z-chunks of at least 16 planes; a lattice alone with
+ * this configuration has the same measured steps too.  Host only.  AH_E_INVAL
+ * for an unknown id. */
 int ah_pool_step_config(const ah_pool* pool, int64_t id, ah_step_config* out);
 
 /* Current step of a request and its target (nsteps may be NULL). */

@@ -410,7 +410,7 @@ class Pool:
         return [ids[k] for k in range(n.value)]
 
     def poll_async(self, cap: int = 4096):
-        """Finished lattices the newest counter copy on the host shows (no wait)."""
+        """Finished lattices as of the newest event the GPU has passed (no wait)."""
         ids = (ctypes.c_int64 * cap)()
         n = ctypes.c_int32()
         self._call(self._lib.ah_pool_poll_async, ids, cap, ctypes.byref(n), what="ah_pool_poll_async")

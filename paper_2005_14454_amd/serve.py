@@ -10,7 +10,8 @@ on the host; time-to-completion (TTC) runs from arrival to that moment.
 
 The loop never waits for the GPU to drain: each advance queues one replay
 (the pool keeps up to eight queued, waiting only for older ones), finished
-requests are found from counter copies that land behind the replays, and
+requests are found from the pool's own step counts as of the newest event
+that the GPU has passed behind the replays, and
 admissions and series downloads are queued or run beside them.
 
 `python -m paper_2005_14454_amd.serve --requests 500` runs the full stream;
