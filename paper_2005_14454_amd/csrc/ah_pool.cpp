@@ -33,7 +33,6 @@
 #include <cstdint>
 #include <cstring>
 #include <deque>
-#include <functional>
 #include <map>
 #include <new>
 #include <string>
@@ -392,51 +391,81 @@ hipError_t retire_graphs(ah_pool* P)
     return hipSuccess;
 }
 
-// z-chunk of every lattice of one two-step node, by side N: the cap on the
-// planes of a chunk (or none: each lattice's z-chunk of its own, which alone
-// fills the chip best) for which the node's items, longest first, fill the
-// chip's workgroup places in the least time.  Forty-eight lattices of 32^3 ..
-// 64^3 FP32 fill it best on chunks of 16 planes (MI355X, an ensemble: 10.4 ms,
-// 11.3 on 8 planes, 12.2 on 32), five of 52^3 .. 131^3 on shorter ones (a
-// stream of 11 requests: 13.2 ms on 16 planes, 12.1 by this rule).  The fields
-// do not depend on it.
-std::map<int, int> two_step_chunks(int precision, int tx, int ty, const std::map<int, int>& count)
+// Lattices of one side in a two-step node: how many, the z-chunk that one alone
+// fills the chip best with, and the one the node runs them with.
+struct SideCount {
+    int N, own, zchunk;
+    int64_t count;
+};
+// z-chunks of the lattices of one two-step node: the cap on the planes of a
+// chunk (or none: each lattice's own) for which the node's items, longest first,
+// fill the chip's workgroup places in the least time.  Forty-eight lattices of
+// 32^3 .. 64^3 FP32 fill it best on chunks of 16 planes (MI355X, an ensemble:
+// 10.4 ms, 11.3 on 8 planes, 12.2 on 32), five of 52^3 .. 131^3 on shorter ones
+// (a stream of 11 requests: 13.2 ms on 16 planes, 12.1 by this rule).  The fields
+// do not depend on it.  Runs at every admission and release, so it takes each
+// lattice's own z-chunk from its slot, leaves out caps that cannot do better and
+// keeps to small arrays (60 lattices of as many sides: 20 us of host time; with
+// maps and every cap followed through 90).
+void two_step_chunks(int precision, int tx, int ty, std::vector<SideCount>& sides)
 {
-    const int places = 256 * resident_per_cu(AH_KERNEL_TILE2, precision, tx, ty, false);
+    const int64_t places = 256 * resident_per_cu(AH_KERNEL_TILE2, precision, tx, ty, false);
     const int start = start_planes(AH_KERNEL_TILE2, tx, ty);
-    std::map<int, int> best, own;
-    for (auto& kv : count) own[kv.first] = auto_zchunk(AH_KERNEL_TILE2, precision, kv.first, tx, ty, false);
+    std::vector<int> zc(sides.size()), last;
+    std::vector<std::pair<int64_t, int64_t>> items, free_at;  // (planes, how many), (time, places)
+    const auto later = [](const std::pair<int64_t, int64_t>& x, const std::pair<int64_t, int64_t>& y) { return x.first > y.first; };
     int64_t best_t = -1;
     for (int cap : {0, 4, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64, 96, 128, 256, 4096}) {
-        std::map<int, int> zc;
-        std::map<int, int64_t, std::greater<int>> items;  // by length in planes
-        for (auto& kv : count) {
-            const int N = kv.first;
-            int c = own[N];
+        for (size_t k = 0; k < sides.size(); ++k) {
+            const int N = sides[k].N;
+            zc[k] = sides[k].own;
             if (cap > 0) {
                 const int most = std::min(std::max(cap, min_zchunk(N)), N), nz = (N + most - 1) / most;
-                c = std::max((N + nz - 1) / nz, std::min(min_zchunk(N), N));
+                zc[k] = std::max((N + nz - 1) / nz, std::min(min_zchunk(N), N));
             }
-            zc[N] = c;
-            items[c + start] += (int64_t)kv.second * ((N + tx - 1) / tx) * ((N + ty - 1) / ty) * ((N + c - 1) / c);
         }
-        // list scheduling: each item to the place that is free first
-        std::map<int64_t, int64_t> free_at{{0, places}};
-        for (auto& it : items)
-            for (int64_t left = it.second; left > 0;) {
-                const auto first = free_at.begin();
-                const int64_t t = first->first, n = std::min(left, first->second);
-                if ((first->second -= n) == 0) free_at.erase(first);
-                free_at[t + it.first] += n;
+        if (zc == last) continue;
+        last = zc;
+        items.clear();
+        int64_t planes = 0;
+        for (size_t k = 0; k < sides.size(); ++k) {
+            const int N = sides[k].N;
+            items.push_back({zc[k] + start,
+                             sides[k].count * ((N + tx - 1) / tx) * ((N + ty - 1) / ty) * ((N + zc[k] - 1) / zc[k])});
+            planes += items.back().first * items.back().second;
+        }
+        const auto no_better = [&](int64_t time) { return best_t >= 0 && time >= best_t; };
+        if (no_better((planes + places - 1) / places)) continue;
+        std::sort(items.begin(), items.end(), later);
+        // list scheduling: each item to the place that is free first (a heap
+        // by time)
+        free_at.assign(1, {0, places});
+        int64_t t = 0;
+        for (const auto& it : items)
+            for (int64_t left = it.second; left > 0 && !no_better(t);) {
+                const int64_t at = free_at.front().first;
+                int64_t have = 0;
+                while (!free_at.empty() && free_at.front().first == at) {
+                    have += free_at.front().second;
+                    std::pop_heap(free_at.begin(), free_at.end(), later);
+                    free_at.pop_back();
+                }
+                const int64_t n = std::min(left, have);
+                const auto put = [&](int64_t when, int64_t how_many) {
+                    if (how_many == 0) return;
+                    free_at.push_back({when, how_many});
+                    std::push_heap(free_at.begin(), free_at.end(), later);
+                };
+                put(at, have - n);
+                put(at + it.first, n);
+                t = std::max(t, at + it.first);
                 left -= n;
             }
-        const int64_t t = free_at.rbegin()->first;
-        if (best_t < 0 || t < best_t) {
+        if (!no_better(t)) {
             best_t = t;
-            best = zc;
+            for (size_t k = 0; k < sides.size(); ++k) sides[k].zchunk = zc[k];
         }
     }
-    return best;
 }
 
 // Rebuild descriptors and work lists, and the per-step graph when its
@@ -480,10 +509,20 @@ int rebuild(ah_pool* P)
     }
     for (auto& kv : by_shape) {
         if (kv.first.kind != 3) continue;
-        std::map<int, int> count;
-        for (int i : kv.second) ++count[P->slots[i].p.N];
-        const std::map<int, int> zc = two_step_chunks(kv.first.precision, kv.first.tx, kv.first.ty, count);
-        for (int i : kv.second) desc[i].two_zchunk = P->slots[i].d.two_zchunk = zc.at(P->slots[i].p.N);
+        std::vector<int> by_side = kv.second;
+        std::sort(by_side.begin(), by_side.end(), [&](int a, int b) { return P->slots[a].p.N < P->slots[b].p.N; });
+        std::vector<SideCount> sides;
+        for (int i : by_side) {
+            const Slot& s = P->slots[i];
+            if (sides.empty() || sides.back().N != s.p.N) sides.push_back({s.p.N, s.two.zchunk, s.two.zchunk, 0});
+            sides.back().count += 1;
+        }
+        two_step_chunks(kv.first.precision, kv.first.tx, kv.first.ty, sides);
+        size_t at = 0;
+        for (int i : by_side) {
+            if (sides[at].N != P->slots[i].p.N) ++at;
+            desc[i].two_zchunk = P->slots[i].d.two_zchunk = sides[at].zchunk;
+        }
     }
     // The step kernels run one block per item and give XCD x (which runs
     // blocks x, x+8, ...) the x-th eighth of the list.  So that every XCD
@@ -515,12 +554,13 @@ int rebuild(ah_pool* P)
             const int nt = tiles_of(d) * tiles_z;
             const int planes = std::min(zc_of(d), d.N);
             auto run = [&](int x) { return (int)((int64_t)nt * x / kXcdCount); };  // first tile of run x
+            std::array<int64_t, kXcdCount> len;                                      // planes in run x
+            for (int x = 0; x < kXcdCount; ++x) len[x] = (int64_t)(run(x + 1) - run(x)) * planes;
             int shift = 0;
             int64_t least = -1;
             for (int c = 0; c < kXcdCount && nt % kXcdCount != 0; ++c) {
                 int64_t most = 0;
-                for (int x = 0; x < kXcdCount; ++x)
-                    most = std::max(most, load[(x + c) % kXcdCount] + (int64_t)(run(x + 1) - run(x)) * planes);
+                for (int x = 0; x < kXcdCount; ++x) most = std::max(most, load[(x + c) % kXcdCount] + len[x]);
                 if (least < 0 || most < least) {
                     least = most;
                     shift = c;
@@ -528,8 +568,11 @@ int rebuild(ah_pool* P)
             }
             for (int x = 0; x < kXcdCount; ++x) {
                 const int to = (x + shift) % kXcdCount;
-                load[to] += (int64_t)(run(x + 1) - run(x)) * planes;
-                for (int t = run(x); t < run(x + 1); ++t) band[to].push_back({i, t});
+                load[to] += len[x];
+                std::vector<WorkItem>& list = band[to];
+                size_t at = list.size();
+                list.resize(at + (run(x + 1) - run(x)));
+                for (int t = run(x), end = run(x + 1); t < end; ++t) list[at++] = {i, t};
             }
         }
     }
