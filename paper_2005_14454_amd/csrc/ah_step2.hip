@@ -20,8 +20,8 @@
 //
 // What bounds it: instruction issue and latency (512^3 FP32 on 64 x 8 tiles,
 // one 11-wave workgroup per CU: vector ALU busy 77%; HBM 4.8 TB/s).  MI355X,
-// us per step: 512^3 FP32 64 x 8 1283 (up to 1410 between cards), FP64 32 x 8
-// 3610 (3800); comparisons here and below are on one card.  Stage 2 one plane
+// us per step in runs of a few steps, as all comparisons here: 512^3 FP32 64 x 8
+// 1283, FP64 32 x 8 3610 (1400 and 3800 over 200 steps).  Stage 2 one plane
 // behind stage 1 with a barrier behind each of them (half the LDS, two
 // barriers a plane) took 1677 and 4420 where this form took 1468 and 3774,
 // before the values in LDS were paired (Pair, ah_stencil.h); stage 2 before stage 1 within a
